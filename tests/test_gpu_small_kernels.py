@@ -1,0 +1,55 @@
+"""Edges of the kernels for small problems against numpy in 64 bits: sizes at
+the tile, wave and LDS limits where each kernel's code changes."""
+import numpy as np
+import pytest
+
+from paper_2512_23917_amd import synth
+from gpu_util import isometry_err
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+U64 = 2.0 ** -53
+
+
+@pytest.fixture(scope="module")
+def T():
+    from paper_2512_23917_amd import tci
+    return tci
+
+
+@pytest.fixture(scope="module")
+def ctx(T):
+    c = T.Context(0)
+    yield c
+    c.close()
+
+
+def draw(shape, complex_, seed):
+    g = synth.rng(31, seed)
+    return synth.complex_gaussian(g, shape) if complex_ else synth.real_gaussian(g, shape)
+
+
+# 32 / 33: threads per workgroup; 16 | 17 rows: lanes of a pair; 64 x 80 and 64 x 81 (complex), 64 x 224 and
+# 225 (real): the largest matrices held in LDS and the smallest that are not; 1 and 2: no pair and one pair
+@pytest.mark.parametrize("complex_,m,n", [(True, 1, 1), (True, 2, 5), (False, 3, 3), (True, 17, 16), (True, 31, 32),
+                                          (True, 33, 33), (True, 64, 80), (True, 81, 64), (True, 300, 63),
+                                          (False, 224, 64), (False, 64, 225), (False, 1000, 64), (True, 40, 5)])
+def test_jacobi_svd_edges(T, ctx, complex_, m, n):
+    """Each pair ends with |<a_p, a_q>| <= max(m, n) u |a_p||a_q|, so an isometry defect is at most a few of
+    that; the at most 64 rotations per sweep and column leave about 1e-14 in the product of 15 sweeps."""
+    a = draw((m, n), complex_, 1000 * m + n)
+    u, s, vh = T.svd(ctx, T.Tensor.from_numpy(ctx, a, T.C128 if complex_ else T.F64), 1)
+    u, s, vh = u.numpy(), s.numpy(), vh.numpy()
+    tol = 1e-13 + 4 * max(m, n) * U64
+    assert np.abs(s - np.linalg.svd(a, compute_uv=False)).max() < tol * s[0]
+    assert np.linalg.norm((u * s) @ vh - a) < tol * np.linalg.norm(a)
+    assert isometry_err(u) < tol and isometry_err(vh, False) < tol
+
+
+@pytest.mark.parametrize("scale", [1e-100, 1e100])
+def test_jacobi_svd_far_from_one(T, ctx, scale):
+    """Real matrices whose squared inner products leave the exponent range."""
+    a = draw((20, 12), False, 5) * scale
+    u, s, vh = T.svd(ctx, T.Tensor.from_numpy(ctx, a, T.F64), 1)
+    assert np.abs(s.numpy() - np.linalg.svd(a, compute_uv=False)).max() < 1e-13 * s.numpy()[0]
+    assert isometry_err(u.numpy()) < 1e-13
