@@ -143,6 +143,58 @@ __device__ inline T quad_sum(T v) {
   }
 }
 
+// Sum over the 16 lanes of a DPP row; every lane receives the total.
+template <int CTRL>
+__device__ inline double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ inline double row16_sum(double v) {
+  v = dpp_add<0xB1>(v);     // quad_perm [1,0,3,2]
+  v = dpp_add<0x4E>(v);     // quad_perm [2,3,0,1]
+  v = dpp_add<0x141>(v);    // row_half_mirror
+  return dpp_add<0x140>(v); // row_mirror
+}
+__device__ inline cd row16_sum(cd v) { return cd{row16_sum(v.x), row16_sum(v.y)}; }
+
+// v + (v of the lane whose number differs in bit 4, or bit 5), by the lane
+// swaps between rows: no LDS round trip as in __shfl_xor.
+__device__ inline double xor16_add(double v) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline double xor32_add(double v) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// sum over the lanes of a wave that share lane % 16, and over the whole wave
+__device__ inline double quarter_sum(double v) { return xor32_add(xor16_add(v)); }
+__device__ inline cd quarter_sum(cd v) { return cd{quarter_sum(v.x), quarter_sum(v.y)}; }
+// Sums of four values over the lanes that share lane % 16: lane l receives the
+// sum of value l / 16.  A lane swap between two different values sums both at
+// once, so the four need three swaps where separate sums need eight.
+__device__ inline double swap16_sum(double a, double b) {   // rows 0, 2: a over two rows; 1, 3: b
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline double swap32_sum(double a, double b) {   // lanes 0..31: a over the two halves; 32..63: b
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline double quarter_sum4(const double (&v)[4]) {
+  return swap32_sum(swap16_sum(v[0], v[1]), swap16_sum(v[2], v[3]));
+}
+__device__ inline cd quarter_sum4(const cd (&v)[4]) {
+  return cd{swap32_sum(swap16_sum(v[0].x, v[1].x), swap16_sum(v[2].x, v[3].x)),
+            swap32_sum(swap16_sum(v[0].y, v[1].y), swap16_sum(v[2].y, v[3].y))};
+}
+template <typename T> __device__ inline T wave64_sum(T v) { return quarter_sum(row16_sum(v)); }
+
 // Reflector scalars from ||x(i+2:n)||^2 and alpha = x(i+1).
 template <typename T>
 __device__ inline void reflector(T alpha, double xn2, double& beta, T& tau, T& scal) {
@@ -519,13 +571,21 @@ __global__ __launch_bounds__(256) void tri_cat_kernel(TriArgs a, int j0, int pe,
   }
 }
 
+// Largest order of a matrix that tri_chip_kernel (below) holds on chip.
+template <typename T> constexpr int TRI_CHIP_N = sizeof(T) == 16 ? 192 : 320;
+template <typename T> static void tri_chip(const TriArgs& a, int i0, int batch, hipStream_t s);
+
 template <typename T, int NB>
 static hipError_t tridiag_impl(const TriArgs& a, int batch, hipStream_t s) {
   const int n = a.n;
   const size_t es = sizeof(T);
   const int nbt = TriWs<T, NB>::nbt(n);
-  for (int j0 = 0; j0 < n; j0 += NB) {
-    const int pe = min(NB, n - j0);
+  for (int j0 = 0, pe; j0 < n; j0 += pe) {
+    if (n - j0 <= TRI_CHIP_N<T>) {   // the rest fits on chip: one launch
+      tri_chip<T>(a, j0, batch, s);
+      break;
+    }
+    pe = min(NB, n - TRI_CHIP_N<T> - j0);   // the last panel leaves the largest order that fits
     for (int p = 0; p < pe; ++p) {
       const int i = j0 + p;
       const int rowsA = n - i;
@@ -565,170 +625,252 @@ static hipError_t tridiag_impl(const TriArgs& a, int batch, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Small matrices (n <= TRI_SMALL_N): the unblocked reduction (LAPACK hetd2
-// order, lower storage) by one 1024-thread workgroup per matrix, all columns
-// in one launch.  The blocked path pays two launches per column, which for
-// n of a few hundred is latency, not bandwidth; here the trailing matrix
-// (at most 2.4 MB) stays in the caches across columns.  Above 384 one
-// compute unit no longer streams the matrix fast enough (measured at
-// n = 512 on 15 complex problems: 33 ms against 27 ms blocked).  Per column i:
-//   reflector of a(i+1:n, i) (same convention as the blocked path);
-//   y = A22 v over the lower triangle: wave w takes rows i+1+w, +16, ...,
-//     its lanes the row's columns; row sums by a wave reduction, the
-//     transposed terms conj(a_rc) v_r by LDS atomics into y_c;
-//   w = tau y - 1/2 |tau|^2 (y^H v) v;  A22 -= v w^H + w v^H (lower triangle).
-// Outputs as the blocked path: d, e, tau and the reflector rows of Vt.
+// Unblocked reduction (LAPACK hetd2 order, lower storage) of a trailing matrix
+// of order nt = n - i0 held on chip: rows and columns i0 .. n-1 of G, at most
+// 32 NB of them, by one 512-thread workgroup per matrix, all columns in one
+// launch; the blocked path pays two launches per column, which at these orders
+// is latency.  Outputs as the blocked path: d, e, tau, reflector rows of Vt.  Thread (ty, tx) = (tid / 16, tid % 16)
+// keeps the elements (32 I + ty, 16 J + tx) of the lower triangle, the slices
+// J < JL (which are finished first) in LDS and the others in registers, so
+// that a column touches no memory but its reflector row of Vt.  Per column:
+//   the column goes to LDS; every wave forms the reflector from it;
+//   y = A v: row sums over the 16 lanes of a row (DPP), column sums over the
+//     4 rows of a wave, then over the 8 waves through LDS;
+//   w = tau y - 1/2 tau (tau y)^H v v;  A -= v w^H + w v^H.
+// Rows and columns <= i of the stored matrix are dead: v and w are zero there,
+// and v is written to LDS once so that no use of it needs a select.
+// Bound by LDS reads of the vectors and by the latency of a column (four
+// barriers): 4.5 us per column at order 192 complex (0.87 ms per launch), 1.9 us
+// at 100 real (0.19 ms).  The same reduction from global memory by one
+// workgroup took 15 and 5.8 us per column (16 problems of order 200 complex
+// 3.07 ms, one of order 100 real 0.58 ms).
 // ---------------------------------------------------------------------------
-constexpr int TRI_SMALL_N = 384;
-
+// Reflector scalars as in reflector(), without the division and square-root
+// sequences, which a column would wait for: refined hardware seeds.
+__device__ inline double rsqrt_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = __builtin_fma(y * 0.5, __builtin_fma(-x * y, y, 1.0), y);
+  return y;
+}
+__device__ inline double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+  return y;
+}
 template <typename T>
-__global__ __launch_bounds__(1024) void tri_small_kernel(TriArgs a) {
-  constexpr int NT = 1024, NW = NT / 64;
-  __shared__ T s_v[TRI_SMALL_N];
-  __shared__ double s_yr[TRI_SMALL_N], s_yi[TRI_SMALL_N];
-  __shared__ double s_red[NW], s_red2[NW];
-  __shared__ T s_scal, s_tau;
-  __shared__ double s_alr, s_ali;
-  const int b = blockIdx.x, n = a.n, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  T* G = reinterpret_cast<T*>(a.G) + b * a.sG;
-  T* V = reinterpret_cast<T*>(a.Vt) + b * a.sVt;
-  T* tau = reinterpret_cast<T*>(a.tau) + b * a.stau;
-  double* dd = a.d + b * a.sde;
-  double* ee = a.e + b * a.sde;
+__device__ inline void reflector_nr(T alpha, double xn2, double& beta, T& tau, T& scal) {
+  const double ar = re(alpha), ai = im(alpha), sum = ar * ar + ai * ai + xn2;
+  if ((xn2 == 0.0 && ai == 0.0) || !(sum > 1e-280 && sum < 1e280)) {
+    reflector(alpha, xn2, beta, tau, scal);
+    return;
+  }
+  const double rs = rsqrt_nr(sum), sg = ar >= 0.0 ? -1.0 : 1.0, ib = sg * rs;
+  beta = sum * ib;
+  const double xr = ar - beta;
+  if constexpr (sizeof(T) == sizeof(double)) {
+    tau = -xr * ib;
+    scal = rcp_nr(xr);
+  } else {
+    const double iden = rcp_nr(xr * xr + ai * ai);
+    tau = cd{-xr * ib, -ai * ib};
+    scal = cd{xr * iden, -ai * iden};
+  }
+}
+
+// acc + a b, acc + conj(a) b, acc - a conj(b) with fused multiply-adds only
+__device__ inline double mac(double c, double a, double b) { return __builtin_fma(a, b, c); }
+__device__ inline double mac_cj(double c, double a, double b) { return __builtin_fma(a, b, c); }
+__device__ inline double msub_cj(double c, double a, double b) { return __builtin_fma(-a, b, c); }
+__device__ inline cd mac(cd c, cd a, cd b) {
+  return cd{__builtin_fma(-a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
+}
+__device__ inline cd mac_cj(cd c, cd a, cd b) {
+  return cd{__builtin_fma(a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(-a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
+}
+__device__ inline cd msub_cj(cd c, cd a, cd b) {
+  return cd{__builtin_fma(-a.y, b.y, __builtin_fma(-a.x, b.x, c.x)), __builtin_fma(-a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
+}
+
+// Barrier for data exchanged through LDS only: __syncthreads would also wait
+// for the column's stores to global memory, a memory round trip per barrier.
+__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <typename T, int NB, int JL>
+__global__ __launch_bounds__(512) void tri_chip_kernel(TriArgs a, int i0) {
+  constexpr int NT = 512, NW = NT / 64, NC = 2 * NB, NN = 32 * NB, JC = 4;
+  // row block I has the slices J < 2 I + 2, of which min(JL, 2 I + 2) are in LDS
+  constexpr int SKIP0 = JL > 2 ? JL - 2 : 0, NREG = NB * (NB + 1) - JL * NB + SKIP0;
+  static_assert(JL <= 4, "only row block 0 may have fewer than JL slices");
+  __shared__ T s_l[JL > 0 ? JL * NB * NT : 1];
+  __shared__ T s_x[NN], s_v[NN], s_w[NN], s_row[NN], s_part[NW][NN];
+  __shared__ T s_dot[NW];
+  const int b = blockIdx.x, n = a.n, nt = n - i0, tid = threadIdx.x;
+  const int tx = tid & 15, ty = tid >> 4, lane = tid & 63, wid = tid >> 6;
   const long ldg = a.ldg;
-  for (int i = 0; i + 1 < n; ++i) {
-    // ||a(i+2:n, i)||^2
-    double part = 0.0;
-    for (int r = i + 2 + tid; r < n; r += NT) part += nrm2(G[(long)r * ldg + i]);
-    part = wave_sum(part);
-    if (lane == 0) s_red[wid] = part;
-    __syncthreads();
+  T* G = reinterpret_cast<T*>(a.G) + b * a.sG + (long)i0 * ldg + i0;
+  T* V = reinterpret_cast<T*>(a.Vt) + b * a.sVt + (long)i0 * n;
+  T* tau = reinterpret_cast<T*>(a.tau) + b * a.stau + i0;
+  double* dd = a.d + b * a.sde + i0;
+  double* ee = a.e + b * a.sde + i0;
+  T areg[NREG];
+  auto slot = [](int I, int J) constexpr { return I * (I + 1) - JL * I + SKIP0 + (J - JL); };
+  auto get = [&](int I, int J) -> T { return J < JL ? s_l[(I * JL + J) * NT + tid] : areg[J < JL ? 0 : slot(I, J)]; };
+  auto put = [&](int I, int J, T v) {
+    if (J < JL) s_l[(I * JL + J) * NT + tid] = v;
+    else areg[J < JL ? 0 : slot(I, J)] = v;
+  };
+#pragma unroll
+  for (int J = 0; J < NC; ++J)
+#pragma unroll
+    for (int I = J / 2; I < NB; ++I) {
+      const int r = 32 * I + ty, c = 16 * J + tx;
+      put(I, J, (r < nt && c <= r) ? G[r * ldg + c] : EigT<T>::zero());
+    }
+#pragma unroll 1
+  for (int i = 0; i + 1 < nt; ++i) {
+#pragma unroll
+    for (int J = 0; J < NC; ++J)
+      if (J == i >> 4) {
+        if (tx == (i & 15)) {
+#pragma unroll
+          for (int I = J / 2; I < NB; ++I) s_x[32 * I + ty] = get(I, J);
+        }
+      }
+    lds_barrier();
+    // ||x(i+2:)||^2 and the reflector, by every wave
+    double xn2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < NN / 64; ++k) {
+      const int r = lane + 64 * k;
+      const double t = nrm2(s_x[r]);
+      xn2 += r >= i + 2 && r < nt ? t : 0.0;
+    }
+    xn2 = wave64_sum(xn2);
+    double beta;
+    T tv, scal;
+    reflector_nr(s_x[i + 1], xn2, beta, tv, scal);
     if (tid == 0) {
-      double xn2 = 0.0;
-      for (int w = 0; w < NW; ++w) xn2 += s_red[w];
-      double beta;
-      T tv, sc;
-      reflector(G[(long)(i + 1) * ldg + i], xn2, beta, tv, sc);
-      s_scal = sc;
-      s_tau = tv;
-      dd[i] = re(G[(long)i * ldg + i]);
+      dd[i] = re(s_x[i]);
       ee[i] = beta;
       tau[i] = tv;
     }
-    __syncthreads();
-    const T scal = s_scal;
-    for (int c = tid; c < n; c += NT) {
-      T v = EigT<T>::zero();
-      if (c == i + 1) v = EigT<T>::one();
-      else if (c > i + 1) v = mulr(G[(long)c * ldg + i], scal);
-      s_v[c] = v;
-      V[(long)i * n + c] = v;
-      s_yr[c] = 0.0;
-      s_yi[c] = 0.0;
+    // v, zero outside i < c < nt, for plain reads of every use
+    if (tid < NN) {
+      T v = mulr(s_x[tid], scal);
+      v = tid <= i || tid >= nt ? EigT<T>::zero() : tid == i + 1 ? EigT<T>::one() : v;
+      s_v[tid] = v;
+      if (tid < nt) V[(long)i * n + i0 + tid] = v;
     }
-    __syncthreads();
-    // y = A22 v (all loads of a row issued before its arithmetic: a row has
-    // at most TRI_SMALL_N / 64 chunks of 64 columns)
-    constexpr int UNR = TRI_SMALL_N / 64;
-    for (int r = i + 1 + wid; r < n; r += NW) {
-      const T vr = s_v[r];
-      T rs = EigT<T>::zero();
-      T g[UNR];
+    for (int c = tid; c < i0; c += NT) V[(long)i * n + c] = EigT<T>::zero();
+    lds_barrier();
+    T vr[NB], acc[NB];
 #pragma unroll
-      for (int m = 0; m < UNR; ++m) {
-        const int c = i + 1 + lane + 64 * m;
-        g[m] = c <= r ? G[(long)r * ldg + c] : EigT<T>::zero();
+    for (int I = 0; I < NB; ++I) {
+      vr[I] = s_v[32 * I + ty];
+      acc[I] = EigT<T>::zero();
+    }
+    // slices in chunks of JC without a branch inside, so that the loads,
+    // products and sums of a chunk overlap
+#pragma unroll
+    for (int J0 = 0; J0 < NC; J0 += JC) {
+      if (16 * (J0 + JC) <= i + 1) continue;
+      T vc[JC], col[JC];
+#pragma unroll
+      for (int k = 0; k < JC; ++k) {
+        vc[k] = s_v[16 * (J0 + k) + tx];
+        col[k] = EigT<T>::zero();
       }
 #pragma unroll
-      for (int m = 0; m < UNR; ++m) {
-        const int c = i + 1 + lane + 64 * m;
-        if (c <= r) {
-          rs = add(rs, mulr(g[m], s_v[c]));
-          if (c < r) {
-            const T t = mulr(cj(g[m]), vr);
-            atomicAdd(&s_yr[c], re(t));
-            if constexpr (sizeof(T) == 16) atomicAdd(&s_yi[c], im(t));
-          }
+      for (int I = J0 / 2; I < NB; ++I)
+#pragma unroll
+        for (int k = 0; k < JC; ++k) {
+          const int J = J0 + k;
+          if (J > 2 * I + 1) continue;
+          const T g = get(I, J);
+          acc[I] = mac(acc[I], g, vc[k]);
+          // an element of the diagonal counts once
+          const T gc = J >= 2 * I && 16 * J + tx == 32 * I + ty ? EigT<T>::zero() : g;
+          col[k] = mac_cj(col[k], gc, vr[I]);
         }
-      }
-      rs = wsum(rs);
-      if (lane == 0) {
-        atomicAdd(&s_yr[r], re(rs));
-        if constexpr (sizeof(T) == 16) atomicAdd(&s_yi[r], im(rs));
-      }
+      s_part[wid][16 * J0 + lane] = quarter_sum4(col);
     }
-    __syncthreads();
-    // w = tau y + alpha v with alpha = -1/2 tau (tau y)^H v
-    const T tv = s_tau;
-    double pr = 0.0, pi = 0.0;
-    for (int c = i + 1 + tid; c < n; c += NT) {
-      T y;
-      if constexpr (sizeof(T) == 16) y = cd{s_yr[c], s_yi[c]};
-      else y = s_yr[c];
-      const T w = mulr(tv, y);
-      const T p = mulr(cj(w), s_v[c]);
-      pr += re(p);
-      pi += im(p);
-    }
-    pr = wave_sum(pr);
-    pi = wave_sum(pi);
-    if (lane == 0) { s_red[wid] = pr; s_red2[wid] = pi; }
-    __syncthreads();
-    if (tid == 0) {
-      double dr = 0.0, di = 0.0;
-      for (int w = 0; w < NW; ++w) { dr += s_red[w]; di += s_red2[w]; }
-      // alpha = -1/2 tau dot
-      if constexpr (sizeof(T) == 16) {
-        const cd al = mulr(tv, cd{dr, di});
-        s_alr = -0.5 * al.x;
-        s_ali = -0.5 * al.y;
-      } else {
-        s_alr = -0.5 * tv * dr;
-        s_ali = 0.0;
-      }
-    }
-    __syncthreads();
-    T alpha;
-    if constexpr (sizeof(T) == 16) alpha = cd{s_alr, s_ali};
-    else alpha = s_alr;
-    for (int c = i + 1 + tid; c < n; c += NT) {
-      T y;
-      if constexpr (sizeof(T) == 16) y = cd{s_yr[c], s_yi[c]};
-      else y = s_yr[c];
-      const T w = add(mulr(tv, y), mulr(alpha, s_v[c]));
-      if constexpr (sizeof(T) == 16) { s_yr[c] = w.x; s_yi[c] = w.y; }
-      else s_yr[c] = w;
-    }
-    __syncthreads();
-    // A22 -= v w^H + w v^H on the lower triangle
-    for (int r = i + 1 + wid; r < n; r += NW) {
-      const T vr = s_v[r];
-      T wr;
-      if constexpr (sizeof(T) == 16) wr = cd{s_yr[r], s_yi[r]};
-      else wr = s_yr[r];
-      T g[UNR];
 #pragma unroll
-      for (int m = 0; m < UNR; ++m) {
-        const int c = i + 1 + lane + 64 * m;
-        g[m] = c <= r ? G[(long)r * ldg + c] : EigT<T>::zero();
+    for (int I = 0; I < NB; ++I) acc[I] = row16_sum(acc[I]);
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+      if (tx == 0) s_row[32 * I + ty] = acc[I];
+    lds_barrier();
+    // w0 = tau y and w0^H v
+    T pd = EigT<T>::zero();
+    if (tid < NN) {
+      T y = s_row[tid];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) y = add(y, s_part[w][tid]);
+      y = mulr(tv, y);
+      y = tid > i && tid < nt ? y : EigT<T>::zero();
+      s_w[tid] = y;
+      pd = mulr(cj(y), s_v[tid]);
+    }
+    pd = wave64_sum(pd);
+    if (lane == 0) s_dot[wid] = pd;
+    lds_barrier();
+    T al = s_dot[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) al = add(al, s_dot[w]);
+    al = scl(-0.5, mulr(tv, al));
+    T wr[NB];
+#pragma unroll
+    for (int I = 0; I < NB; ++I) wr[I] = mac(s_w[32 * I + ty], al, vr[I]);
+#pragma unroll
+    for (int J0 = 0; J0 < NC; J0 += JC) {
+      if (16 * (J0 + JC) <= i + 1) continue;
+      T vc[JC], wc[JC];
+#pragma unroll
+      for (int k = 0; k < JC; ++k) {
+        vc[k] = s_v[16 * (J0 + k) + tx];
+        wc[k] = mac(s_w[16 * (J0 + k) + tx], al, vc[k]);
       }
 #pragma unroll
-      for (int m = 0; m < UNR; ++m) {
-        const int c = i + 1 + lane + 64 * m;
-        if (c <= r) {
-          T wc;
-          if constexpr (sizeof(T) == 16) wc = cd{s_yr[c], s_yi[c]};
-          else wc = s_yr[c];
-          G[(long)r * ldg + c] = sub(g[m], add(mulr(vr, cj(wc)), mulr(wr, cj(s_v[c]))));
+      for (int I = J0 / 2; I < NB; ++I)
+#pragma unroll
+        for (int k = 0; k < JC; ++k) {
+          const int J = J0 + k;
+          if (J > 2 * I + 1) continue;
+          const T g = get(I, J);
+          const T u = msub_cj(msub_cj(g, vr[I], wc[k]), wr[I], vc[k]);
+          put(I, J, J >= 2 * I && 16 * J + tx > 32 * I + ty ? g : u);
         }
-      }
     }
-    __syncthreads();
   }
-  if (tid == 0 && n > 0) {
-    dd[n - 1] = re(G[(long)(n - 1) * ldg + (n - 1)]);
-    ee[n - 1] = 0.0;
-  }
+  // the last diagonal element, held by the thread of its place
+  const int l = nt - 1;
+#pragma unroll
+  for (int J = 0; J < NC; ++J)
+#pragma unroll
+    for (int I = J / 2; I < NB; ++I)
+      if (32 * I + ty == l && 16 * J + tx == l) {
+        dd[l] = re(get(I, J));
+        ee[l] = 0.0;
+      }
+}
+
+// 6 row blocks of complex elements take 120 registers and 96 KiB of LDS per
+// workgroup, 10 of real ones 162 and 120 KiB; one block more exceeds the
+// register file beside the vectors.
+template <typename T>
+static void tri_chip(const TriArgs& a, int i0, int batch, hipStream_t s) {
+  const int nt = a.n - i0;
+  // work figure: the lower triangle of the trailing matrix, summed over the columns
+  ProfScope ps(s, sizeof(T) * (double)nt * (nt - 1) * (nt + 1) / 6.0 * batch, "tri_chip");
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(batch), dim3(512), 0, s, a, i0); };
+  if (nt <= 64) go(tri_chip_kernel<T, 2, 0>);
+  else if (nt <= 128) go(tri_chip_kernel<T, 4, 0>);
+  else if constexpr (sizeof(T) == 16) go(tri_chip_kernel<T, 6, 2>);
+  else if (nt <= 192) go(tri_chip_kernel<T, 6, 0>);
+  else if (nt <= 256) go(tri_chip_kernel<T, 8, 0>);
+  else go(tri_chip_kernel<T, 10, 3>);
 }
 
 size_t tridiag_ws_bytes(int dtype, int n) {
@@ -737,14 +879,10 @@ size_t tridiag_ws_bytes(int dtype, int n) {
 
 hipError_t tridiagonalize(int dtype, const TriArgs& a, int batch, hipStream_t s) {
   if (dtype != C128 && dtype != F64) return hipErrorInvalidValue;
-  if (a.n <= TRI_SMALL_N) {
-    if (a.n <= 0 || batch <= 0) return hipSuccess;
-    // work figure: the lower triangle of the trailing matrix, summed over the columns
-    const double es = dtype == C128 ? 16.0 : 8.0;
-    const double nn = a.n;
-    ProfScope ps(s, es * nn * (nn - 1) * (nn + 1) / 6.0 * batch, "tri_small");
-    if (dtype == C128) hipLaunchKernelGGL(tri_small_kernel<cd>, dim3(batch), dim3(1024), 0, s, a);
-    else hipLaunchKernelGGL(tri_small_kernel<double>, dim3(batch), dim3(1024), 0, s, a);
+  if (a.n <= 0 || batch <= 0) return hipSuccess;
+  if (a.n <= (dtype == C128 ? TRI_CHIP_N<cd> : TRI_CHIP_N<double>)) {
+    if (dtype == C128) tri_chip<cd>(a, 0, batch, s);
+    else tri_chip<double>(a, 0, batch, s);
     return hipGetLastError();
   }
   if (a.sws < (long long)tridiag_ws_bytes(dtype, a.n)) return hipErrorInvalidValue;

@@ -53,3 +53,22 @@ def test_jacobi_svd_far_from_one(T, ctx, scale):
     u, s, vh = T.svd(ctx, T.Tensor.from_numpy(ctx, a, T.F64), 1)
     assert np.abs(s.numpy() - np.linalg.svd(a, compute_uv=False)).max() < 1e-13 * s.numpy()[0]
     assert isometry_err(u.numpy()) < 1e-13
+
+
+# 64, 128, 192 (complex and real), 256 and 320 (real): row blocks held on chip; 321 .. 384 (193 .. 384 complex): first
+# columns from global memory, the rest on chip; 385 and up: panels, the rest on chip
+@pytest.mark.parametrize("complex_,n", [(True, n) for n in (1, 2, 3, 16, 17, 33, 64, 65, 128, 129, 192, 193, 290, 384,
+                                                            385, 417)] +
+                         [(False, n) for n in (1, 2, 31, 64, 65, 128, 129, 192, 193, 256, 257, 320, 321, 384, 385,
+                                               500)])
+def test_eigh_edges(T, ctx, complex_, n):
+    """Householder reduction and its eigensolver are backward stable: eigenvalues and residuals to a small
+    multiple of n u ||A||."""
+    a = draw((n, n), complex_, 7 * n)
+    a = (a + a.conj().T) / 2
+    w, v = T.eigh(ctx, T.Tensor.from_numpy(ctx, a, T.C128 if complex_ else T.F64))
+    w, v = w.numpy(), v.numpy()
+    tol = (8 * n + 64) * U64 * np.linalg.norm(a, 2)
+    assert np.abs(w - np.linalg.eigvalsh(a)).max() < tol
+    assert np.abs(a @ v - v * w).max() < tol
+    assert isometry_err(v) < (8 * n + 64) * U64
