@@ -483,7 +483,7 @@ tci_status tci_lanczos_ground(tci_context ctx, tci_tensor L, tci_tensor W1, tci_
   const int n = n_matvec;
   double* dd = static_cast<double*>(ctx->arena.get(sizeof(double) * 64));
   double* ee = static_cast<double*>(ctx->arena.get(sizeof(double) * 64));
-  double* e2 = static_cast<double*>(ctx->arena.get(sizeof(double) * 64));
+  double* e2 = static_cast<double*>(ctx->arena.get(sizeof(double) * tridiag_e2_elems(64, 1)));
   double* lam = static_cast<double*>(ctx->arena.get(sizeof(double) * 8));
   double* z = static_cast<double*>(ctx->arena.get(sizeof(double) * 64));
   double* iw = static_cast<double*>(ctx->arena.get(sizeof(double) * 4 * 64));

@@ -898,122 +898,245 @@ hipError_t tridiagonalize(int dtype, const TriArgs& a, int batch, hipStream_t s)
 
 // ---------------------------------------------------------------------------
 // Bisection: lam[b][j] = j-th largest eigenvalue of the symmetric tridiagonal
-// (d, e), j < kmax.  Sturm count: number of negative pivots of the LDL^T
-// factorisation of T - x I equals the number of eigenvalues below x.
+// (d, e), j < kmax.  Sturm count: number of negative pivots q_i = d_i - x -
+// e_{i-1}^2 / q_{i-1} of the LDL^T factorisation of T - x I = number of
+// eigenvalues below x.
+//
+// With q_i = p_i / p_{i-1} the pivots' signs are the sign changes of
+//   p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2},
+// whose step is one fused multiply-add on the dependent chain instead of a
+// division.  Its rounding errors are the division form's: each rounding of p_i
+// enters the ratios q_i and q_{i+1} and amounts to relative changes of e^2 and
+// of d - x by a few ulps.  T is scaled by a power of two to a norm in [1, 2),
+// and p is rescaled after every block of STURM_BLK steps: a step grows |p| at
+// most 8 times, and a pair (p_i, p_{i-1}) shrinks by about e^2 per two steps,
+// so blocks whose e^2 are all above STURM_TINY cannot under- or overflow
+// (an exact zero of one p_i counts its sign change one step later).  The other
+// blocks (splits, padding) take the guarded division form; tridiag_scale_kernel
+// marks them by the sign bit of their first e^2.
 // ---------------------------------------------------------------------------
-// The recurrence is one long dependent chain; d and e2 are the same for every
-// lane of the wave, so they are read in blocks of STURM_BLK entries ahead of
-// their use (one memory wait per block instead of one per step).
-constexpr int STURM_BLK = 16;
-__device__ inline int sturm_count(const double* __restrict__ d, const double* __restrict__ e2, int n, double x,
-                                  double pivmin) {
-  double q = d[0] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  int cnt = q < 0.0;
+constexpr int STURM_BLK = 8;
+constexpr double STURM_TINY = 1e-60;
+constexpr double STURM_PIVMIN = 2.2250738585072014e-308 * 64.0;   // of the scaled matrix
+
+__device__ inline int sign_of(double v) { return __double2hiint(v) >> 31; }   // 0 or -1
+
+// Guarded division steps from q_{i-1} over m steps; returns q.
+__device__ inline double sturm_steps_div(const double* __restrict__ d, const double* __restrict__ e2, int m, double sc,
+                                         double x, double q, int& cnt) {
+  for (int u = 0; u < m; ++u) {
+    q = __builtin_fma(d[u], sc, -x) - fabs(e2[u]) / q;
+    if (fabs(q) < STURM_PIVMIN) q = -STURM_PIVMIN;
+    cnt += q < 0.0;
+  }
+  return q;
+}
+
+// e2: scaled squares with block marks; sc: the scale of d; x: a point of the scaled matrix.
+__device__ inline int sturm_count(const double* __restrict__ d, const double* __restrict__ e2, int n, double sc,
+                                  double x) {
+  double p = __builtin_fma(d[0], sc, -x), pp = 1.0;
+  if (fabs(p) < STURM_PIVMIN) p = -STURM_PIVMIN;
+  int cnt = p < 0.0;
+  auto ratio = [&]() -> double {   // q with the sign that was counted
+    const double q = fmax(fabs(p / pp), STURM_PIVMIN);
+    return sign_of(p) == sign_of(pp) ? q : -q;
+  };
   int i = 1;
-  for (; i + STURM_BLK <= n; i += STURM_BLK) {
-    double dd[STURM_BLK], ee[STURM_BLK];
+  double dd[STURM_BLK], ee[STURM_BLK];
+  if (i + STURM_BLK <= n) {
 #pragma unroll
     for (int u = 0; u < STURM_BLK; ++u) {
       dd[u] = d[i + u];
       ee[u] = e2[i - 1 + u];
     }
+  }
+  for (; i + STURM_BLK <= n; i += STURM_BLK) {
+    // the next block's entries (the same for the whole wave) are loaded
+    // while this one is evaluated
+    double dn[STURM_BLK], en[STURM_BLK];
+    const int nx = i + 2 * STURM_BLK <= n ? i + STURM_BLK : i;
 #pragma unroll
     for (int u = 0; u < STURM_BLK; ++u) {
-      q = dd[u] - x - ee[u] / q;
-      if (fabs(q) < pivmin) q = -pivmin;
-      cnt += q < 0.0;
+      dn[u] = d[nx + u];
+      en[u] = e2[nx - 1 + u];
+    }
+    if (__builtin_amdgcn_readfirstlane(__double2hiint(ee[0])) < 0) {
+      p = sturm_steps_div(d + i, e2 + i - 1, STURM_BLK, sc, x, ratio(), cnt);
+      pp = 1.0;
+    } else {
+#pragma unroll
+      for (int u = 0; u < STURM_BLK; ++u) {
+        const double a = __builtin_fma(dd[u], sc, -x);
+        const double pn = __builtin_fma(a, p, -(ee[u] * pp));
+        pp = p;
+        p = pn;
+        cnt += (unsigned)(__double2hiint(p) ^ __double2hiint(pp)) >> 31;
+      }
+    }
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
+    p = __builtin_amdgcn_ldexp(p, ex);
+    pp = __builtin_amdgcn_ldexp(pp, ex);
+#pragma unroll
+    for (int u = 0; u < STURM_BLK; ++u) {
+      dd[u] = dn[u];
+      ee[u] = en[u];
     }
   }
-  for (; i < n; ++i) {
-    q = d[i] - x - e2[i - 1] / q;
-    if (fabs(q) < pivmin) q = -pivmin;
-    cnt += q < 0.0;
-  }
+  if (i < n) sturm_steps_div(d + i, e2 + i - 1, n - i, sc, x, ratio(), cnt);
   return cnt;
 }
 
-__global__ void e2_kernel(const double* e, double* e2, long long sde, int n, int batch) {
-  const long idx = blockIdx.x * (long)blockDim.x + threadIdx.x;
-  if (idx >= (long)batch * n) return;
-  const int b = (int)(idx / n), i = (int)(idx % n);
-  const double v = (i < n - 1) ? e[b * sde + i] : 0.0;
-  e2[b * sde + i] = v * v;
-}
-
-// Multisection, BIS_L lanes per wanted eigenvalue (64 / BIS_L per wave):
-// the lanes of eigenvalue j evaluate the Sturm count at the BIS_L interior
-// points that cut its interval [lo, hi] (count(lo) <= t < count(hi), t the
-// ascending index) into BIS_L + 1 equal parts, and all of them move to the
-// part whose ends keep that invariant (the first point whose count exceeds t
-// and the point before it), until the interval is at rounding level
-// relative to the eigenvalue itself.  Small eigenvalues are resolved to that
-// relative accuracy (more steps than the absolute accuracy of the norm would
-// need) because inverse iteration with shifts only absolutely accurate
-// leaves the vectors of closely spaced small eigenvalues far from
-// orthogonal, which costs a second Cholesky-QR pass.  One lane per
-// eigenvalue leaves one wave per SIMD on a 64 x 1024 batch, bound by the
-// latency of the recurrence's division chain; BIS_L = 4 gives four waves per
-// SIMD to interleave and needs about half the rounds (log2 5 bits each).
-constexpr int BIS_L = 4;
-
-__global__ __launch_bounds__(64) void bisect_kernel(const double* d, const double* e, const double* e2,
-                                                    long long sde, int n, int kmax, double* lam, long long slam,
-                                                    int batch) {
-  const int b = blockIdx.y;
-  const int lane = threadIdx.x;
-  const int sub = lane & (BIS_L - 1);
-  const int j = blockIdx.x * (64 / BIS_L) + lane / BIS_L;
-  if (b >= batch) return;
+// Per problem: Gershgorin bounds and the scale into bnd[3 b ..] (lo, hi of the
+// scaled matrix, the scale), squares of the scaled e with block marks into e2.
+__global__ __launch_bounds__(256) void tridiag_scale_kernel(const double* d, const double* e, double* e2,
+                                                            long long sde, int n, double* bnd) {
+  __shared__ double s_lo[4], s_hi[4];
+  const int b = blockIdx.x, tid = threadIdx.x;
   const double* db = d + b * sde;
   const double* eb = e + b * sde;
-  const double* e2b = e2 + b * sde;
-  double lo = db[0], hi = db[0], emax2 = 0.0;
-  for (int i = lane; i < n; i += 64) {
+  double lo = db[0], hi = db[0];
+  for (int i = tid; i < n; i += 256) {
     const double r = (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i < n - 1 ? fabs(eb[i]) : 0.0);
     lo = fmin(lo, db[i] - r);
     hi = fmax(hi, db[i] + r);
-    if (i < n - 1) emax2 = fmax(emax2, e2b[i]);
   }
   for (int off = 32; off > 0; off >>= 1) {
     lo = fmin(lo, __shfl_xor(lo, off));
     hi = fmax(hi, __shfl_xor(hi, off));
-    emax2 = fmax(emax2, __shfl_xor(emax2, off));
   }
+  if ((tid & 63) == 0) { s_lo[tid >> 6] = lo; s_hi[tid >> 6] = hi; }
+  __syncthreads();
+  lo = fmin(fmin(s_lo[0], s_lo[1]), fmin(s_lo[2], s_lo[3]));
+  hi = fmax(fmax(s_hi[0], s_hi[1]), fmax(s_hi[2], s_hi[3]));
   const double scale = fmax(fabs(lo), fabs(hi));
-  const double pivmin = 2.2250738585072014e-308 * fmax(1.0, emax2) * 64.0;
-  lo -= 4.0 * 2.220446049250313e-16 * scale + pivmin;
-  hi += 4.0 * 2.220446049250313e-16 * scale + pivmin;
+  // the scale stays a normal number at both ends of the exponent range
+  const int ex = scale > 0.0 ? max(-1000, min(1000, 1 - __builtin_amdgcn_frexp_exp(scale))) : 0;
+  const double sc = __builtin_amdgcn_ldexp(1.0, ex);
+  if (tid == 0) {
+    const double eps = 4.0 * 2.220446049250313e-16 * scale * sc + STURM_PIVMIN;
+    bnd[3 * b] = lo * sc - eps;
+    bnd[3 * b + 1] = hi * sc + eps;
+    bnd[3 * b + 2] = sc;
+  }
+  for (int i0 = tid * STURM_BLK; i0 < n; i0 += 256 * STURM_BLK) {
+    double v[STURM_BLK];
+    bool tiny = false;
+#pragma unroll
+    for (int u = 0; u < STURM_BLK; ++u) {
+      const double x = i0 + u < n - 1 ? eb[i0 + u] * sc : 0.0;
+      v[u] = x * x;
+      tiny = tiny || !(v[u] >= STURM_TINY);
+    }
+    if (tiny) v[0] = -v[0];
+#pragma unroll
+    for (int u = 0; u < STURM_BLK; ++u)
+      if (i0 + u < n) e2[b * sde + i0 + u] = v[u];
+  }
+}
+
+// Multisection, L lanes per wanted eigenvalue (64 / L per wave): the lanes of
+// eigenvalue j evaluate the Sturm count at L interior points that cut its
+// interval [lo, hi] (count(lo) <= t < count(hi), t the ascending index) into
+// L + 1 parts, and all of them move to the part whose ends keep that invariant
+// (the first point whose count exceeds t and the point before it), until the
+// interval is at rounding level relative to the eigenvalue itself.  Small
+// eigenvalues are resolved to that relative accuracy because inverse iteration
+// with shifts only absolutely accurate leaves the vectors of closely spaced
+// small eigenvalues far from orthogonal, which costs a second Cholesky-QR pass.
+// The first counts, at +- BIS_ZERO of the scaled matrix, settle the sign and
+// the exact zeros (padding); an interval whose ends differ more than 4 times is
+// cut evenly in the exponent, so that a small eigenvalue takes about
+// log2 log2(norm / |lambda|) rounds more than a large one, not log2.
+constexpr double BIS_ZERO = 0x1p-900;
+
+// piecewise linear logarithm to base 2 of a positive normal number, and its inverse
+__device__ inline double plog2(double v) {
+  return (double)(__builtin_amdgcn_frexp_exp(v) - 1) + (2.0 * __builtin_amdgcn_frexp_mant(v) - 1.0);
+}
+__device__ inline double pexp2(double g) {
+  const double f = floor(g);
+  return __builtin_amdgcn_ldexp(1.0 + (g - f), (int)f);
+}
+
+template <int L>
+__global__ __launch_bounds__(64) void bisect_kernel(const double* __restrict__ d, const double* __restrict__ e2,
+                                                    const double* __restrict__ bnd, long long sde, int n, int kmax,
+                                                    double* __restrict__ lam, long long slam) {
+  const int b = blockIdx.y;
+  const int lane = threadIdx.x;
+  const int sub = lane & (L - 1);
+  const int j = blockIdx.x * (64 / L) + lane / L;
+  const double* db = d + b * sde;
+  const double* e2b = e2 + b * sde;
+  double lo = bnd[3 * b], hi = bnd[3 * b + 1];
+  const double sc = bnd[3 * b + 2];
   const int t = n - 1 - min(j, kmax - 1);  // ascending index of this lane group's eigenvalue
-  const int q0 = lane & ~(BIS_L - 1);      // first lane of the group
+  const int q0 = lane & ~(L - 1);          // first lane of the group
+  int cneg, cpos;
+  if constexpr (L > 1) {
+    const int c = sturm_count(db, e2b, n, sc, sub & 1 ? BIS_ZERO : -BIS_ZERO);
+    cneg = __shfl(c, q0, 64);
+    cpos = __shfl(c, q0 + 1, 64);
+  } else {
+    cneg = sturm_count(db, e2b, n, sc, -BIS_ZERO);
+    cpos = sturm_count(db, e2b, n, sc, BIS_ZERO);
+  }
+  const bool neg = cneg > t;
+  if (neg) hi = fmin(hi, -BIS_ZERO);
+  else if (cpos <= t) lo = fmax(lo, BIS_ZERO);
+  else lo = hi = 0.0;
   for (int it = 0; it < 128; ++it) {
-    const bool done = hi - lo <= 2.220446049250313e-16 * fmax(fabs(lo), fabs(hi)) + pivmin;
+    const bool done = hi - lo <= 2.220446049250313e-16 * fmax(fabs(lo), fabs(hi));
     if (__ballot(!done) == 0ull) break;
-    const double w = (hi - lo) / (BIS_L + 1);
-    const double x = lo + w * (sub + 1);
-    const bool below = sturm_count(db, e2b, n, x, pivmin) <= t;
+    const double near = neg ? -hi : lo, far = neg ? -lo : hi;   // the ends by magnitude
+    const bool geo = !done && near > 0.0 && far > 4.0 * near;
+    const double p0 = geo ? plog2(near) : 0.0, dp = geo ? plog2(far) - p0 : 0.0;
+    auto point = [&](int k) -> double {
+      if (!geo) return lo + (hi - lo) * (1.0 / (L + 1)) * k;
+      const double v = pexp2(p0 + dp * (1.0 / (L + 1)) * (neg ? L + 1 - k : k));
+      return neg ? -v : v;
+    };
+    const bool below = sturm_count(db, e2b, n, sc, point(sub + 1)) <= t;
     // the group's flags (bit s: count at point s <= t); c = leading points below
-    const unsigned flags = (unsigned)(__ballot(below) >> q0) & ((1u << BIS_L) - 1);
-    const int c = __builtin_ctz(~flags);
+    unsigned long long above = ~(__ballot(below) >> q0);
+    if constexpr (L < 64) above |= 1ull << L;
+    const int c = above ? __builtin_ctzll(above) : 64;
     if (!done) {
-      const double nlo = c > 0 ? lo + w * c : lo;
-      const double nhi = c < BIS_L ? lo + w * (c + 1) : hi;
+      const double nlo = c > 0 ? point(c) : lo;
+      const double nhi = c < L ? point(c + 1) : hi;
       if (nlo >= lo && nhi <= hi && nlo < nhi) {
         lo = nlo;
         hi = nhi;
       }
     }
   }
-  if (sub == 0 && j < kmax) lam[b * slam + j] = 0.5 * (lo + hi);
+  if (sub == 0 && j < kmax) lam[b * slam + j] = 0.5 * (lo + hi) / sc;
 }
+
+size_t tridiag_e2_elems(int n, int batch) { return (size_t)(n + 3) * batch; }
 
 hipError_t tridiag_eigvals_top(const double* d, const double* e, double* e2, long long sde, int n,
                                int kmax, double* lam, long long slam, int batch, hipStream_t s) {
-  if (kmax <= 0 || batch <= 0) return hipSuccess;
-  const long tot = (long)batch * n;
-  hipLaunchKernelGGL(e2_kernel, dim3((tot + 255) / 256), dim3(256), 0, s, e, e2, sde, n, batch);
-  hipLaunchKernelGGL(bisect_kernel, dim3((kmax + 64 / BIS_L - 1) / (64 / BIS_L), batch), dim3(64), 0, s, d, e, e2,
-                     sde, n, kmax, lam, slam, batch);
+  if (kmax <= 0 || batch <= 0 || n <= 0) return hipSuccess;
+  double* bnd = e2 + (size_t)n * batch;
+  if (sde != n) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(tridiag_scale_kernel, dim3(batch), dim3(256), 0, s, d, e, e2, sde, n, bnd);
+  auto go = [&](auto kernel, int L) {
+    hipLaunchKernelGGL(kernel, dim3((kmax + 64 / L - 1) / (64 / L), batch), dim3(64), 0, s, d, (const double*)e2,
+                       (const double*)bnd, sde, n, kmax, lam, slam);
+  };
+  // L lanes cut the rounds to 1 / log2(L + 1) of a bisection's at L times its
+  // counts.  A wave alone on a SIMD takes about 100 cycles per step (it waits on
+  // its scalar loads), four waves about 60 each: more lanes pay up to one or
+  // two waves per SIMD (1024 SIMDs) and cost above (order 2048, 16 problems of
+  // 1024 values: 2.06 ms with L = 4, 2.63 ms with L = 16; the division form with
+  // L = 4 took 6.77 ms).
+  const long long want = (long long)kmax * batch;
+  if (want <= 1024) go(bisect_kernel<64>, 64);
+  else if (want <= 8192) go(bisect_kernel<16>, 16);
+  else if (want <= 32768) go(bisect_kernel<4>, 4);
+  else go(bisect_kernel<1>, 1);
   return hipGetLastError();
 }
 

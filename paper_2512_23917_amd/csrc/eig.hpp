@@ -31,7 +31,9 @@ size_t tridiag_ws_bytes(int dtype, int n);
 
 // G = Q T Q^H (dtype C128 or F64).
 hipError_t tridiagonalize(int dtype, const TriArgs& a, int batch, hipStream_t s);
-// lam[b][j], j < kmax: the j-th largest eigenvalue of tridiag(d, e).  e2: scratch like e.
+// lam[b][j], j < kmax: the j-th largest eigenvalue of tridiag(d, e), stored with
+// stride sde = n.  e2: scratch of tridiag_e2_elems(n, batch) doubles.
+size_t tridiag_e2_elems(int n, int batch);
 hipError_t tridiag_eigvals_top(const double* d, const double* e, double* e2, long long sde, int n,
                                int kmax, double* lam, long long slam, int batch, hipStream_t s);
 // Z[b] (n x kmax, ld ldz, real): unit eigenvectors of tridiag(d, e) for lam[b][j], j < chi[b]

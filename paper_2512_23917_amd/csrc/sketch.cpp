@@ -184,7 +184,7 @@ tci_status sketch_run(tci_context ctx, int dt_lo, int wdt, int prec, int nb, int
   const int ng = kmax;
   SK_ARENA(d, double, (size_t)ng * nb);
   SK_ARENA(e, double, (size_t)ng * nb);
-  SK_ARENA(e2, double, (size_t)ng * nb);
+  SK_ARENA(e2, double, tridiag_e2_elems(ng, nb));
   SK_ARENA(tau, char, ew * (size_t)ng * nb);
   SK_ARENA(Vt, char, ew * (size_t)sG * nb);
   SK_ARENA(Wp, char, ew * (size_t)ng * TRIDIAG_NB * nb);

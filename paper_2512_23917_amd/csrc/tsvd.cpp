@@ -136,7 +136,7 @@ tci_status tsvd_eigvals(tci_context ctx, int wdt, int nb, int m, int n, const vo
   // tridiagonal reduction
   ARENA(d, double, (size_t)ng * nb);
   ARENA(e, double, (size_t)ng * nb);
-  ARENA(e2, double, (size_t)ng * nb);
+  ARENA(e2, double, tridiag_e2_elems(ng, nb));
   ARENA(tau, char, es * (size_t)ng * nb);
   ARENA(Vt, char, es * (size_t)ng * ng * nb);
   ARENA(Wp, char, es * (size_t)ng * TRIDIAG_NB * nb);
@@ -1040,7 +1040,7 @@ static tci_status eigh_core(tci_context ctx, tci_tensor a, int k_rows, tci_tenso
   TCI_CHECK_HIP(hipMemcpyAsync(G, src, es * (size_t)n * n, hipMemcpyDeviceToDevice, s));
   ARENA(d, double, n);
   ARENA(e, double, n);
-  ARENA(e2, double, n);
+  ARENA(e2, double, tridiag_e2_elems(n, 1));
   ARENA(tau, char, es * n);
   ARENA(Vt, char, es * (size_t)n * n);
   ARENA(Wp, char, es * (size_t)n * TRIDIAG_NB);

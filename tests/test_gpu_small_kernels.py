@@ -72,3 +72,39 @@ def test_eigh_edges(T, ctx, complex_, n):
     assert np.abs(w - np.linalg.eigvalsh(a)).max() < tol
     assert np.abs(a @ v - v * w).max() < tol
     assert isometry_err(v) < (8 * n + 64) * U64
+
+
+@pytest.mark.parametrize("n,scale", [(9, 1.0), (40, 1e-120), (40, 1e120), (130, 1.0)])
+def test_eigvalsh_of_diagonals(T, ctx, n, scale):
+    """Diagonal matrices with values over 200 decades, both signs, repeated values and zeros: the reduction
+    leaves them as they are, and bisection resolves every value to a few ulps of itself."""
+    d = 10.0 ** -np.linspace(0, 100, n) * np.where(np.arange(n) % 3 == 1, -1.0, 1.0) * scale
+    d[n // 2:n // 2 + 2] = 0.0
+    d[-1] = d[0]
+    w = T.eigvalsh(ctx, T.Tensor.from_numpy(ctx, np.diag(d), T.F64)).numpy()
+    ref = np.sort(d)
+    assert np.all(np.abs(w - ref) <= 8 * U64 * np.abs(ref))
+
+
+# L lanes per eigenvalue: 64 up to 1024 eigenvalues, 16 up to 8192, 4 up to 32768, 1 above
+@pytest.mark.parametrize("batch,chi", [(2, 40), (60, 40), (64, 130), (64, 300)])
+def test_singular_values_of_padded_batches(T, ctx, batch, chi):
+    """Two-site updates of tensors whose last bond indices are zero: exact zero eigenvalues beside a graded
+    spectrum, for every number of lanes per eigenvalue.  The Gram route leaves n u of the largest square."""
+    n = 2 * chi
+    p = T.update_params(chi_min=1, chi_max=n, target_trunc_err=0.0, direction=T.DIR_LEFT, precision=T.PREC_FP64)
+    A, B, ref = [], [], []
+    for i in range(2):
+        a, b = draw((chi, 2, chi), False, 50 + i), draw((chi, 2, chi), False, 90 + i)
+        a[chi - 9:] = 0.0
+        b *= 10.0 ** -np.linspace(0, 4, chi)[:, None, None]
+        ref.append(np.linalg.svd(a.reshape(n, chi) @ b.reshape(chi, n), compute_uv=False))
+        A.append(T.Tensor.from_numpy(ctx, a, T.F64))
+        B.append(T.Tensor.from_numpy(ctx, b, T.F64))
+    A, B, ref = (x * (batch // 2) for x in (A, B, ref))
+    _, s, _, info = T.two_site_update_batched(ctx, A, B, None, p)
+    for x, r, f in zip(s, ref, info):
+        x = x.numpy() * np.sqrt(f.norm2)
+        k = chi - 20    # well above the rounding level of the Gram matrix
+        assert np.abs(x[:k] ** 2 - r[:k] ** 2).max() < 8 * n * U64 * r[0] ** 2
+        assert np.all(x[chi:] ** 2 < 8 * n * U64 * r[0] ** 2)
