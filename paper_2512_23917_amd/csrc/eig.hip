@@ -55,6 +55,10 @@ __device__ inline double sub(double a, double b) { return a - b; }
 __device__ inline cd sub(cd a, cd b) { return a - b; }
 __device__ inline double shfl_xor_t(double v, int m) { return __shfl_xor(v, m); }
 __device__ inline cd shfl_xor_t(cd v, int m) { return cd{__shfl_xor(v.x, m), __shfl_xor(v.y, m)}; }
+__device__ inline double shfl_t(double v, int l) { return __shfl(v, l); }
+__device__ inline cd shfl_t(cd v, int l) { return cd{__shfl(v.x, l), __shfl(v.y, l)}; }
+__device__ inline double rl(double, double r) { return r; }   // a real number as the element type
+__device__ inline cd rl(cd, double r) { return cd{r, 0.0}; }
 __device__ inline double wsum(double v) { return wave_sum(v); }
 __device__ inline cd wsum(cd v) { return cd{wave_sum(v.x), wave_sum(v.y)}; }
 __device__ inline double bsum(double v, double* sh) { return block_sum(v, sh); }
@@ -97,9 +101,10 @@ struct TriWs {
   __host__ __device__ static size_t P(int n) { return align(sizeof(T) * (size_t)n); }
   __host__ __device__ static size_t pa(int n) { return P(n) + align(sizeof(T) * (size_t)nbt(n) * n); }
   __host__ __device__ static size_t pc(int n) { return pa(n) + align(sizeof(double) * (size_t)nbt(n)); }
+  __host__ __device__ static size_t pt(int n) { return pc(n) + align(sizeof(T) * (size_t)ntile(n)); }
   // [V_panel; W^T] and [W^T; V_panel], 2 NB rows of n each: operands of the
   // fused rank-2NB trailing update
-  __host__ __device__ static size_t cat1(int n) { return pc(n) + align(sizeof(T) * (size_t)ntile(n) * (1 + 2 * NB)); }
+  __host__ __device__ static size_t cat1(int n) { return pt(n) + align(sizeof(T) * (size_t)nbt(n) * 2 * NB); }
   __host__ __device__ static size_t cat2(int n) { return cat1(n) + align(sizeof(T) * (size_t)2 * NB * n); }
   __host__ __device__ static size_t bytes(int n) { return cat2(n) + align(sizeof(T) * (size_t)2 * NB * n); }
   __host__ __device__ static int nbt(int n) { return (n + TT - 1) / TT; }
@@ -108,22 +113,34 @@ struct TriWs {
 };
 
 // Tiles per workgroup of the trailing matvec: band R (rows R*TT ...) is cut
-// into chunks of up to CH consecutive tiles C, and one workgroup handles one
+// into chunks of up to ch consecutive tiles C, and one workgroup handles one
 // chunk, so that the reflector set-up and the final reduction are paid once
 // per chunk.  The row sums of a chunk starting at tile cA go to P[cA][rows];
 // the column sums of an off-diagonal tile (R, C) go to P[R][columns of C].
-constexpr int CH = 32;
-
-__host__ __device__ inline int tri_chunks(int nact) {
+__host__ __device__ inline int tri_chunks(int nact, int ch) {
   int k = 0;
-  for (int t = 1; t <= nact; ++t) k += (t + CH - 1) / CH;
+  for (int t = 1; t <= nact; ++t) k += (t + ch - 1) / ch;
   return k;
 }
 
+// Chunk length of a launch over nact bands of each of batch problems: whole
+// bands (32 tiles) when these already give the chip TRI_WG workgroups, else
+// the longest power of two that does.  A workgroup streams a tile in about
+// 1.9 us, so a launch takes as long as its longest chunk: four problems of
+// order 2048 ran 61.7 us per column on average with whole bands (128
+// workgroups) and 20.8 us so cut, sixteen 70.9 and 51.2 us (512 to 2048
+// workgroups within 1% of each other, 4096 2% slower).
+constexpr int TRI_CH_MAX = 32, TRI_WG = 1024;
+static int tri_chunk_len(int nact, int batch) {
+  int ch = TRI_CH_MAX;
+  while (ch > 1 && (long long)tri_chunks(nact, ch) * batch < TRI_WG) ch >>= 1;
+  return ch;
+}
+
 // Is P[t][r] written in the column step whose first active block is b0?
-__device__ inline bool tri_slot_used(int t, int r, int b0) {
+__device__ inline bool tri_slot_used(int t, int r, int b0, int ch) {
   const int Rr = r / TT;
-  return t > Rr || ((t - b0) % CH == 0);
+  return t > Rr || ((t - b0) & (ch - 1)) == 0;
 }
 
 // Sum of a per-thread complex / real value over groups of 4 consecutive lanes.
@@ -244,10 +261,9 @@ __device__ inline T parts_sum(T v, T* sh256) {
 }
 
 template <typename T, int NB>
-__global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int icol, int ifin, int j0) {
+__global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int icol, int ifin, int j0, int ch) {
   __shared__ T s_t1[NB], s_t2[NB], s_vrow[NB], s_wrow[NB];
   __shared__ T s_alpha, s_wi;
-  __shared__ T s_fc[1 + 2 * NB];
   __shared__ T s_red[256];
   __shared__ T s_sh4[4];
   __shared__ double red[256];
@@ -257,6 +273,7 @@ __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int 
   const T* P = reinterpret_cast<const T*>(ws + TriWs<T, NB>::P(n));
   double* pa = reinterpret_cast<double*>(ws + TriWs<T, NB>::pa(n));
   const T* pc_in = reinterpret_cast<const T*>(ws + TriWs<T, NB>::pc(n));
+  const T* pt_in = reinterpret_cast<const T*>(ws + TriWs<T, NB>::pt(n));
   T* G = reinterpret_cast<T*>(a.G) + b * a.sG;
   T* V = reinterpret_cast<T*>(a.Vt) + b * a.sVt;
   T* W = reinterpret_cast<T*>(a.Wp) + b * a.sWp;
@@ -270,34 +287,40 @@ __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int 
   // ---- finish w_ifin (panel column pp = ifin - j0) on rows >= ifin + 1 = row0
   if (ifin >= 0) {
     const int pp = ifin - j0;
-    // reduce the chunk partials of the trailing matvec of column ifin (one
-    // value per thread; the kernel boundary made them visible)
-    if (tid < 1 + 2 * NB) {
-      const int nwg = tri_chunks(TriWs<T, NB>::nbt(n) - (ifin + 1) / TT);
-      // loads in groups of 8 (one wait per group), sums in chunk order
-      T acc = EigT<T>::zero();
-      int k = 0;
-      for (; k + 8 <= nwg; k += 8) {
-        T v[8];
+    // reduce the partials of the trailing matvec of column ifin (the kernel
+    // boundary made them visible): t1 and t2 from one partial per band, four
+    // threads per value, and the quadratic form from one per chunk
+    static_assert(2 * NB == 64, "four threads per value of t1, t2");
+    {
+      const int fb0 = (ifin + 1) / TT, nband = TriWs<T, NB>::nbt(n) - fb0, nwg = tri_chunks(nband, ch);
+      T acc = EigT<T>::zero(), qv = EigT<T>::zero();
+      int k = part;
+      for (; k + 12 < nband; k += 16) {   // four loads in flight
+        T v[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = pc_in[(long)(k + u) * (1 + 2 * NB) + tid];
+        for (int u = 0; u < 4; ++u) v[u] = pt_in[(long)(k + 4 * u) * (2 * NB) + (tid & 63)];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc = add(acc, v[u]);
+        for (int u = 0; u < 4; ++u) acc = add(acc, v[u]);
       }
-      for (; k < nwg; ++k) acc = add(acc, pc_in[(long)k * (1 + 2 * NB) + tid]);
-      s_fc[tid] = acc;
+      for (; k < nband; k += 4) acc = add(acc, pt_in[(long)k * (2 * NB) + (tid & 63)]);
+      for (int w = tid; w < nwg; w += 256) qv = add(qv, pc_in[w]);
+      qv = wave64_sum(qv);
+      s_red[tid] = acc;
+      if ((tid & 63) == 0) s_sh4[part] = qv;
     }
     __syncthreads();
-    if (tid < pp) { s_t1[tid] = s_fc[1 + tid]; s_t2[tid] = s_fc[1 + NB + tid]; }
-    __syncthreads();
-    if (tid == 0) {
-      const T taup = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
-      T yv = s_fc[0];
-      for (int q = 0; q < pp; ++q) {
-        yv = sub(yv, mulr(cj(s_t1[q]), s_t2[q]));
-        yv = sub(yv, mulr(cj(s_t2[q]), s_t1[q]));
+    if (tid < 64) {
+      const T t = add(add(s_red[tid], s_red[tid + 64]), add(s_red[tid + 128], s_red[tid + 192]));
+      // yv - t1^H t2 - t2^H t1 over the panel columns q < pp
+      const T t2 = shfl_t(t, (tid + NB) & 63);
+      const double cross = wave64_sum(tid < pp ? 2.0 * re(mulr(cj(t), t2)) : 0.0);
+      if (tid < pp) s_t1[tid] = t;
+      if (tid >= NB && tid - NB < pp) s_t2[tid - NB] = t;
+      if (tid == 0) {
+        const T taup = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
+        const T yv = add(add(s_sh4[0], s_sh4[1]), add(s_sh4[2], s_sh4[3]));
+        s_alpha = scl(-0.5 * nrm2(taup), sub(yv, rl(T{}, cross)));
       }
-      s_alpha = scl(-0.5 * nrm2(taup), yv);
     }
     __syncthreads();
     const T taup = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
@@ -316,10 +339,10 @@ __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int 
         for (int u = 0; u < 4; ++u) pv[u] = P[(long)(t + 4 * u) * n + r];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (tri_slot_used(t + 4 * u, r, tb0)) acc = add(acc, pv[u]);
+          if (tri_slot_used(t + 4 * u, r, tb0, ch)) acc = add(acc, pv[u]);
       }
       for (; t < nbt; t += 4)
-        if (tri_slot_used(t, r, tb0)) acc = add(acc, P[(long)t * n + r]);
+        if (tri_slot_used(t, r, tb0, ch)) acc = add(acc, P[(long)t * n + r]);
 #pragma unroll 4
       for (int q = part; q < pp; q += 4) {
         acc = sub(acc, mulr(V[(long)(j0 + q) * n + r], s_t1[q]));
@@ -352,7 +375,7 @@ __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int 
     T acc = EigT<T>::zero();
     const int tb0 = (ifin + 1) / TT, nbt = TriWs<T, NB>::nbt(n);
     for (int t = tb0 + tid; t < nbt; t += 256)
-      if (tri_slot_used(t, i, tb0)) acc = add(acc, P[(long)t * n + i]);
+      if (tri_slot_used(t, i, tb0, ch)) acc = add(acc, P[(long)t * n + i]);
     if (tid < pp) {
       acc = sub(acc, mulr(V[(long)(j0 + tid) * n + i], s_t1[tid]));
       acc = sub(acc, mulr(W[(long)i * NB + tid], s_t2[tid]));
@@ -390,7 +413,7 @@ __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int 
 }
 
 template <typename T, int NB>
-__global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0) {
+__global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0, int ch) {
   __shared__ T s_vR[TT];
   __shared__ T s_q[4];
   __shared__ T s_colsum[2][4][TT];
@@ -404,6 +427,7 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0)
   const T* xv = reinterpret_cast<const T*>(ws + TriWs<T, NB>::xv(n));
   T* P = reinterpret_cast<T*>(ws + TriWs<T, NB>::P(n));
   T* pc = reinterpret_cast<T*>(ws + TriWs<T, NB>::pc(n));
+  T* pt = reinterpret_cast<T*>(ws + TriWs<T, NB>::pt(n));
   const double* pa = reinterpret_cast<const double*>(ws + TriWs<T, NB>::pa(n));
   const T* G = reinterpret_cast<const T*>(a.G) + b * a.sG;
   T* V = reinterpret_cast<T*>(a.Vt) + b * a.sVt;
@@ -412,12 +436,12 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0)
   const int b0 = (i + 1) / TT;
   int k = wg, R = b0;
   for (;;) {
-    const int nch = (R - b0 + CH) / CH;
+    const int nch = (R - b0 + ch) / ch;
     if (k < nch) break;
     k -= nch;
     ++R;
   }
-  const int cA = b0 + k * CH, cB = min(R, cA + CH - 1);
+  const int cA = b0 + k * ch, cB = min(R, cA + ch - 1);
   const bool has_diag = (cB == R);
   // reflector scalars (every workgroup computes them from the norm partials of
   // the column kernel, one per block of TT rows from row i)
@@ -543,11 +567,9 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0)
   qo = wsum(qo);
   if (cl == 0) s_q[rg] = add(add(qd, qo), cj(qo));
   __syncthreads();
-  T* mypc = pc + (long)wg * (1 + 2 * NB);
-  if (tid == 0) mypc[0] = add(add(s_q[0], s_q[1]), add(s_q[2], s_q[3]));
-  if (tid < 2 * NB)
-    mypc[1 + tid] = has_diag ? add(add(s_tt[0][tid], s_tt[1][tid]), add(s_tt[2][tid], s_tt[3][tid]))
-                             : EigT<T>::zero();
+  if (tid == 0) pc[wg] = add(add(s_q[0], s_q[1]), add(s_q[2], s_q[3]));
+  if (tid < 2 * NB && has_diag)
+    pt[(long)(R - b0) * (2 * NB) + tid] = add(add(s_tt[0][tid], s_tt[1][tid]), add(s_tt[2][tid], s_tt[3][tid]));
 }
 
 // Operands of the trailing update G -= V W^H + W V^H = [V W] [W V]^H over
@@ -592,19 +614,20 @@ static hipError_t tridiag_impl(const TriArgs& a, int batch, hipStream_t s) {
       const int i = j0 + p;
       const int rowsA = n - i;
       hipLaunchKernelGGL((tri_colA_kernel<T, NB>), dim3((rowsA + TT - 1) / TT, batch), dim3(256), 0, s, a, i, i,
-                         p > 0 ? i - 1 : -1, j0);
+                         p > 0 ? i - 1 : -1, j0, tri_chunk_len(nbt - i / TT, batch));
       if (i + 1 < n) {
-        const int nact = nbt - (i + 1) / TT;
+        const int nact = nbt - (i + 1) / TT, ch = tri_chunk_len(nact, batch);
         // algorithmic bytes: the lower triangle of the trailing matrix read once
         ProfScope ps(s, 0.5 * (double)(n - i - 1) * (n - i) * sizeof(T) * batch, "hemv");
-        hipLaunchKernelGGL((tri_colC_kernel<T, NB>), dim3(batch, tri_chunks(nact)), dim3(256), 0, s, a, i, j0);
+        hipLaunchKernelGGL((tri_colC_kernel<T, NB>), dim3(batch, tri_chunks(nact, ch)), dim3(256), 0, s, a, i,
+                           j0, ch);
       }
     }
     const int t = j0 + pe;
     if (t < n) {
       // finish w of the panel's last column, then the trailing update
       hipLaunchKernelGGL((tri_colA_kernel<T, NB>), dim3((n - t + TT - 1) / TT, batch), dim3(256), 0, s, a, t, -1,
-                         t - 1, j0);
+                         t - 1, j0, tri_chunk_len(nbt - t / TT, batch));
       const int m = n - t;
       {
         const long long tot = (long long)pe * m;
