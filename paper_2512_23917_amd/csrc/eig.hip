@@ -236,191 +236,201 @@ __device__ inline void reflector(T alpha, double xn2, double& beta, T& tau, T& s
   }
 }
 
-// Sum of one value per thread over a 256-thread block (wave shuffles, then
-// the four wave sums through LDS); every thread receives the total.
+// Reflector scalars as in reflector(), without the division and square-root
+// sequences, which a column would wait for: refined hardware seeds.
+__device__ inline double rsqrt_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = __builtin_fma(y * 0.5, __builtin_fma(-x * y, y, 1.0), y);
+  return y;
+}
+__device__ inline double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+  return y;
+}
 template <typename T>
-__device__ inline T block_sum256(T v, T* sh4) {
-  v = wsum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh4[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return add(add(sh4[0], sh4[1]), add(sh4[2], sh4[3]));
+__device__ inline void reflector_nr(T alpha, double xn2, double& beta, T& tau, T& scal) {
+  const double ar = re(alpha), ai = im(alpha), sum = ar * ar + ai * ai + xn2;
+  if ((xn2 == 0.0 && ai == 0.0) || !(sum > 1e-280 && sum < 1e280)) {
+    reflector(alpha, xn2, beta, tau, scal);
+    return;
+  }
+  const double rs = rsqrt_nr(sum), sg = ar >= 0.0 ? -1.0 : 1.0, ib = sg * rs;
+  beta = sum * ib;
+  const double xr = ar - beta;
+  if constexpr (sizeof(T) == sizeof(double)) {
+    tau = -xr * ib;
+    scal = rcp_nr(xr);
+  } else {
+    const double iden = rcp_nr(xr * xr + ai * ai);
+    tau = cd{-xr * ib, -ai * ib};
+    scal = cd{xr * iden, -ai * iden};
+  }
 }
 
-// Sum over the four thread groups part = tid >> 6 that share a row
-// (tid & 63): the result is valid in part 0.
-template <typename T>
-__device__ inline T parts_sum(T v, T* sh256) {
-  __syncthreads();
-  sh256[threadIdx.x] = v;
-  __syncthreads();
-  T r = v;
-  if (threadIdx.x < 64) r = add(add(sh256[threadIdx.x], sh256[threadIdx.x + 64]),
-                                add(sh256[threadIdx.x + 128], sh256[threadIdx.x + 192]));
-  return r;
+// acc + a b, acc + conj(a) b, acc - a conj(b) with fused multiply-adds only
+__device__ inline double mac(double c, double a, double b) { return __builtin_fma(a, b, c); }
+__device__ inline double mac_cj(double c, double a, double b) { return __builtin_fma(a, b, c); }
+__device__ inline double msub_cj(double c, double a, double b) { return __builtin_fma(-a, b, c); }
+__device__ inline cd mac(cd c, cd a, cd b) {
+  return cd{__builtin_fma(-a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
+}
+__device__ inline cd mac_cj(cd c, cd a, cd b) {
+  return cd{__builtin_fma(a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(-a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
+}
+__device__ inline cd msub_cj(cd c, cd a, cd b) {
+  return cd{__builtin_fma(-a.y, b.y, __builtin_fma(-a.x, b.x, c.x)), __builtin_fma(-a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
 }
 
+// Barrier for data exchanged through LDS only: __syncthreads would also wait
+// for the column's stores to global memory, a memory round trip per barrier.
+__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// One workgroup per 64 rows: lane = row, the four waves share a row's sums (wave
+// w takes every fourth slot of P and every fourth panel column).  A launch is
+// one chain of latencies, so every global load is issued before the first
+// wait, what all waves need of row icol and of the partials is reduced by each
+// wave for itself, and two barriers remain per half.
 template <typename T, int NB>
 __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int icol, int ifin, int j0, int ch) {
-  __shared__ T s_t1[NB], s_t2[NB], s_vrow[NB], s_wrow[NB];
-  __shared__ T s_alpha, s_wi;
-  __shared__ T s_red[256];
-  __shared__ T s_sh4[4];
-  __shared__ double red[256];
-  const int b = blockIdx.y, n = a.n, tid = threadIdx.x;
+  constexpr int PU = NB / 4, SU = 8;   // panel columns and slots of P (the first 32) per wave
+  static_assert(2 * NB == 64, "lane l: t1 (l < NB) or t2");
+  __shared__ T s_part[4][64], s_col[4][64];
+  __shared__ T s_t[4][64], s_row[4][64];
+  __shared__ T s_q[4];
+  const int b = blockIdx.y, n = a.n, tid = threadIdx.x, lane = tid & 63, part = tid >> 6;
   char* ws = reinterpret_cast<char*>(a.ws) + b * a.sws;
   T* xv = reinterpret_cast<T*>(ws + TriWs<T, NB>::xv(n));
   const T* P = reinterpret_cast<const T*>(ws + TriWs<T, NB>::P(n));
   double* pa = reinterpret_cast<double*>(ws + TriWs<T, NB>::pa(n));
-  const T* pc_in = reinterpret_cast<const T*>(ws + TriWs<T, NB>::pc(n));
-  const T* pt_in = reinterpret_cast<const T*>(ws + TriWs<T, NB>::pt(n));
+  const T* pc = reinterpret_cast<const T*>(ws + TriWs<T, NB>::pc(n));
+  const T* pt = reinterpret_cast<const T*>(ws + TriWs<T, NB>::pt(n));
   T* G = reinterpret_cast<T*>(a.G) + b * a.sG;
-  T* V = reinterpret_cast<T*>(a.Vt) + b * a.sVt;
-  T* W = reinterpret_cast<T*>(a.Wp) + b * a.sWp;
-  const T* Y = reinterpret_cast<const T*>(a.y) + b * a.sy;
-  const long ldg = a.ldg;
-  const int rlo = row0 + blockIdx.x * TT;          // first row of this block
-  const int r = rlo + (tid & (TT - 1));            // row of this thread (4 threads per row)
-  const int part = tid >> 6;                       // 0..3
+  const T* V = reinterpret_cast<const T*>(a.Vt) + b * a.sVt + (long)j0 * n;   // panel row q at V + q n
+  T* W = reinterpret_cast<T*>(a.Wp) + b * a.sWp;                              // panel column q at W + q n
+  const T zero = EigT<T>::zero();
+  const int r = row0 + blockIdx.x * TT + lane, rc = min(r, n - 1);
   const bool rv = r < n;
+  const int pp = ifin >= 0 ? ifin - j0 : 0;     // panel columns before the one finished here
+  const int p = icol >= 0 ? icol - j0 : 0;      // panel columns of the column update
 
-  // ---- finish w_ifin (panel column pp = ifin - j0) on rows >= ifin + 1 = row0
+  // ---- loads, from clamped addresses: what lies outside the finished panel
+  // columns or the used slots is replaced by zero where it is used
+  T vq[PU], wq[PU];
+#pragma unroll
+  for (int u = 0; u < PU; ++u) {
+    const int q = min(part + 4 * u, max(pp - 1, 0));
+    vq[u] = V[(long)q * n + rc];
+    wq[u] = W[(long)q * n + rc];
+  }
+  const T gcol = G[(long)rc * a.ldg + max(icol, 0)];
+  // row icol of V (lanes < NB) and of W (lanes >= NB): the finished columns
+  const int lq = lane & (NB - 1);
+  const T* vwsrc = lane < NB ? V : W;
+  T vw = vwsrc[(long)min(lq, max(pp - 1, 0)) * n + max(icol, 0)];
+  T wr = zero, wi = zero;                       // w of this row and of row icol
+  T vfin = zero;
   if (ifin >= 0) {
-    const int pp = ifin - j0;
-    // reduce the partials of the trailing matvec of column ifin (the kernel
-    // boundary made them visible): t1 and t2 from one partial per band, four
-    // threads per value, and the quadratic form from one per chunk
-    static_assert(2 * NB == 64, "four threads per value of t1, t2");
-    {
-      const int fb0 = (ifin + 1) / TT, nband = TriWs<T, NB>::nbt(n) - fb0, nwg = tri_chunks(nband, ch);
-      T acc = EigT<T>::zero(), qv = EigT<T>::zero();
-      int k = part;
-      for (; k + 12 < nband; k += 16) {   // four loads in flight
-        T v[4];
+    const int tb0 = (ifin + 1) / TT, nbt = TriWs<T, NB>::nbt(n), nband = nbt - tb0, nwg = tri_chunks(nband, ch);
+    vfin = V[(long)pp * n + rc];
+    const T tau = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
+    T ps[SU], tv[SU], pi = zero, qv = zero;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = pt_in[(long)(k + 4 * u) * (2 * NB) + (tid & 63)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = add(acc, v[u]);
-      }
-      for (; k < nband; k += 4) acc = add(acc, pt_in[(long)k * (2 * NB) + (tid & 63)]);
-      for (int w = tid; w < nwg; w += 256) qv = add(qv, pc_in[w]);
-      qv = wave64_sum(qv);
-      s_red[tid] = acc;
-      if ((tid & 63) == 0) s_sh4[part] = qv;
+    for (int u = 0; u < SU; ++u) {
+      const int t = tb0 + part + 4 * u, k = part + 4 * u;
+      ps[u] = P[(long)min(t, nbt - 1) * n + rc];
+      tv[u] = pt[(long)min(k, nband - 1) * (2 * NB) + lane];
     }
-    __syncthreads();
-    if (tid < 64) {
-      const T t = add(add(s_red[tid], s_red[tid + 64]), add(s_red[tid + 128], s_red[tid + 192]));
-      // yv - t1^H t2 - t2^H t1 over the panel columns q < pp
-      const T t2 = shfl_t(t, (tid + NB) & 63);
-      const double cross = wave64_sum(tid < pp ? 2.0 * re(mulr(cj(t), t2)) : 0.0);
-      if (tid < pp) s_t1[tid] = t;
-      if (tid >= NB && tid - NB < pp) s_t2[tid - NB] = t;
-      if (tid == 0) {
-        const T taup = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
-        const T yv = add(add(s_sh4[0], s_sh4[1]), add(s_sh4[2], s_sh4[3]));
-        s_alpha = scl(-0.5 * nrm2(taup), sub(yv, rl(T{}, cross)));
-      }
+    if (icol >= 0)
+      for (int t = tb0 + lane; t < nbt; t += 64)
+        if (tri_slot_used(t, icol, tb0, ch)) pi = add(pi, P[(long)t * n + icol]);
+    for (int w = tid; w < nwg; w += 256) qv = add(qv, pc[w]);
+    // ---- t1, t2 from one partial per band, the quadratic form from one per chunk
+    T tsum = zero, y = zero;
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int t = tb0 + part + 4 * u, k = part + 4 * u;
+      if (k < nband) tsum = add(tsum, tv[u]);
+      if (t < nbt && tri_slot_used(t, rc, tb0, ch)) y = add(y, ps[u]);
     }
-    __syncthreads();
-    const T taup = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
-    const T alpha = s_alpha;
-    const int tb0 = (ifin + 1) / TT, nbt = TriWs<T, NB>::nbt(n);
-    const T* vfin = V + (long)ifin * n;
-    // w for this thread's row (4 threads share a row: each sums a quarter)
-    T acc = EigT<T>::zero();
-    if (rv) {
-      // slots t = tb0 + part, +4, ...: loaded four at a time (every address
-      // is valid), the unused ones dropped, sums in slot order
-      int t = tb0 + part;
-      for (; t + 12 < nbt; t += 16) {
-        T pv[4];
+    for (int k = part + 4 * SU; k < nband; k += 4) tsum = add(tsum, pt[(long)k * (2 * NB) + lane]);
+    for (int t = tb0 + part + 4 * SU; t < nbt; t += 4)
+      if (tri_slot_used(t, rc, tb0, ch)) y = add(y, P[(long)t * n + rc]);
+    qv = wave64_sum(qv);
+    s_part[part][lane] = tsum;
+    if (lane == 0) s_q[part] = qv;
+    lds_barrier();
+    T t12 = add(add(s_part[0][lane], s_part[1][lane]), add(s_part[2][lane], s_part[3][lane]));
+    if (lq >= pp) t12 = vw = zero;
+    s_t[part][lane] = t12;                      // read back by this wave only
+    const T yv = add(add(s_q[0], s_q[1]), add(s_q[2], s_q[3]));
+    // yv - t1^H t2 - t2^H t1 (each product appears in both halves of the wave)
+    const double cross = wave64_sum(re(mulr(cj(t12), shfl_xor_t(t12, NB))));
+    const T alpha = scl(-0.5 * nrm2(tau), sub(yv, rl(T{}, cross)));
+    // w of row icol: y(icol) - V(icol,:) t1 - W(icol,:) t2, v(icol) = 1
+    if (icol >= 0) {
+      const T yi = wave64_sum(sub(pi, mulr(vw, t12)));
+      wi = add(mulr(tau, yi), alpha);
+    }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) pv[u] = P[(long)(t + 4 * u) * n + r];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (tri_slot_used(t + 4 * u, r, tb0, ch)) acc = add(acc, pv[u]);
-      }
-      for (; t < nbt; t += 4)
-        if (tri_slot_used(t, r, tb0, ch)) acc = add(acc, P[(long)t * n + r]);
-#pragma unroll 4
-      for (int q = part; q < pp; q += 4) {
-        acc = sub(acc, mulr(V[(long)(j0 + q) * n + r], s_t1[q]));
-        acc = sub(acc, mulr(W[(long)r * NB + q], s_t2[q]));
+    for (int u = 0; u < PU; ++u) {
+      const int q = part + 4 * u;
+      if (q < pp) {
+        y = sub(y, mulr(vq[u], s_t[part][q]));
+        y = sub(y, mulr(wq[u], s_t[part][NB + q]));
       }
     }
-    const T yy = parts_sum(acc, s_red);
-    if (part == 0 && rv) {
-      const T w = add(mulr(taup, yy), mulr(alpha, vfin[r]));
-      W[(long)r * NB + pp] = w;
-    }
-    // rows above ifin + 1 carry a zero w
-    if (blockIdx.x == 0)
-      for (int q = tid; q < row0; q += 256) W[(long)q * NB + pp] = EigT<T>::zero();
-    __syncthreads();
+    s_col[part][lane] = y;
+    lds_barrier();
+    y = add(add(s_col[0][lane], s_col[1][lane]), add(s_col[2][lane], s_col[3][lane]));
+    wr = add(mulr(tau, y), mulr(alpha, vfin));
+    if (part == 0 && rv) W[(long)pp * n + r] = wr;
   }
   if (icol < 0) return;
 
-  // ---- column update of icol (row0 == icol) with p panel columns
-  const int i = icol, p = i - j0;
-  // row i of V and W (W(i, p-1) was just finished by the workgroup owning row i:
-  // recompute it here so that every workgroup has it without a grid-wide wait)
-  if (tid < p) {
-    s_vrow[tid] = V[(long)(j0 + tid) * n + i];
-    if (tid < p - 1 || ifin < 0) s_wrow[tid] = W[(long)i * NB + tid];
-  }
-  if (ifin >= 0 && p >= 1) {
-    // W(i, p-1): same formula as above for row i
-    const int pp = p - 1;
-    T acc = EigT<T>::zero();
-    const int tb0 = (ifin + 1) / TT, nbt = TriWs<T, NB>::nbt(n);
-    for (int t = tb0 + tid; t < nbt; t += 256)
-      if (tri_slot_used(t, i, tb0, ch)) acc = add(acc, P[(long)t * n + i]);
-    if (tid < pp) {
-      acc = sub(acc, mulr(V[(long)(j0 + tid) * n + i], s_t1[tid]));
-      acc = sub(acc, mulr(W[(long)i * NB + tid], s_t2[tid]));
-    }
-    const T yy = block_sum256(acc, s_sh4);
-    if (tid == 0) {
-      const T taup = reinterpret_cast<const T*>(a.tau)[b * a.stau + ifin];
-      s_wi = add(mulr(taup, yy), mulr(s_alpha, V[(long)ifin * n + i]));
-      s_wrow[pp] = s_wi;
+  // ---- column icol (= row0) minus its p panel terms
+  s_row[part][lane] = vw;
+  T acc = part == 0 ? gcol : zero;
+#pragma unroll
+  for (int u = 0; u < PU; ++u) {
+    const int q = part + 4 * u;
+    if (q < pp) {
+      acc = msub_cj(acc, vq[u], s_row[part][NB + q]);
+      acc = msub_cj(acc, wq[u], s_row[part][q]);
     }
   }
-  __syncthreads();
-  double xn2 = 0.0;
-  {
-    // the four groups of a row share the p panel terms
-    T acc = (part == 0 && rv) ? G[(long)r * ldg + i] : EigT<T>::zero();
+  if (part == 0 && p > pp) {                    // the column finished above: V(icol) = 1
+    acc = msub_cj(acc, vfin, wi);
+    acc = sub(acc, wr);
+  }
+  s_part[part][lane] = acc;
+  lds_barrier();
+  if (part == 0) {
+    acc = add(add(s_part[0][lane], s_part[1][lane]), add(s_part[2][lane], s_part[3][lane]));
+    double xn2 = 0.0;
     if (rv) {
-#pragma unroll 4
-      for (int q = part; q < p; q += 4) {
-        acc = sub(acc, mulr(V[(long)(j0 + q) * n + r], cj(s_wrow[q])));
-        acc = sub(acc, mulr(W[(long)r * NB + q], cj(s_vrow[q])));
-      }
+      G[(long)r * a.ldg + icol] = acc;
+      if (r >= icol + 1) xv[r] = acc;
+      if (r >= icol + 2) xn2 = nrm2(acc);
+      if (r == icol) a.d[b * a.sde + icol] = re(acc);
     }
-    acc = parts_sum(acc, s_red);
-    if (part == 0 && rv) {
-      G[(long)r * ldg + i] = acc;
-      if (r >= i + 1) xv[r] = acc;
-      if (r >= i + 2) xn2 = nrm2(acc);
-      if (r == i) a.d[b * a.sde + i] = re(acc);
-    }
+    // ||x||^2 partial of this block (summed by the next kernel)
+    xn2 = wave64_sum(xn2);
+    if (lane == 0 && icol + 1 < n) pa[blockIdx.x] = xn2;
   }
-  // ||x||^2 partial of this block (summed by the next kernel)
-  const double xsum = block_sum256(xn2, red);
-  if (tid == 0 && i + 1 < n) pa[blockIdx.x] = xsum;
 }
 
+// Every wave forms the reflector scalars for itself, so that no barrier stands
+// before the tiles.
 template <typename T, int NB>
 __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0, int ch) {
-  __shared__ T s_vR[TT];
+  __shared__ T s_vR[4][TT];
   __shared__ T s_q[4];
   __shared__ T s_colsum[2][4][TT];
-  __shared__ T s_tt[4][2 * NB];
-  static_assert(2 * NB == TT, "t1/t2 thread mapping assumes 2 NB == TT");
-  __shared__ T s_scal;
-  const int b = blockIdx.x, n = a.n, tid = threadIdx.x;
+  static_assert(2 * NB == TT, "t1/t2 mapping assumes 2 NB == TT");
+  const int b = blockIdx.x, n = a.n, tid = threadIdx.x, lane = tid & 63, part = tid >> 6;
   const int wg = (int)gridDim.y - 1 - (int)blockIdx.y;   // chunk: largest bands first
   const int p = i - j0;
   char* ws = reinterpret_cast<char*>(a.ws) + b * a.sws;
@@ -432,6 +442,7 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0,
   const T* G = reinterpret_cast<const T*>(a.G) + b * a.sG;
   T* V = reinterpret_cast<T*>(a.Vt) + b * a.sVt;
   const T* W = reinterpret_cast<const T*>(a.Wp) + b * a.sWp;
+  const T zero = EigT<T>::zero();
   // chunk -> (band R, first tile cA, last tile cB)
   const int b0 = (i + 1) / TT;
   int k = wg, R = b0;
@@ -443,138 +454,113 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0,
   }
   const int cA = b0 + k * ch, cB = min(R, cA + ch - 1);
   const bool has_diag = (cB == R);
-  // reflector scalars (every workgroup computes them from the norm partials of
-  // the column kernel, one per block of TT rows from row i)
+  T xc = xv[min(cA * TT + lane, n - 1)];
+  const T xr = xv[min(R * TT + lane, n - 1)];
+  const T x1 = xv[i + 1];
   double xn2 = 0.0;
-  if (tid < 64) {
-    const int na = (n - i + TT - 1) / TT;
-    for (int k = tid; k < na; k += 64) xn2 += pa[k];
-    xn2 = wave_sum(xn2);
+  for (int q = lane; q < (n - i + TT - 1) / TT; q += 64) xn2 += pa[q];
+  xn2 = wave64_sum(xn2);
+  double beta;
+  T tv, scal;
+  reflector_nr(x1, xn2, beta, tv, scal);
+  if (wg == 0 && tid == 0) {
+    a.e[b * a.sde + i] = beta;
+    reinterpret_cast<T*>(a.tau)[b * a.stau + i] = tv;
   }
-  if (tid == 0) {
-    double beta;
-    T tv, sc;
-    reflector(xv[i + 1], xn2, beta, tv, sc);
-    s_scal = sc;
-    if (wg == 0) {
-      a.e[b * a.sde + i] = beta;
-      reinterpret_cast<T*>(a.tau)[b * a.stau + i] = tv;
-    }
-  }
-  __syncthreads();
-  const T scal = s_scal;
-  auto vval = [&](int c) -> T {
-    if (c <= i || c >= n) return EigT<T>::zero();
-    if (c == i + 1) return EigT<T>::one();
-    return mulr(xv[c], scal);
+  auto vval = [&](int c, T x) -> T {
+    const T v = mulr(x, scal);
+    return c <= i || c >= n ? zero : c == i + 1 ? EigT<T>::one() : v;
   };
-  if (tid < TT) s_vR[tid] = vval(R * TT + tid);
-  __syncthreads();
+  const T vR = vval(R * TT + lane, xr);
+  s_vR[part][lane] = vR;                        // read back by this wave only
   // reflector i into Vt (the chunk holding the diagonal tile owns band R's
   // rows; chunk 0 zeroes the rows above the active blocks)
-  if (has_diag && tid < TT) {
-    const int rr = R * TT + tid;
-    if (rr < n) V[(long)i * n + rr] = s_vR[tid];
-  }
+  if (has_diag && part == 0 && R * TT + lane < n) V[(long)i * n + R * TT + lane] = vR;
   if (wg == 0)
-    for (int rr = tid; rr < b0 * TT; rr += 256) V[(long)i * n + rr] = EigT<T>::zero();
+    for (int rr = tid; rr < b0 * TT; rr += 256) V[(long)i * n + rr] = zero;
 
-  const int cl = tid & 63, rg = tid >> 6;
-  // row-sum accumulators of the two row halves (diagonal / off-diagonal tiles)
-  T rs_off0 = EigT<T>::zero(), rs_off1 = EigT<T>::zero();
-  T rs_dg0 = EigT<T>::zero(), rs_dg1 = EigT<T>::zero();
+  // row sums of the chunk: lane l of entry e = 2 h + m holds row
+  // part + 4 (4 e + l / 16)
+  T rs[4] = {zero, zero, zero, zero}, qd = zero, qo = zero;
 #pragma unroll 1
   for (int C = cA; C <= cB; ++C) {
     const bool diag = (C == R);
-    const int c = C * TT + cl;
-    const bool cok = (c > i) && (c < n);
-    const T vc = vval(c);
-    T colacc = EigT<T>::zero();
+    const int c = C * TT + lane;
+    const bool cok = c > i && c < n;
+    const T vc = vval(c, xc);
+    if (C < cB) xc = xv[min(c + TT, n - 1)];
+    T colacc = zero;
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
       T ps[8];
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
-        const int rl = rg + 4 * (kk + 8 * h);
-        const int r = R * TT + rl;
-        T g = EigT<T>::zero();
+        const int rl = part + 4 * (kk + 8 * h), r = R * TT + rl;
+        T g = zero;
         if (cok && r > i && r < n) g = G[(long)r * a.ldg + c];
-        ps[kk] = mulr(g, vc);                           // row-sum term
-        colacc = add(colacc, mulr(cj(g), s_vR[rl]));    // column-sum term
+        ps[kk] = mulr(g, vc);                              // row-sum term
+        colacc = mac_cj(colacc, g, s_vR[part][rl]);        // column-sum term
       }
-      // butterfly over lane bits 5..3 leaves lane l the partial of
-      // kk = (l >> 3) & 7 over 8 lanes; bits 2..0 finish the sum
+      T v[2];
 #pragma unroll
-      for (int half = 4, bit = 32; half >= 1; half >>= 1, bit >>= 1) {
-        const bool hi = (cl & bit) != 0;
-#pragma unroll
-        for (int t = 0; t < half; ++t) {
-          const T mine = hi ? ps[t + half] : ps[t];
-          const T other = hi ? ps[t] : ps[t + half];
-          ps[t] = add(mine, shfl_xor_t(other, bit));
-        }
+      for (int m = 0; m < 2; ++m) {
+        const T four[4] = {ps[4 * m], ps[4 * m + 1], ps[4 * m + 2], ps[4 * m + 3]};
+        v[m] = row16_sum(quarter_sum4(four));
+        const T w = s_vR[part][part + 4 * (8 * h + 4 * m + (lane >> 4))];
+        if (diag) qd = mac_cj(qd, w, v[m]);
+        else qo = mac_cj(qo, w, v[m]);
       }
-      T v = add(ps[0], shfl_xor_t(ps[0], 4));
-      v = add(v, shfl_xor_t(v, 2));
-      v = add(v, shfl_xor_t(v, 1));
-      if (diag) {
-        if (h == 0) rs_dg0 = add(rs_dg0, v);
-        else rs_dg1 = add(rs_dg1, v);
-      } else {
-        if (h == 0) rs_off0 = add(rs_off0, v);
-        else rs_off1 = add(rs_off1, v);
-      }
+      if (h == 0) { rs[0] = add(rs[0], v[0]); rs[1] = add(rs[1], v[1]); }
+      else { rs[2] = add(rs[2], v[0]); rs[3] = add(rs[3], v[1]); }
     }
     if (!diag) {
       const int sb = (C - cA) & 1;
-      s_colsum[sb][rg][cl] = colacc;
-      __syncthreads();
-      if (tid < TT) {
-        const T cs = add(add(s_colsum[sb][0][tid], s_colsum[sb][1][tid]),
-                         add(s_colsum[sb][2][tid], s_colsum[sb][3][tid]));
-        const int cc = C * TT + tid;
-        if (cc < n) P[(long)R * n + cc] = cs;
-      }
+      s_colsum[sb][part][lane] = colacc;
+      lds_barrier();
+      if (part == 0 && c < n)
+        P[(long)R * n + c] = add(add(s_colsum[sb][0][lane], s_colsum[sb][1][lane]),
+                                 add(s_colsum[sb][2][lane], s_colsum[sb][3][lane]));
     } else {
-      // t1 = W^H v and t2 = V^H v over the diagonal tile's rows: thread
-      // (q, part), q < NB for W's column q, q >= NB for V's row q - NB
-      const int q = tid & 63, part = tid >> 6, qq = q & (NB - 1);
-      T acc = EigT<T>::zero();
-      if (qq < p) {
-#pragma unroll 4
-        for (int kk = 0; kk < TT / 4; ++kk) {
-          const int rl = part * (TT / 4) + kk, r = R * TT + rl;
-          if (r > i && r < n) {
-            const T other = q < NB ? W[(long)r * NB + qq] : V[(long)(j0 + qq) * n + r];
-            acc = add(acc, mulr(cj(other), s_vR[rl]));
-          }
+      // t1 = W^H v and t2 = V^H v over the diagonal tile's rows: values
+      // m = 16 part .. + 15, m < NB for W's column m, else V's row m - NB
+#pragma unroll 1
+      for (int m0 = 16 * part; m0 < 16 * part + 16; m0 += 8) {
+        T tt[8];
+        const int rr = min(R * TT + lane, n - 1);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const T* src = m0 < NB ? W : V + (long)j0 * n;
+          tt[u] = src[(long)min((m0 + u) & (NB - 1), max(p - 1, 0)) * n + rr];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) tt[u] = ((m0 + u) & (NB - 1)) < p ? mulr(cj(tt[u]), vR) : zero;
+#pragma unroll
+        for (int u = 0; u < 8; u += 4) {
+          const T four[4] = {tt[u], tt[u + 1], tt[u + 2], tt[u + 3]};
+          const T v = row16_sum(quarter_sum4(four));
+          if ((lane & 15) == 0) pt[(long)(R - b0) * (2 * NB) + m0 + u + (lane >> 4)] = v;
         }
       }
-      s_tt[part][q] = acc;
     }
   }
   // row sums of the chunk -> P[cA][rows]; quadratic-form pieces
-  T qd = EigT<T>::zero(), qo = EigT<T>::zero();
-  if ((cl & 7) == 0) {
-    const int rl0 = rg + 4 * ((cl >> 3) & 7), rl1 = rl0 + 32;
-    const int r0 = R * TT + rl0, r1 = R * TT + rl1;
-    if (r0 < n) P[(long)cA * n + r0] = add(rs_dg0, rs_off0);
-    if (r1 < n) P[(long)cA * n + r1] = add(rs_dg1, rs_off1);
-    qd = add(mulr(cj(s_vR[rl0]), rs_dg0), mulr(cj(s_vR[rl1]), rs_dg1));
-    qo = add(mulr(cj(s_vR[rl0]), rs_off0), mulr(cj(s_vR[rl1]), rs_off1));
+  if ((lane & 15) == 0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = R * TT + part + 4 * (4 * e + (lane >> 4));
+      if (r < n) P[(long)cA * n + r] = rs[e];
+    }
   }
-  qd = wsum(qd);
-  qo = wsum(qo);
-  if (cl == 0) s_q[rg] = add(add(qd, qo), cj(qo));
-  __syncthreads();
+  qd = quarter_sum(qd);   // the 16 lanes of a row hold the same sums
+  qo = quarter_sum(qo);
+  if (lane == 0) s_q[part] = add(add(qd, qo), cj(qo));
+  lds_barrier();
   if (tid == 0) pc[wg] = add(add(s_q[0], s_q[1]), add(s_q[2], s_q[3]));
-  if (tid < 2 * NB && has_diag)
-    pt[(long)(R - b0) * (2 * NB) + tid] = add(add(s_tt[0][tid], s_tt[1][tid]), add(s_tt[2][tid], s_tt[3][tid]));
 }
 
 // Operands of the trailing update G -= V W^H + W V^H = [V W] [W V]^H over
 // rows and columns >= t: cat1 = [V_panel; W^T], cat2 = [W^T; V_panel] (rows
-// q < pe from V_panel = Vt rows j0 .., from W^T = W columns), columns >= t.
+// q < pe from V_panel = Vt rows j0 .., from W^T), columns >= t.
 template <typename T, int NB>
 __global__ __launch_bounds__(256) void tri_cat_kernel(TriArgs a, int j0, int pe, int t) {
   const int b = blockIdx.y, n = a.n;
@@ -587,7 +573,7 @@ __global__ __launch_bounds__(256) void tri_cat_kernel(TriArgs a, int j0, int pe,
   for (long long e = blockIdx.x * 256LL + threadIdx.x; e < tot; e += (long long)gridDim.x * 256) {
     const int q = (int)(e / (n - t)), r = t + (int)(e % (n - t));
     const T v = V[(long)(j0 + q) * n + r];
-    const T w = W[(long)r * NB + q];
+    const T w = W[(long)q * n + r];
     c1[(long)q * n + r] = v;
     c1[(long)(pe + q) * n + r] = w;
     c2[(long)q * n + r] = w;
@@ -670,58 +656,6 @@ static hipError_t tridiag_impl(const TriArgs& a, int batch, hipStream_t s) {
 // workgroup took 15 and 5.8 us per column (16 problems of order 200 complex
 // 3.07 ms, one of order 100 real 0.58 ms).
 // ---------------------------------------------------------------------------
-// Reflector scalars as in reflector(), without the division and square-root
-// sequences, which a column would wait for: refined hardware seeds.
-__device__ inline double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) y = __builtin_fma(y * 0.5, __builtin_fma(-x * y, y, 1.0), y);
-  return y;
-}
-__device__ inline double rcp_nr(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
-  return y;
-}
-template <typename T>
-__device__ inline void reflector_nr(T alpha, double xn2, double& beta, T& tau, T& scal) {
-  const double ar = re(alpha), ai = im(alpha), sum = ar * ar + ai * ai + xn2;
-  if ((xn2 == 0.0 && ai == 0.0) || !(sum > 1e-280 && sum < 1e280)) {
-    reflector(alpha, xn2, beta, tau, scal);
-    return;
-  }
-  const double rs = rsqrt_nr(sum), sg = ar >= 0.0 ? -1.0 : 1.0, ib = sg * rs;
-  beta = sum * ib;
-  const double xr = ar - beta;
-  if constexpr (sizeof(T) == sizeof(double)) {
-    tau = -xr * ib;
-    scal = rcp_nr(xr);
-  } else {
-    const double iden = rcp_nr(xr * xr + ai * ai);
-    tau = cd{-xr * ib, -ai * ib};
-    scal = cd{xr * iden, -ai * iden};
-  }
-}
-
-// acc + a b, acc + conj(a) b, acc - a conj(b) with fused multiply-adds only
-__device__ inline double mac(double c, double a, double b) { return __builtin_fma(a, b, c); }
-__device__ inline double mac_cj(double c, double a, double b) { return __builtin_fma(a, b, c); }
-__device__ inline double msub_cj(double c, double a, double b) { return __builtin_fma(-a, b, c); }
-__device__ inline cd mac(cd c, cd a, cd b) {
-  return cd{__builtin_fma(-a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
-}
-__device__ inline cd mac_cj(cd c, cd a, cd b) {
-  return cd{__builtin_fma(a.y, b.y, __builtin_fma(a.x, b.x, c.x)), __builtin_fma(-a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
-}
-__device__ inline cd msub_cj(cd c, cd a, cd b) {
-  return cd{__builtin_fma(-a.y, b.y, __builtin_fma(-a.x, b.x, c.x)), __builtin_fma(-a.y, b.x, __builtin_fma(a.x, b.y, c.y))};
-}
-
-// Barrier for data exchanged through LDS only: __syncthreads would also wait
-// for the column's stores to global memory, a memory round trip per barrier.
-__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <typename T, int NB, int JL>
 __global__ __launch_bounds__(512) void tri_chip_kernel(TriArgs a, int i0) {
   constexpr int NT = 512, NW = NT / 64, NC = 2 * NB, NN = 32 * NB, JC = 4;

@@ -12,7 +12,7 @@ constexpr int TRIDIAG_BAND = 64;
 // Layout per problem (row-major unless stated), problems strided by s*:
 //   G    n x n, ld ldg      the Hermitian matrix; read (and overwritten) only at col - row < TRIDIAG_BAND
 //   Vt   n x n, ld n        Vt[c * n + r] = reflector c at row r (0 for r <= c, 1 at r = c+1)
-//   Wp   n x NB, ld NB      panel W of the blocked reduction
+//   Wp   NB x n, ld n       panel W^T of the blocked reduction
 //   y    n                  Hermitian matrix-vector product
 //   d, e (real), tau        tridiagonal diagonal / off-diagonal, reflector scalars (dtype)
 struct TriArgs {
