@@ -751,54 +751,72 @@ static hipError_t launch(K kern, const GemmArgs& a, int BM, int BN, hipStream_t 
   return hipGetLastError();
 }
 
-// Number of K chunks for an FP64 launch (1 = no split).  Model: the chip runs
-// 256 workgroups per round (one per compute unit), each at SPLITK_CU_RATE; a
-// launch of W equal workgroups takes ceil(W / 256) rounds.  Cutting K into sp
-// chunks multiplies W by sp and divides a round by sp, and adds a reduction
-// pass that writes and reads sp partial slabs.  The cheapest sp wins (by 5%
-// at least), with chunks of SPLITK_MIN_K or more and within the caller's
-// scratch.
+// Tile shape and number of K chunks of an FP64 launch.  A 16 x 16 x 4 product
+// takes 64 cycles of a SIMD, so the four waves of a BM x BN complex tile spend
+// BM * BN cycles per k tile of 16 (a quarter of that when real): a small output
+// in one large tile is one long chain (100 x 100 x 100 complex: 40 us in two
+// 128 x 64 tiles, 13 us in sixteen of 32 x 32).  Model, in cycles: the
+// chip runs 256 workgroups per round, each round its k tiles at that rate; a
+// chain pays TILE_LAT per k tile once and TILE_SETUP for its first loads and
+// its epilogue; cutting K into sp chunks adds a reduction pass that writes and
+// reads sp partial slabs.  The largest tile and the fewest chunks win unless
+// another choice is 10% cheaper.  Chunks have SPLITK_MIN_K or more and fit the
+// caller's scratch.  Neither choice changes the order of the sums within a
+// chunk, so the tile shape does not change a result.
 constexpr int SPLITK_MIN_K = 128;
 constexpr int SPLITK_MAX = 32;
 constexpr long long SPLITK_MAX_TILES = 1024;
-constexpr double SPLITK_CU_RATE = 0.3e12;      // FP64 MFMA flop/s of one compute unit
+constexpr double CYCLES_PER_S = 2.4e9;
+constexpr double TILE_LAT = 1500.0, TILE_SETUP = 8000.0;
 constexpr double SPLITK_REDUCE_BW = 4.0e12;    // bytes/s of the reduction pass
 constexpr double SPLITK_LAUNCH_S = 5e-6;
 
-static int splitk_chunks(const GemmArgs& a, int BM, int BN, size_t es) {
-  if (!a.kws || a.dims || a.lower_band > 0 || a.k < 2 * SPLITK_MIN_K) return 1;
-  const long long tiles = (long long)((a.n + BN - 1) / BN) * ((a.m + BM - 1) / BM) * a.batch;
-  if (tiles >= SPLITK_MAX_TILES) return 1;
-  const double wg_s = (es == 16 ? 8.0 : 2.0) * BM * BN * (double)a.k / SPLITK_CU_RATE;   // one unsplit tile
-  const double slab = (double)es * a.m * a.n * a.batch;
-  auto rounds = [](long long w) { return (double)((w + 255) / 256); };
-  int best = 1;
-  double best_t = rounds(tiles) * wg_s;
-  const int spmax = std::min<long long>(SPLITK_MAX, a.k / SPLITK_MIN_K);
-  for (int sp = 2; sp <= spmax; ++sp) {
-    if (sp * slab > (double)a.kws_bytes) break;
-    const double t = rounds(tiles * sp) * wg_s / sp + 2.0 * sp * slab / SPLITK_REDUCE_BW + SPLITK_LAUNCH_S;
-    if (t < 0.95 * best_t) {
-      best = sp;
-      best_t = t;
+struct F64Plan {
+  int bm, bn, sp;
+};
+
+static F64Plan f64_plan(const GemmArgs& a, bool cplx) {
+  const int bms[3] = {128, 64, 32}, bns[3] = {cplx ? 64 : 128, 64, 32};
+  F64Plan best{bms[0], bns[0], 1};
+  double best_t = 0.0;
+  const double slab = (cplx ? 16.0 : 8.0) * a.m * a.n * a.batch;
+  for (int c = 0; c < 3; ++c) {
+    const int bm = bms[c], bn = bns[c];
+    const long long tiles = (long long)((a.n + bn - 1) / bn) * ((a.m + bm - 1) / bm) * a.batch;
+    int spmax = 1;
+    if (a.kws && !a.dims && a.lower_band <= 0 && a.k >= 2 * SPLITK_MIN_K && tiles < SPLITK_MAX_TILES)
+      spmax = std::min(SPLITK_MAX, a.k / SPLITK_MIN_K);
+    if ((a.m + bm - 1) / bm > 65535) continue;   // grid limit
+    for (int sp = 1; sp <= spmax; ++sp) {
+      if (sp > 1 && sp * slab > (double)a.kws_bytes) break;
+      const double kt = std::ceil(std::ceil(a.k / 16.0) / sp);
+      const double rounds = (double)((tiles * sp + 255) / 256);
+      double t = rounds * kt * bm * bn * (cplx ? 1.0 : 0.25) + kt * TILE_LAT + TILE_SETUP;
+      if (sp > 1) t += CYCLES_PER_S * (2.0 * sp * slab / SPLITK_REDUCE_BW + SPLITK_LAUNCH_S);
+      if (best_t == 0.0 || t < 0.9 * best_t) {
+        best = F64Plan{bm, bn, sp};
+        best_t = t;
+      }
     }
   }
   return best;
 }
 
-template <typename T, int BM, int BN>
+template <typename T>
 static hipError_t launch_f64(const GemmArgs& a0, hipStream_t s) {
   GemmArgs a = a0;
-  a.ksplit = splitk_chunks(a, BM, BN, sizeof(T));
-  if (a.ksplit <= 1) {
-    a.ksplit = 0;
-    return launch(gemm_f64_kernel<T, BM, BN>, a, BM, BN, s);
+  const F64Plan pl = f64_plan(a, Elem<T>::cplx);
+  a.ksplit = pl.sp > 1 ? pl.sp : 0;
+  const dim3 grid((a.n + pl.bn - 1) / pl.bn, (a.m + pl.bm - 1) / pl.bm, a.batch * pl.sp);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
+  if (pl.bm == 128) go(gemm_f64_kernel<T, 128, Elem<T>::cplx ? 64 : 128>);
+  else if (pl.bm == 64) go(gemm_f64_kernel<T, 64, 64>);
+  else go(gemm_f64_kernel<T, 32, 32>);
+  if (a.ksplit > 1) {
+    const long long mn = (long long)a.m * a.n;
+    const unsigned gx = (unsigned)std::min<long long>(1024, (mn + 255) / 256);
+    hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(gx, a.batch), dim3(256), 0, s, a);
   }
-  dim3 grid((a.n + BN - 1) / BN, (a.m + BM - 1) / BM, a.batch * a.ksplit);
-  hipLaunchKernelGGL((gemm_f64_kernel<T, BM, BN>), grid, dim3(256), 0, s, a);
-  const long long mn = (long long)a.m * a.n;
-  const unsigned gx = (unsigned)std::min<long long>(1024, (mn + 255) / 256);
-  hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(gx, a.batch), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -828,9 +846,9 @@ hipError_t gemm(int dtype, int prec, const GemmArgs& a, hipStream_t s) {
   }
   switch (dtype) {
     case C128:
-      return launch_f64<cd, 128, 64>(a, s);
+      return launch_f64<cd>(a, s);
     case F64:
-      return launch_f64<double, 128, 128>(a, s);
+      return launch_f64<double>(a, s);
     case C64:
       if (prec == PREC_BF16X3) return launch(gemm_bf16x3_kernel<cf, 64, 64>, a, 64, 64, s);
       return launch(gemm_f32_kernel<cf, 128, 64>, a, 128, 64, s);

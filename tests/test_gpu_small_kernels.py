@@ -108,3 +108,17 @@ def test_singular_values_of_padded_batches(T, ctx, batch, chi):
         k = chi - 20    # well above the rounding level of the Gram matrix
         assert np.abs(x[:k] ** 2 - r[:k] ** 2).max() < 8 * n * U64 * r[0] ** 2
         assert np.all(x[chi:] ** 2 < 8 * n * U64 * r[0] ** 2)
+
+
+# complex FP64 tiles are 128 x 64, 64 x 64 or 32 x 32 by the size of the launch: a single element, remainders of each
+# tile, a long inner dimension (split) on a small output, and sizes that choose each shape
+@pytest.mark.parametrize("complex_,m,n,k", [(True, 1, 1, 1), (True, 33, 31, 17), (True, 31, 65, 1), (True, 129, 63, 300),
+                                            (True, 520, 530, 40), (True, 1100, 1000, 33), (True, 2050, 2047, 19),
+                                            (False, 33, 70, 5), (False, 65, 64, 1000), (False, 1030, 1040, 20),
+                                            (False, 2300, 2200, 18), (True, 40, 40, 3000)])
+def test_fp64_product_tiles(T, ctx, complex_, m, n, k):
+    """Sums of k products: error at most about 2 k u of sum |a||b| per element (four real products when complex)."""
+    a, b = draw((m, k), complex_, m + k), draw((k, n), complex_, n + 2 * k)
+    dt = T.C128 if complex_ else T.F64
+    c = T.contract(ctx, T.Tensor.from_numpy(ctx, a, dt), "ik", T.Tensor.from_numpy(ctx, b, dt), "kj", "ij").numpy()
+    assert np.all(np.abs(c - a @ b) <= 4 * (k + 2) * U64 * (np.abs(a) @ np.abs(b)))
