@@ -72,77 +72,168 @@ __device__ inline float gelu_d(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * expf(-0.5f * x * x) * 0.3989422804014327f;
 }
 
-// Forward of one sample per workgroup (128 threads); z1, z2 (n x 128) kept for backward.
-__global__ __launch_bounds__(128) void mlp_forward_kernel(const float* __restrict__ p, const float* __restrict__ X,
-                                                          int n, float* z1o, float* z2o, float* y) {
-  __shared__ float x[NI], h1[NH], h2[NH], red[2];
-  const int s = blockIdx.x, j = threadIdx.x;
-  if (s >= n) return;
-  if (j < NI) x[j] = X[(long long)s * NI + j];
+// Forward of SPB samples per workgroup (128 threads, thread j = hidden unit j)
+// and, when `grad` is set, the backward pass down to the units' derivatives:
+// rows s of h1, g2, g1, h2 (n x 128) and gy, loss (n).  With few samples a
+// workgroup per sample spreads them over the chip; with many, SPB samples
+// share each read of the weights.  W2's row of a thread is read four at a time.
+struct MlpWork {
+  float *h1, *g2, *g1, *h2, *gy, *loss;
+};
+
+template <int SPB>
+__global__ __launch_bounds__(128) void mlp_sample_kernel(const float* __restrict__ p, const float* __restrict__ X,
+                                                         const float* __restrict__ T, int n, float* y, MlpWork w,
+                                                         bool grad) {
+  __shared__ float x[SPB][NI], h1[SPB][NH], g2[SPB][NH], red[SPB][2];
+  const int s0 = blockIdx.x * SPB, j = threadIdx.x;
+  for (int e = j; e < SPB * NI; e += NH) x[e / NI][e % NI] = s0 + e / NI < n ? X[(long long)s0 * NI + e] : 0.f;
   __syncthreads();
-  float a = p[OFF_B1 + j];
-  for (int i = 0; i < NI; ++i) a += p[OFF_W1 + j * NI + i] * x[i];
-  if (z1o) z1o[(long long)s * NH + j] = a;
-  h1[j] = gelu(a);
+  float a[SPB], b[SPB], h2[SPB];
+#pragma unroll
+  for (int q = 0; q < SPB; ++q) a[q] = p[OFF_B1 + j];
+#pragma unroll 5
+  for (int i = 0; i < NI; ++i) {
+    const float wv = p[OFF_W1 + j * NI + i];
+#pragma unroll
+    for (int q = 0; q < SPB; ++q) a[q] += wv * x[q][i];
+  }
+#pragma unroll
+  for (int q = 0; q < SPB; ++q) {
+    h1[q][j] = gelu(a[q]);
+    b[q] = p[OFF_B2 + j];
+  }
   __syncthreads();
-  float b = p[OFF_B2 + j];
-  for (int i = 0; i < NH; ++i) b += p[OFF_W2 + j * NH + i] * h1[i];
-  if (z2o) z2o[(long long)s * NH + j] = b;
-  h2[j] = gelu(b);
-  float c = p[OFF_W3 + j] * h2[j];
-  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-  if ((j & 63) == 0) red[j >> 6] = c;
+  static_assert(OFF_W2 % 4 == 0 && NH % 4 == 0, "16-byte rows of W2");
+  const float4* w2 = reinterpret_cast<const float4*>(p + OFF_W2 + j * NH);
+#pragma unroll 8
+  for (int i = 0; i < NH / 4; ++i) {
+    const float4 v = w2[i];
+#pragma unroll
+    for (int q = 0; q < SPB; ++q) {
+      b[q] += v.x * h1[q][4 * i];
+      b[q] += v.y * h1[q][4 * i + 1];
+      b[q] += v.z * h1[q][4 * i + 2];
+      b[q] += v.w * h1[q][4 * i + 3];
+    }
+  }
+  const float w3 = p[OFF_W3 + j];
+#pragma unroll
+  for (int q = 0; q < SPB; ++q) {
+    h2[q] = gelu(b[q]);
+    float c = w3 * h2[q];
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if ((j & 63) == 0) red[q][j >> 6] = c;
+  }
   __syncthreads();
-  if (j == 0) y[s] = red[0] + red[1] + p[OFF_B3];
+  if (!grad) {
+    if (j < SPB && s0 + j < n) y[s0 + j] = red[j][0] + red[j][1] + p[OFF_B3];
+    return;
+  }
+  // d loss / d y of the mean pinball loss, then the units' derivatives
+#pragma unroll
+  for (int q = 0; q < SPB; ++q) {
+    const int s = s0 + q;
+    const float u = s < n ? T[s] - (red[q][0] + red[q][1] + p[OFF_B3]) : 0.f;
+    const float gy = (u < 0.f ? (1.f - TAU) : -TAU) / (float)n;
+    g2[q][j] = gy * w3 * gelu_d(b[q]);
+    if (s < n) {
+      w.h1[(long long)s * NH + j] = h1[q][j];
+      w.h2[(long long)s * NH + j] = h2[q];
+      w.g2[(long long)s * NH + j] = g2[q][j];
+      if (j == 0) {
+        w.gy[s] = gy;
+        w.loss[s] = fmaxf(TAU * u, (TAU - 1.f) * u) / (float)n;
+      }
+    }
+  }
+  __syncthreads();
+  float gh[SPB] = {};
+#pragma unroll 8
+  for (int r = 0; r < NH; ++r) {
+    const float wv = p[OFF_W2 + r * NH + j];
+#pragma unroll
+    for (int q = 0; q < SPB; ++q) gh[q] += g2[q][r] * wv;
+  }
+#pragma unroll
+  for (int q = 0; q < SPB; ++q)
+    if (s0 + q < n) w.g1[(long long)(s0 + q) * NH + j] = gh[q] * gelu_d(a[q]);
 }
 
-// Per-sample gradient of the mean pinball loss (one sample per workgroup),
-// written to G[s][0..NPARAM); loss_s = rho(t - y) / n.
-__global__ __launch_bounds__(128) void mlp_backward_kernel(const float* __restrict__ p, const float* __restrict__ X,
-                                                           const float* __restrict__ T, int n, const float* z1,
-                                                           const float* z2, const float* y, float* G, float* loss) {
-  __shared__ float x[NI], h1[NH], gz2[NH];
-  const int s = blockIdx.x, j = threadIdx.x;
-  if (s >= n) return;
-  float* g = G + (long long)s * NPARAM;
-  if (j < NI) x[j] = X[(long long)s * NI + j];
-  const float a1 = z1[(long long)s * NH + j];
-  const float a2 = z2[(long long)s * NH + j];
-  h1[j] = gelu(a1);
-  const float u = T[s] - y[s];
-  const float gy = (u < 0.f ? (1.f - TAU) : -TAU) / (float)n;
-  if (j == 0) {
-    loss[s] = fmaxf(TAU * u, (TAU - 1.f) * u) / (float)n;
-    g[OFF_B3] = gy;
+// Weight gradients as products over the samples: dW2 = g2^T [h1 | 1] (its last
+// column is db2), dW1 = g1^T [x | 1], dW3 = gy^T [h2 | 1], in 32 x 32 tiles.
+// Block (tile, chunk) sums MLP_CHUNK-sample stages of its chunk in FP32 and
+// writes its part of the flat gradient to part[chunk].  (A gradient row of
+// 21249 values per sample, summed by one thread per value, took 93 us of a
+// batch of 256 and 85 KB of workspace per sample.)
+constexpr int MLP_STAGE = 64, MLP_TILES = 20 + 8 + 5, MLP_MAX_CHUNKS = 32;
+
+__global__ __launch_bounds__(256) void mlp_grad_kernel(const float* __restrict__ X, int n, MlpWork w, int per_chunk,
+                                                       float* part) {
+  __shared__ float As[MLP_STAGE][33], Bs[MLP_STAGE][33];
+  const int t = blockIdx.x, tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+  // operands (rows = samples) with their widths, and the flat offsets of the weights and the bias
+  const float *A, *B;
+  int wa, wb, rt, ct, offw, offb;
+  if (t < 20) {
+    A = w.g2; B = w.h1; wa = NH; wb = NH; rt = t / 5; ct = t % 5; offw = OFF_W2; offb = OFF_B2;
+  } else if (t < 28) {
+    A = w.g1; B = X; wa = NH; wb = NI; rt = (t - 20) / 2; ct = (t - 20) % 2; offw = OFF_W1; offb = OFF_B1;
+  } else {
+    A = w.gy; B = w.h2; wa = 1; wb = NH; rt = 0; ct = t - 28; offw = OFF_W3; offb = OFF_B3;
   }
-  const float h2j = gelu(a2);
-  g[OFF_W3 + j] = gy * h2j;
-  const float gzj = gy * p[OFF_W3 + j] * gelu_d(a2);
-  gz2[j] = gzj;
-  g[OFF_B2 + j] = gzj;
-  __syncthreads();
-  for (int i = 0; i < NH; ++i) g[OFF_W2 + j * NH + i] = gzj * h1[i];
-  // g_h1[j] = sum_r gz2[r] W2[r][j]
-  float gh = 0.f;
-  for (int r = 0; r < NH; ++r) gh += gz2[r] * p[OFF_W2 + r * NH + j];
-  const float g1 = gh * gelu_d(a1);
-  g[OFF_B1 + j] = g1;
-  for (int i = 0; i < NI; ++i) g[OFF_W1 + j * NI + i] = g1 * x[i];
+  const int r0 = 32 * rt, c0 = 32 * ct;
+  const int sbeg = blockIdx.y * per_chunk, send = min(n, sbeg + per_chunk);
+  float acc[2][2] = {};
+  for (int s0 = sbeg; s0 < send; s0 += MLP_STAGE) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < MLP_STAGE * 32 / 256; ++u) {
+      const int e = tid + 256 * u, k = e >> 5, c = e & 31, s = s0 + k;
+      As[k][c] = s < send && r0 + c < wa ? A[(long long)s * wa + r0 + c] : 0.f;
+      Bs[k][c] = s < send && c0 + c < wb ? B[(long long)s * wb + c0 + c] : s < send && c0 + c == wb ? 1.f : 0.f;
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int k = 0; k < MLP_STAGE; ++k) {
+      const float a0 = As[k][2 * ti], a1 = As[k][2 * ti + 1], b0 = Bs[k][2 * tj], b1 = Bs[k][2 * tj + 1];
+      acc[0][0] += a0 * b0;
+      acc[0][1] += a0 * b1;
+      acc[1][0] += a1 * b0;
+      acc[1][1] += a1 * b1;
+    }
+  }
+  float* g = part + (long long)blockIdx.y * NPARAM;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int r = r0 + 2 * ti + u, c = c0 + 2 * tj + v;
+      if (r >= wa) continue;
+      if (c < wb) g[offw + r * wb + c] = acc[u][v];
+      else if (c == wb) g[offb + r] = acc[u][v];
+    }
 }
 
-// grad[q] = sum_s G[s][q] (fixed order), loss_total = sum_s loss[s] (thread 0)
-__global__ void mlp_reduce_kernel(const float* G, const float* loss, int n, float* grad, float* loss_total) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < NPARAM) {
-    float acc = 0.f;
-    for (int s = 0; s < n; ++s) acc += G[(long long)s * NPARAM + q];
-    grad[q] = acc;
-  }
-  if (q == 0) {
+// grad[q] = sum over the chunks in order; the last block sums the losses.
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* part, int nchunk, const float* loss, int n,
+                                                         float* grad, float* loss_total) {
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ float red[4];
     float l = 0.f;
-    for (int s = 0; s < n; ++s) l += loss[s];
-    *loss_total = l;
+    for (int s = threadIdx.x; s < n; s += 256) l += loss[s];
+    l = wave_sum(l);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
+    __syncthreads();
+    if (threadIdx.x == 0) *loss_total = red[0] + red[1] + red[2] + red[3];
+    return;
   }
+  const int q = blockIdx.x * 256 + threadIdx.x;
+  if (q >= NPARAM) return;
+  float acc = 0.f;
+#pragma unroll 8
+  for (int c = 0; c < nchunk; ++c) acc += part[(long long)c * NPARAM + q];
+  grad[q] = acc;
 }
 
 __global__ void adam_kernel(float* p, float* m, float* v, const float* g, float lr, float b1, float b2, float eps,
@@ -182,18 +273,29 @@ static tci_status model_check(tci_sketch_model m) {
   return TCI_OK;
 }
 
+// One sample per workgroup up to two per compute unit, four above.
+static void mlp_samples(const float* p, const float* X, const float* T, int n, float* y, const MlpWork& w, bool grad,
+                        hipStream_t s) {
+  if (n <= 512) hipLaunchKernelGGL(mlp_sample_kernel<1>, dim3(n), dim3(NH), 0, s, p, X, T, n, y, w, grad);
+  else hipLaunchKernelGGL(mlp_sample_kernel<4>, dim3((n + 3) / 4), dim3(NH), 0, s, p, X, T, n, y, w, grad);
+}
+
 static tci_status grads_impl(tci_context ctx, tci_sketch_model m, const float* X, const float* T, int n, float* grad,
                              float* loss_dev) {
   hipStream_t s = ctx->stream;
-  float* z1 = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n * NH));
-  float* z2 = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n * NH));
-  float* y = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n));
-  float* G = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n * NPARAM));
-  float* ls = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n));
-  if (!z1 || !z2 || !y || !G || !ls) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "mlp workspace");
-  hipLaunchKernelGGL(mlp_forward_kernel, dim3(n), dim3(NH), 0, s, m->params, X, n, z1, z2, y);
-  hipLaunchKernelGGL(mlp_backward_kernel, dim3(n), dim3(NH), 0, s, m->params, X, T, n, z1, z2, y, G, ls);
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 255) / 256), dim3(256), 0, s, G, ls, n, grad, loss_dev);
+  // chunks of whole stages, at most MLP_MAX_CHUNKS (the reduction reads each once)
+  const int stages = (n + MLP_STAGE - 1) / MLP_STAGE;
+  const int per_chunk = (stages + MLP_MAX_CHUNKS - 1) / MLP_MAX_CHUNKS * MLP_STAGE;
+  const int nchunk = (n + per_chunk - 1) / per_chunk;
+  float* rows = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n * (4 * NH + 2)));
+  float* part = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)nchunk * NPARAM));
+  if (!rows || !part) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "mlp workspace");
+  const size_t nh = (size_t)n * NH;
+  const MlpWork w{rows, rows + nh, rows + 2 * nh, rows + 3 * nh, rows + 4 * nh, rows + 4 * nh + n};
+  mlp_samples(m->params, X, T, n, nullptr, w, true, s);
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3(MLP_TILES, nchunk), dim3(256), 0, s, X, n, w, per_chunk, part);
+  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 255) / 256 + 1), dim3(256), 0, s, (const float*)part, nchunk,
+                     (const float*)w.loss, n, grad, loss_dev);
   TCI_CHECK_HIP(hipGetLastError());
   return TCI_OK;
 }
@@ -203,8 +305,7 @@ int sketch_model_nparams() { return NPARAM; }
 tci_status sketch_predict_dev(tci_context ctx, tci_sketch_model m, const float* X, int n, float* y) {
   TCI_TRY(model_check(m));
   if (n <= 0) return TCI_OK;
-  hipLaunchKernelGGL(mlp_forward_kernel, dim3(n), dim3(NH), 0, ctx->stream, m->params, X, n, (float*)nullptr,
-                     (float*)nullptr, y);
+  mlp_samples(m->params, X, nullptr, n, y, MlpWork{}, false, ctx->stream);
   TCI_CHECK_HIP(hipGetLastError());
   return TCI_OK;
 }

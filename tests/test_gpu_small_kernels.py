@@ -122,3 +122,28 @@ def test_fp64_product_tiles(T, ctx, complex_, m, n, k):
     dt = T.C128 if complex_ else T.F64
     c = T.contract(ctx, T.Tensor.from_numpy(ctx, a, dt), "ik", T.Tensor.from_numpy(ctx, b, dt), "kj", "ij").numpy()
     assert np.all(np.abs(c - a @ b) <= 4 * (k + 2) * U64 * (np.abs(a) @ np.abs(b)))
+
+
+# 64 samples per stage, one per workgroup up to 512 and four above, more than one stage per chunk above 2048
+@pytest.mark.parametrize("n", [1, 63, 65, 512, 513, 2051])
+def test_sketch_gradients(T, ctx, n):
+    """FP32 sums of n products of values of order one: error at most about n 2^-24 of the sum of magnitudes, which
+    a gradient of the mean bounds by 2^-24 n times its largest entries; a few thousand ulps here."""
+    g = torch.Generator().manual_seed(n)
+    X, t = torch.rand((n, 35), generator=g) * 2 - 1, torch.rand(n, generator=g) * 8
+    m = T.SketchModel(ctx, seed=3)
+    flat = torch.from_numpy(m.params()).double().requires_grad_(True)
+    h, at = X.double(), 0
+    for k, (r, c) in enumerate(((128, 35), (128, 128), (1, 128))):
+        h = h @ flat[at:at + r * c].reshape(r, c).t() + flat[at + r * c:at + r * c + r]
+        h = torch.nn.functional.gelu(h) if k < 2 else h
+        at += r * c + r
+    u = t.double() - h[:, 0]
+    ref = torch.maximum(0.9 * u, -0.1 * u).mean()
+    ref.backward()
+    loss, grad = m.grads(X, t)
+    ref = float(ref.detach())
+    assert abs(loss - ref) < 2e-5 * ref
+    err = (grad.cpu().double() - flat.grad).abs().max() / flat.grad.abs().max()
+    assert float(err) < 2e-5
+    assert float((m.predict(X).cpu().double() - h[:, 0].detach()).abs().max()) < 2e-5 * float(h.detach().abs().max())
