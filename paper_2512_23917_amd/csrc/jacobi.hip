@@ -18,10 +18,13 @@
 // them at once.  V and, when it fits, W live in LDS.  A step is a chain of
 // latencies (LDS read, reduction, rotation scalars, LDS write, barrier), so
 // the scalars come from reciprocal-square-root seeds refined by two Newton
-// steps instead of the division and square-root sequences.  One complex
-// problem takes 367 us at 32 x 32 (1.3 us per step) and 1788 us at 64 x 64
-// (bound by LDS bandwidth: a step moves up to 256 KiB); four waves that took
-// the pairs in turn from global memory, a wave per pair, ran 2218 and 11220 us.
+// steps instead of the division and square-root sequences, the column norms
+// are carried along within a sweep, and up to 64 rows a lane holds its elements
+// in registers from the inner product to the rotation.  One complex problem
+// takes 330 us at 32 x 32 (1.1 us per step) and 1519 us at 64 x 64 (a step
+// moves up to 192 KiB of LDS); with the norms summed in every step 367 and 1788
+// us; four waves that took the pairs in turn from global memory, a wave per
+// pair, 2218 and 11220 us.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -152,8 +155,9 @@ __device__ void complete_vector(T* P, long long vs, long long is, int len, int r
 // ties) made real positive, the matching vh row scaled by the conjugate
 // phase.  sweeps[b] receives the sweep count (-1 if not converged).
 // LDS: bytes of shared memory; W_LDS: W fits there beside V (otherwise W is
-// the global workspace Wk).
-template <typename T, int NT, int LDS, bool W_LDS>
+// the global workspace Wk).  MI > 0: m <= 16 MI, and a lane keeps its elements
+// of both columns in registers between the inner product and the rotation.
+template <typename T, int NT, int LDS, bool W_LDS, int MI>
 __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long lda, long long sA, int m, int n,
                                                         int wide, T* Wk, long long sW, T* u, long long su, T* vh,
                                                         long long svh, double* s, long long ss, int* sweeps,
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
   if constexpr (W_LDS) W = reinterpret_cast<T*>(smem) + n * n;
   else W = Wk + b * sW;
   __shared__ int rotated;
-  __shared__ double sig[JACOBI_MAX_K];
+  __shared__ double sig[JACOBI_MAX_K];   // squared column norms; at the end the singular values
   __shared__ int rank_of[JACOBI_MAX_K];
   using Idx = std::conditional_t<W_LDS, int, long long>;
   // load and V = I
@@ -190,7 +194,17 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
   int sweep = 0;
   bool conv = (n < 2);
   for (; !conv && sweep < max_sweeps; ++sweep) {
+    // squared norms afresh in every sweep; within it the rotations carry them
+    // along (|w_p|^2 - t |g|, |w_q|^2 + t |g|).  Their rounding can only spoil an
+    // angle or postpone a rotation: the sweep that ends the iteration rotated
+    // nothing and used the fresh norms.
     if (tid == 0) rotated = 0;
+    for (int j = slot; j < n; j += NT / 16) {
+      double nn = 0.0;
+      for (int i = sub; i < m; i += 16) nn += sq(W[(Idx)j * m + i]);
+      nn = row_sum(nn);
+      if (sub == 0) sig[j] = nn;
+    }
     __syncthreads();
     // players of this slot: position 0 is fixed, the others advance by one per step
     int t1 = slot == 0 ? 0 : slot, t2 = N - 1 - slot;
@@ -199,16 +213,21 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
       if (slot < N / 2 && q < n) {
         T* wp = W + (Idx)p * m;
         T* wq = W + (Idx)q * m;
-        double al = 0.0, be = 0.0;
+        const double al = sig[p], be = sig[q];
         T ga = zero_of(T{});
-        for (int i = sub; i < m; i += 16) {
-          const T x = wp[i], y = wq[i];
-          al += sq(x);
-          be += sq(y);
-          ga = addv(ga, mulr(cj(x), y));
+        T x[MI > 0 ? MI : 1], y[MI > 0 ? MI : 1];
+        if constexpr (MI > 0) {
+#pragma unroll
+          for (int k = 0; k < MI; ++k) {
+            const int i = sub + 16 * k;
+            x[k] = i < m ? wp[i] : zero_of(T{});
+            y[k] = i < m ? wq[i] : zero_of(T{});
+          }
+#pragma unroll
+          for (int k = 0; k < MI; ++k) ga = addv(ga, mulr(cj(x[k]), y[k]));
+        } else {
+          for (int i = sub; i < m; i += 16) ga = addv(ga, mulr(cj(wp[i]), wq[i]));
         }
-        al = row_sum(al);
-        be = row_sum(be);
         ga = row_sum(ga);
         double ag, ig;
         modulus(ga, ag, ig);
@@ -228,19 +247,36 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
           if (zeta < 0.0) t = -t;
           const double c = rsqrt_nr(__builtin_fma(t, t, 1.0)), sn = c * t;
           const T phc = cj(scl(ig, ga));
-          for (int i = sub; i < m; i += 16) {
-            const T x = wp[i], y = mulr(wq[i], phc);
-            wp[i] = addv(scl(c, x), scl(-sn, y));
-            wq[i] = addv(scl(sn, x), scl(c, y));
+          if constexpr (MI > 0) {
+#pragma unroll
+            for (int k = 0; k < MI; ++k) {
+              const int i = sub + 16 * k;
+              const T z = mulr(y[k], phc);
+              if (i < m) {
+                wp[i] = addv(scl(c, x[k]), scl(-sn, z));
+                wq[i] = addv(scl(sn, x[k]), scl(c, z));
+              }
+            }
+          } else {
+            for (int i = sub; i < m; i += 16) {
+              const T u0 = wp[i], z = mulr(wq[i], phc);
+              wp[i] = addv(scl(c, u0), scl(-sn, z));
+              wq[i] = addv(scl(sn, u0), scl(c, z));
+            }
           }
           T* vp = V + p * n;
           T* vq = V + q * n;
+#pragma unroll 4
           for (int i = sub; i < n; i += 16) {
-            const T x = vp[i], y = mulr(vq[i], phc);
-            vp[i] = addv(scl(c, x), scl(-sn, y));
-            vq[i] = addv(scl(sn, x), scl(c, y));
+            const T u0 = vp[i], z = mulr(vq[i], phc);
+            vp[i] = addv(scl(c, u0), scl(-sn, z));
+            vq[i] = addv(scl(sn, u0), scl(c, z));
           }
-          if (sub == 0) rotated = 1;
+          if (sub == 0) {
+            rotated = 1;
+            sig[p] = fmax(0.0, al - t * ag);
+            sig[q] = fmax(0.0, be + t * ag);
+          }
         }
       }
       if (t1 != 0) t1 = t1 == N - 1 ? 1 : t1 + 1;
@@ -346,9 +382,10 @@ static void jacobi_launch(const T* A, long long lda, long long sA, int m, int n,
     hipLaunchKernelGGL(kernel, dim3(batch), dim3(NT), 0, st, A, lda, sA, m, n, wide, W, sW, u, su, vh, svh, s, ss,
                        sweeps, max_sweeps);
   };
-  if (need <= (size_t)JACOBI_LDS_SMALL) go(jacobi_svd_kernel<T, NT, JACOBI_LDS_SMALL, true>);
-  else if (need <= (size_t)JACOBI_LDS) go(jacobi_svd_kernel<T, NT, JACOBI_LDS, true>);
-  else go(jacobi_svd_kernel<T, NT, 64 * 64 * (int)sizeof(T), false>);
+  if (need <= (size_t)JACOBI_LDS_SMALL && m <= 32) go(jacobi_svd_kernel<T, NT, JACOBI_LDS_SMALL, true, 2>);
+  else if (need <= (size_t)JACOBI_LDS && m <= 64) go(jacobi_svd_kernel<T, NT, JACOBI_LDS, true, 4>);
+  else if (need <= (size_t)JACOBI_LDS) go(jacobi_svd_kernel<T, NT, JACOBI_LDS, true, 0>);
+  else go(jacobi_svd_kernel<T, NT, 64 * 64 * (int)sizeof(T), false, 0>);
 }
 
 hipError_t jacobi_svd(int dtype, const void* A, long long lda, long long sA, int rows, int cols, void* work,
