@@ -13,6 +13,7 @@
 
 #include "../../include/tci_c.h"
 #include "common.hpp"
+#include "contract.hpp"
 #include "eig.hpp"
 #include "gemm.hpp"
 #include "grouped.hpp"
@@ -672,6 +673,14 @@ tci_status tci_close(tci_context ctx, tci_tensor a, tci_tensor b, double eps, in
 } TCI_API_CATCH
 
 // ----------------------------------------------------------------- contraction
+static void row_major_strides(int order, const int64_t* shape, long long* st) {
+  long long acc = 1;
+  for (int b = order - 1; b >= 0; --b) {
+    st[b] = acc;
+    acc *= shape[b];
+  }
+}
+
 static int find_lab(const int32_t* l, int n, int32_t x) {
   for (int i = 0; i < n; ++i)
     if (l[i] == x) return i;
@@ -730,6 +739,13 @@ tci_status tci_contract(tci_context ctx, tci_tensor a, const int32_t* la, int na
     for (size_t i = 0; i < p.size(); ++i) if (p[i] != (int)i) return false;
     return true;
   };
+  // natural output order: I then J
+  std::vector<int32_t> nat;
+  for (int i : I) nat.push_back(la[i]);
+  for (int i : J) nat.push_back(lb[i]);
+  bool same = (int)nat.size() == nc;
+  for (int i = 0; same && i < nc; ++i) same = (nat[i] == lc[i]);
+  const bool alias = (c == a || c == b);
   // A^T form: a == [S..., I...]
   std::vector<int> permAt;
   for (int i : S) permAt.push_back(i);
@@ -737,6 +753,42 @@ tci_status tci_contract(tci_context ctx, tci_tensor a, const int32_t* la, int na
   std::vector<int> permBt;
   for (int i : J) permBt.push_back(i);
   for (int i : Sb) permBt.push_back(i);
+  // Small FP64 contractions in one launch: always up to 32 summed terms (a tile
+  // of the matrix product takes as long), and beyond that where the general
+  // path would have to permute an operand or the result first (three launches
+  // instead of one outweigh the uncoalesced loads up to 64 terms).
+  const bool moves = !(is_ident(permA) || is_ident(permAt)) || !(is_ident(permB) || is_ident(permBt)) || !same;
+  if ((dt == C128 || dt == F64) && !alias && M > 0 && N > 0 && K > 0 && K <= (moves ? CONTRACT_MAX_K : 32) &&
+      M * N <= CONTRACT_MAX_WORK / K && std::max({na, nb, nc}) <= CONTRACT_MAX_BONDS) {
+    TCI_TRY(ensure_shape(ctx, c, dt, nc, cshape));
+    auto apart = [&](tci_tensor t) {   // wrapped tensors may share memory
+      const char *x = static_cast<const char*>(t->data), *y = static_cast<const char*>(c->data);
+      return x + tbytes(t) <= y || y + tbytes(c) <= x;
+    };
+    if (apart(a) && apart(b)) {
+      long long sta[MAX_ORDER + 1], stb[MAX_ORDER + 1];
+      int64_t sha[MAX_ORDER], shb[MAX_ORDER];
+      for (int i = 0; i < na; ++i) sha[i] = a->shape[i];
+      for (int i = 0; i < nb; ++i) shb[i] = b->shape[i];
+      row_major_strides(na, sha, sta);
+      row_major_strides(nb, shb, stb);
+      ContractArgs g{};
+      g.nc = nc; g.ns = (int)S.size(); g.nout = (int)(M * N); g.k = (int)K;
+      for (int i = 0; i < nc; ++i) {
+        const int ia = find_lab(la, na, lc[i]);
+        g.cdim[i] = (int)cshape[i];
+        g.sa[i] = ia >= 0 ? (int)sta[ia] : 0;
+        g.sb[i] = ia >= 0 ? 0 : (int)stb[find_lab(lb, nb, lc[i])];
+      }
+      for (size_t i = 0; i < S.size(); ++i) {
+        g.sdim[i] = (int)a->shape[S[i]];
+        g.ta[i] = (int)sta[S[i]];
+        g.tb[i] = (int)stb[Sb[i]];
+      }
+      TCI_CHECK_HIP(contract_small(dt, a->data, b->data, c->data, g, ctx->stream));
+      return TCI_OK;
+    }
+  }
   const void* Ap = a->data;
   const void* Bp = b->data;
   int opA = OP_N, opB = OP_N;
@@ -765,13 +817,6 @@ tci_status tci_contract(tci_context ctx, tci_tensor a, const int32_t* la, int na
     TCI_CHECK_HIP(tci::permute(dt, b->data, tmp, nb, sh, p, ctx->stream));
     Bp = tmp; opB = OP_N; ldb = N;
   }
-  // natural output order: I then J
-  std::vector<int32_t> nat;
-  for (int i : I) nat.push_back(la[i]);
-  for (int i : J) nat.push_back(lb[i]);
-  bool same = (int)nat.size() == nc;
-  for (int i = 0; same && i < nc; ++i) same = (nat[i] == lc[i]);
-  const bool alias = (c == a || c == b);
   void* Cp;
   if (same && !alias) {
     TCI_TRY(ensure_shape(ctx, c, dt, nc, cshape));
@@ -820,13 +865,6 @@ tci_status tci_contract_str(tci_context ctx, tci_tensor a, const char* la, tci_t
 
 namespace {
 
-void row_major_strides(int order, const int64_t* shape, long long* st) {
-  long long acc = 1;
-  for (int b = order - 1; b >= 0; --b) {
-    st[b] = acc;
-    acc *= shape[b];
-  }
-}
 
 // Source of an out-of-place operation: the input itself, or a copy of it in
 // the arena when the output handle is the input handle (its storage may be

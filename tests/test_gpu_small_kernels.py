@@ -147,3 +147,34 @@ def test_sketch_gradients(T, ctx, n):
     err = (grad.cpu().double() - flat.grad).abs().max() / flat.grad.abs().max()
     assert float(err) < 2e-5
     assert float((m.predict(X).cpu().double() - h[:, 0].detach()).abs().max()) < 2e-5 * float(h.detach().abs().max())
+
+
+# one launch up to 32 summed terms, 64 with permuted operands, 2^17 multiply-adds; the general path above
+@pytest.mark.parametrize("la,lb,lc,dims", [
+    ("ab", "ab", "", dict(a=4, b=16)), ("ab", "bc", "ac", dict(a=1, b=1, c=1)), ("ab", "bc", "ca", dict(a=5, b=33, c=7)),
+    ("sabc", "bx", "saxc", dict(s=2, a=3, b=16, c=4, x=16)), ("cabs", "cds", "dab", dict(a=3, b=2, c=4, d=9, s=16)),
+    ("cabs", "cds", "dab", dict(a=3, b=2, c=4, d=9, s=17)), ("a", "b", "ba", dict(a=300, b=437)),
+    ("abc", "cbd", "da", dict(a=64, b=8, c=8, d=32)), ("abc", "cbd", "da", dict(a=64, b=8, c=8, d=33)),
+    ("ab", "bc", "ac", dict(a=64, b=32, c=64)), ("ab", "bc", "ac", dict(a=64, b=33, c=64)),
+    ("abcd", "efgh", "hagbfced", dict.fromkeys("abcdefgh", 2))])
+@pytest.mark.parametrize("complex_", [True, False])
+def test_small_contractions(T, ctx, la, lb, lc, dims, complex_):
+    a, b = (draw([dims[x] for x in lab], complex_, 11 + i) for i, lab in enumerate((la, lb)))
+    dt = T.C128 if complex_ else T.F64
+    ta, tb = T.Tensor.from_numpy(ctx, a, dt), T.Tensor.from_numpy(ctx, b, dt)
+    ref, mag = (np.einsum(f"{la},{lb}->{lc}", x, y) for x, y in ((a, b), (np.abs(a), np.abs(b))))
+    k = max(1, int(np.prod([dims[x] for x in set(la) & set(lb)])))
+    c = T.contract(ctx, ta, la, tb, lb, lc).numpy()
+    assert c.shape == ref.shape and np.all(np.abs(c - ref) <= 4 * (k + 2) * U64 * mag)
+
+
+def test_small_contraction_into_shared_memory(T, ctx):
+    """The result over an operand's handle, and over its memory through another wrapped tensor."""
+    a, b = draw((4, 6), True, 1), draw((6, 6), True, 2)
+    ref = np.einsum("ab,bc->ca", a, b)
+    ta, tb = T.Tensor.from_numpy(ctx, a, T.C128), T.Tensor.from_numpy(ctx, b, T.C128)
+    buf = ta.buf
+    shared = T.Tensor(ctx, buf.view(-1), shape=[24])
+    assert np.abs(T.contract(ctx, ta, "ab", tb, "bc", "ca", out=shared).numpy() - ref).max() < 1e-13
+    ta = T.Tensor.from_numpy(ctx, a, T.C128)
+    assert np.abs(T.contract(ctx, ta, "ab", tb, "bc", "ca", out=ta).numpy() - ref).max() < 1e-13
