@@ -326,6 +326,11 @@ tci_status tci_stack(tci_context ctx, int n, const tci_tensor* ins, int bond, tc
  * all bonds paired gives order 0.  FP64 accumulation.  out == in works in
  * place.  Errors: TCI_ERR_INVALID_ARGUMENT, TCI_ERR_SHAPE. */
 tci_status tci_trace(tci_context ctx, tci_tensor in, int npairs, const int32_t* pairs, tci_tensor out);
+/* inout /= trace(inout) for a square order-2 tensor, the trace in FP64: what
+ * tci_trace, a host read and tci_scale by its reciprocal give, without the
+ * wait.  A zero trace leaves non-finite elements.  Stream-ordered.  Errors:
+ * TCI_ERR_SHAPE. */
+tci_status tci_normalize_trace(tci_context ctx, tci_tensor inout);
 
 /* Spec, linear algebra: exp.  Matricise with the first k_rows bonds as rows
  * (rows must equal columns), take the matrix exponential, fold back to the

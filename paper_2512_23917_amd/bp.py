@@ -75,7 +75,8 @@ class BPState:
                 d = self.V[i].shape()[1 + pos]
                 self.M[(i, j)] = self._t(np.eye(d) / d)
 
-    def message(self, i, j, M):
+    def message(self, i, j, M, conj=None):
+        """conj: V_i conjugated, where the caller has it (V does not change during BP)."""
         c = self.ctx
         lab = self._labels(i)
         a = self.V[i]
@@ -87,17 +88,18 @@ class BPState:
             lab = out
         pj = self.nb[i].index(j)
         bra = [S_LABEL] + [BRA + p for p in range(len(self.nb[i]))]
-        m = tci.contract(c, a, lab, tci.cplx_conj(c, self.V[i]), bra, [KET + pj, BRA + pj])
-        tr = tci.trace(c, m, [(0, 1)]).numpy().reshape(-1)[0]
-        return tci.scale(c, m, 1.0 / tr)
+        m = tci.contract(c, a, lab, tci.cplx_conj(c, self.V[i]) if conj is None else conj, bra, [KET + pj, BRA + pj])
+        return tci.normalize_trace(c, m)
 
-    def sweep(self):
-        self.M = {(i, j): self.message(i, j, self.M) for (i, j) in self.M}
+    def sweep(self, conj=None):
+        conj = [tci.cplx_conj(self.ctx, v) for v in self.V] if conj is None else conj
+        self.M = {(i, j): self.message(i, j, self.M, conj[i]) for (i, j) in self.M}
 
     def run_bp(self, iters: int):
         self.init_messages()
+        conj = [tci.cplx_conj(self.ctx, v) for v in self.V]
         for _ in range(iters):
-            self.sweep()
+            self.sweep(conj)
 
     def bp_norm(self) -> complex:
         c = self.ctx

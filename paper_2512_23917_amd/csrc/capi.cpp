@@ -1156,6 +1156,20 @@ tci_status tci_trace(tci_context ctx, tci_tensor in, int npairs, const int32_t* 
   return TCI_OK;
 } TCI_API_CATCH
 
+tci_status tci_normalize_trace(tci_context ctx, tci_tensor inout) try {
+  TCI_TRY(check_ctx(ctx));
+  TCI_TRY(check_t(inout, "inout"));
+  if (inout->order != 2 || inout->shape[0] != inout->shape[1])
+    TCI_RET(TCI_ERR_SHAPE, "normalize_trace needs a square matrix");
+  if (inout->shape[0] > (1LL << 30)) TCI_RET(TCI_ERR_UNSUPPORTED, "matrix too large");
+  Trace tr(ctx, "normalize_trace", shape_str(inout));
+  ctx->arena.reset();
+  double* scratch = static_cast<double*>(ctx->arena.get(2 * sizeof(double)));
+  if (!scratch) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "workspace");
+  TCI_CHECK_HIP(divide_by_trace(inout->dtype, inout->data, (int)inout->shape[0], scratch, ctx->stream));
+  return TCI_OK;
+} TCI_API_CATCH
+
 tci_status tci_diag(tci_context ctx, tci_tensor in, tci_tensor out) try {
   TCI_TRY(check_ctx(ctx));
   TCI_TRY(check_t(in, "in"));

@@ -168,6 +168,77 @@ hipError_t add_diag(int dt, void* a, long long ld, int n, double v, hipStream_t 
   return hipGetLastError();
 }
 
+namespace {
+
+// 1 / trace of a (n x n) in FP64, by one 256-thread block; valid in every thread
+template <typename T>
+__device__ cd inverse_trace(const T* a, int n, double* sh) {
+  double r = 0.0, im = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) acc_add<T>(r, im, a[(long long)i * n + i]);
+  r = block_sum(r, sh);
+  im = block_sum(im, sh);
+  const double m2 = r * r + im * im;
+  return im == 0.0 ? cd{1.0 / r, 0.0} : cd{r / m2, -im / m2};
+}
+
+__device__ inline cd widen(double v) { return cd{v, 0.0}; }
+__device__ inline cd widen(float v) { return cd{v, 0.0}; }
+__device__ inline cd widen(cd v) { return v; }
+__device__ inline cd widen(cf v) { return cd{v.x, v.y}; }
+
+// A small matrix by one block: the reciprocal and the scaling in one launch.
+template <typename T>
+__global__ __launch_bounds__(256) void divide_trace_small_kernel(T* a, int n) {
+  __shared__ double sh[16];
+  const cd inv = inverse_trace(a, n, sh);
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * n; e += 256) {
+    const cd v = widen(a[e]) * inv;
+    a[e] = make_val<T>(v.x, v.y);
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void inverse_trace_kernel(const T* a, int n, double* out) {
+  __shared__ double sh[16];
+  const cd inv = inverse_trace(a, n, sh);
+  if (threadIdx.x == 0) { out[0] = inv.x; out[1] = inv.y; }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void scale_by_kernel(T* a, long long n, const double* s) {
+  const cd inv{s[0], s[1]};
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
+    const cd v = widen(a[e]) * inv;
+    a[e] = make_val<T>(v.x, v.y);
+  }
+}
+
+template <typename T>
+hipError_t divide_by_trace_t(T* a, int n, double* scratch, hipStream_t s) {
+  if (n <= 64) {
+    hipLaunchKernelGGL(divide_trace_small_kernel<T>, dim3(1), dim3(256), 0, s, a, n);
+  } else {
+    const long long total = (long long)n * n;
+    hipLaunchKernelGGL(inverse_trace_kernel<T>, dim3(1), dim3(256), 0, s, (const T*)a, n, scratch);
+    hipLaunchKernelGGL(scale_by_kernel<T>, dim3(grid_of(total)), dim3(256), 0, s, a, total, (const double*)scratch);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t divide_by_trace(int dt, void* a, int n, double* scratch, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  switch (dt) {
+    case F32: return divide_by_trace_t((float*)a, n, scratch, s);
+    case F64: return divide_by_trace_t((double*)a, n, scratch, s);
+    case C64: return divide_by_trace_t((cf*)a, n, scratch, s);
+    case C128: return divide_by_trace_t((cd*)a, n, scratch, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t partial_trace(int dt, const void* in, void* out, const TraceArgs& a, hipStream_t s) {
   if (a.nout <= 0) return hipSuccess;
   const unsigned g = grid_of(a.nout);

@@ -38,4 +38,7 @@ struct TraceArgs {
 };
 hipError_t partial_trace(int dtype, const void* in, void* out, const TraceArgs& a, hipStream_t s);
 
+// a (n x n, row-major) /= trace(a); scratch: two doubles (orders above 64 only).
+hipError_t divide_by_trace(int dtype, void* a, int n, double* scratch, hipStream_t s);
+
 }  // namespace tci

@@ -10,6 +10,7 @@ no fallback.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 
 import numpy as np
@@ -135,6 +136,7 @@ def lib():
         "tci_replace_sub": (i32, [p, p, p, P(i64), p]),
         "tci_concatenate": (i32, [p, ctypes.c_int, P(p), ctypes.c_int, p]),
         "tci_stack": (i32, [p, ctypes.c_int, P(p), ctypes.c_int, p]),
+        "tci_normalize_trace": (i32, [p, p]),
         "tci_trace": (i32, [p, p, ctypes.c_int, P(i32), p]),
         "tci_exp": (i32, [p, p, ctypes.c_int, p]),
         "tci_lq": (i32, [p, p, ctypes.c_int, p, p]),
@@ -319,7 +321,7 @@ class Tensor:
     def torch(self) -> torch.Tensor:
         """View of the data with the current shape (shares memory)."""
         shp = self.shape()
-        n = int(np.prod(shp)) if shp else 1
+        n = int(math.prod(shp)) if shp else 1
         dt = TORCH_OF[self.current_dtype()]
         ptr = ctypes.c_void_p()
         _check(lib().tci_data_ptr(self.ctx.h, self.h, ctypes.byref(ptr)), "tci_data_ptr")
@@ -359,7 +361,7 @@ def normalize(ctx: Context, t: Tensor) -> float:
 
 def transpose(ctx: Context, t: Tensor, perm, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, t.dtype, int(np.prod(t.shape())))
+        out = Tensor.empty(ctx, t.dtype, int(math.prod(t.shape())))
     _check(lib().tci_transpose(ctx.h, t.h, _i32(perm), out.h), "tci_transpose")
     return out
 
@@ -381,7 +383,7 @@ def contract(ctx: Context, a: Tensor, la, b: Tensor, lb, lc, out: Tensor | None 
     if out is None:
         dims = dict(zip(la, a.shape()))
         dims.update(zip(lb, b.shape()))
-        cap = int(np.prod([dims.get(x, 1) for x in lc])) if lc else 1
+        cap = int(math.prod([dims.get(x, 1) for x in lc])) if lc else 1
         out = Tensor.empty(ctx, a.dtype, cap)
     _check(lib().tci_contract(ctx.h, a.h, _i32(la), len(la), b.h, _i32(lb), len(lb), out.h, _i32(lc), len(lc)),
            "tci_contract")
@@ -391,8 +393,8 @@ def contract(ctx: Context, a: Tensor, la, b: Tensor, lb, lc, out: Tensor | None 
 def trunc_svd(ctx: Context, a: Tensor, k_rows: int, chi_min: int, chi_max: int, target: float = 0.0,
               s_min: float = 0.0):
     shp = a.shape()
-    rows = int(np.prod(shp[:k_rows]))
-    cols = int(np.prod(shp[k_rows:]))
+    rows = int(math.prod(shp[:k_rows]))
+    cols = int(math.prod(shp[k_rows:]))
     kap = min(rows, cols, chi_max)
     u = Tensor.empty(ctx, a.dtype, rows * kap)
     vh = Tensor.empty(ctx, a.dtype, kap * cols)
@@ -405,8 +407,8 @@ def trunc_svd(ctx: Context, a: Tensor, k_rows: int, chi_min: int, chi_max: int, 
 
 def svd(ctx: Context, a: Tensor, k_rows: int):
     shp = a.shape()
-    rows = int(np.prod(shp[:k_rows]))
-    cols = int(np.prod(shp[k_rows:]))
+    rows = int(math.prod(shp[:k_rows]))
+    cols = int(math.prod(shp[k_rows:]))
     kap = min(rows, cols)
     u = Tensor.empty(ctx, a.dtype, rows * kap)
     vh = Tensor.empty(ctx, a.dtype, kap * cols)
@@ -417,8 +419,8 @@ def svd(ctx: Context, a: Tensor, k_rows: int):
 
 def qr(ctx: Context, a: Tensor, k_rows: int):
     shp = a.shape()
-    rows = int(np.prod(shp[:k_rows]))
-    cols = int(np.prod(shp[k_rows:]))
+    rows = int(math.prod(shp[:k_rows]))
+    cols = int(math.prod(shp[k_rows:]))
     rho = min(rows, cols)
     q = Tensor.empty(ctx, a.dtype, rows * rho)
     r = Tensor.empty(ctx, a.dtype, rho * cols)
@@ -432,7 +434,7 @@ def _real_of(dt: int) -> int:
 
 def eigh(ctx: Context, a: Tensor, k_rows: int = 1):
     shp = a.shape()
-    n = int(np.prod(shp[:k_rows]))
+    n = int(math.prod(shp[:k_rows]))
     w = Tensor.empty(ctx, _real_of(a.dtype), n)
     v = Tensor.empty(ctx, a.dtype, n * n)
     _check(lib().tci_eigh(ctx.h, a.h, k_rows, w.h, v.h), "tci_eigh")
@@ -440,7 +442,7 @@ def eigh(ctx: Context, a: Tensor, k_rows: int = 1):
 
 
 def eigvalsh(ctx: Context, a: Tensor, k_rows: int = 1):
-    n = int(np.prod(a.shape()[:k_rows]))
+    n = int(math.prod(a.shape()[:k_rows]))
     w = Tensor.empty(ctx, _real_of(a.dtype), n)
     _check(lib().tci_eigvalsh(ctx.h, a.h, k_rows, w.h), "tci_eigvalsh")
     return w
@@ -452,7 +454,7 @@ def _cplx_of(dt: int) -> int:
 
 def eig(ctx: Context, a: Tensor, k_rows: int = 1):
     """tci_eig: (w, v), eigenvalues ascending by (real, imaginary) part."""
-    n = int(np.prod(a.shape()[:k_rows]))
+    n = int(math.prod(a.shape()[:k_rows]))
     w = Tensor.empty(ctx, _cplx_of(a.dtype), n)
     v = Tensor.empty(ctx, _cplx_of(a.dtype), n * n)
     _check(lib().tci_eig(ctx.h, a.h, k_rows, w.h, v.h), "tci_eig")
@@ -460,7 +462,7 @@ def eig(ctx: Context, a: Tensor, k_rows: int = 1):
 
 
 def eigvals(ctx: Context, a: Tensor, k_rows: int = 1):
-    n = int(np.prod(a.shape()[:k_rows]))
+    n = int(math.prod(a.shape()[:k_rows]))
     w = Tensor.empty(ctx, _cplx_of(a.dtype), n)
     _check(lib().tci_eigvals(ctx.h, a.h, k_rows, w.h), "tci_eigvals")
     return w
@@ -474,8 +476,8 @@ def close(ctx: Context, a: Tensor, b: Tensor, eps: float) -> bool:
 
 def lq(ctx: Context, a: Tensor, k_rows: int):
     shp = a.shape()
-    rows = int(np.prod(shp[:k_rows]))
-    cols = int(np.prod(shp[k_rows:]))
+    rows = int(math.prod(shp[:k_rows]))
+    cols = int(math.prod(shp[k_rows:]))
     rho = min(rows, cols)
     l = Tensor.empty(ctx, a.dtype, rows * rho)
     q = Tensor.empty(ctx, a.dtype, rho * cols)
@@ -485,7 +487,7 @@ def lq(ctx: Context, a: Tensor, k_rows: int):
 
 def exp(ctx: Context, a: Tensor, k_rows: int, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, a.dtype, int(np.prod(a.shape())))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod(a.shape())))
     _check(lib().tci_exp(ctx.h, a.h, k_rows, out.h), "tci_exp")
     return out
 
@@ -497,7 +499,7 @@ def _scalar_bytes(dtype: int, value) -> ctypes.Array:
 
 def _adopt(ctx: Context, h: ctypes.c_void_p, dtype: int, shape) -> Tensor:
     """Copy an owning library tensor into a torch-backed Tensor and free it."""
-    n = max(1, int(np.prod(shape)))
+    n = max(1, int(math.prod(shape)))
     out = Tensor(ctx, torch.empty(n, dtype=TORCH_OF[dtype], device=ctx.torch_device), shape=[n])
     try:
         _check(lib().tci_reshape(ctx.h, h, len(shape), _i64(shape), out.h), "tci_reshape")
@@ -523,7 +525,7 @@ def extract_sub(ctx: Context, a: Tensor, ranges, out: Tensor | None = None) -> T
     first = [int(f) for f, _ in ranges]
     last = [int(l) for _, l in ranges]
     if out is None:
-        out = Tensor.empty(ctx, a.dtype, int(np.prod([max(0, l - f) for f, l in zip(first, last)])))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod([max(0, l - f) for f, l in zip(first, last)])))
     _check(lib().tci_extract_sub(ctx.h, a.h, _i64(first), _i64(last), out.h), "tci_extract_sub")
     return out
 
@@ -535,7 +537,7 @@ def shrink(ctx: Context, a: Tensor, ranges: dict, out: Tensor | None = None) -> 
         for b, (f, l) in ranges.items():
             if 0 <= b < len(shp):   # bad bonds are reported by the library
                 shp[b] = max(0, l - f)
-        out = Tensor.empty(ctx, a.dtype, int(np.prod(shp)))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod(shp)))
     _check(lib().tci_shrink(ctx.h, a.h, len(bonds), _i32(bonds), _i64([ranges[b][0] for b in bonds]),
                             _i64([ranges[b][1] for b in bonds]), out.h), "tci_shrink")
     return out
@@ -548,7 +550,7 @@ def expand(ctx: Context, a: Tensor, increments: dict, out: Tensor | None = None)
         for b, inc in increments.items():
             if 0 <= b < len(shp):   # bad bonds are reported by the library
                 shp[b] += max(0, inc)
-        out = Tensor.empty(ctx, a.dtype, int(np.prod(shp)))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod(shp)))
     _check(lib().tci_expand(ctx.h, a.h, len(bonds), _i32(bonds), _i64([increments[b] for b in bonds]), out.h),
            "tci_expand")
     return out
@@ -556,7 +558,7 @@ def expand(ctx: Context, a: Tensor, increments: dict, out: Tensor | None = None)
 
 def replace_sub(ctx: Context, a: Tensor, sub: Tensor, begin, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, a.dtype, int(np.prod(a.shape())))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod(a.shape())))
     _check(lib().tci_replace_sub(ctx.h, a.h, sub.h, _i64(begin), out.h), "tci_replace_sub")
     return out
 
@@ -567,14 +569,14 @@ def _handles(ins):
 
 def concatenate(ctx: Context, ins: list, bond: int, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, ins[0].dtype, sum(int(np.prod(t.shape())) for t in ins))
+        out = Tensor.empty(ctx, ins[0].dtype, sum(int(math.prod(t.shape())) for t in ins))
     _check(lib().tci_concatenate(ctx.h, len(ins), _handles(ins), bond, out.h), "tci_concatenate")
     return out
 
 
 def stack(ctx: Context, ins: list, bond: int, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, ins[0].dtype, sum(int(np.prod(t.shape())) for t in ins))
+        out = Tensor.empty(ctx, ins[0].dtype, sum(int(math.prod(t.shape())) for t in ins))
     _check(lib().tci_stack(ctx.h, len(ins), _handles(ins), bond, out.h), "tci_stack")
     return out
 
@@ -584,7 +586,7 @@ def trace(ctx: Context, a: Tensor, pairs, out: Tensor | None = None) -> Tensor:
     if out is None:
         shp = a.shape()
         used = set(flat)
-        out = Tensor.empty(ctx, a.dtype, int(np.prod([d for b, d in enumerate(shp) if b not in used])))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod([d for b, d in enumerate(shp) if b not in used])))
     _check(lib().tci_trace(ctx.h, a.h, len(pairs), _i32(flat), out.h), "tci_trace")
     return out
 
@@ -696,7 +698,7 @@ def split_batched(ctx: Context, thetas: list, params: UpdateParams, prev_spectra
 def heff_matvec(ctx: Context, L: Tensor, W1: Tensor, W2: Tensor, R: Tensor, x: Tensor,
                 y: Tensor | None = None) -> Tensor:
     if y is None:
-        y = Tensor.empty(ctx, x.dtype, int(np.prod(x.shape())))
+        y = Tensor.empty(ctx, x.dtype, int(math.prod(x.shape())))
     _check(lib().tci_heff_matvec(ctx.h, L.h, W1.h, W2.h, R.h, x.h, y.h), "tci_heff_matvec")
     return y
 
@@ -923,9 +925,15 @@ def bs_two_site_update_batched(ctx: Context, A: list, B: list, gates: list | Non
     return A_out, s_out, B_out, list(infos)
 
 
+def normalize_trace(ctx: Context, a: Tensor) -> Tensor:
+    """In place: a /= trace(a), without waiting for the device."""
+    _check(lib().tci_normalize_trace(ctx.h, a.h), "tci_normalize_trace")
+    return a
+
+
 def inverse(ctx: Context, a: Tensor, k_rows: int, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, a.dtype, int(np.prod(a.shape())))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod(a.shape())))
     _check(lib().tci_inverse(ctx.h, a.h, k_rows, out.h), "tci_inverse")
     return out
 
@@ -935,19 +943,19 @@ REAL_OF = {F32: F32, F64: F64, C64: F32, C128: F64}
 
 
 def to_cplx(ctx: Context, a: Tensor) -> Tensor:
-    out = Tensor.empty(ctx, COMPLEX_OF[a.dtype], int(np.prod(a.shape())))
+    out = Tensor.empty(ctx, COMPLEX_OF[a.dtype], int(math.prod(a.shape())))
     _check(lib().tci_to_cplx(ctx.h, a.h, out.h), "tci_to_cplx")
     return out
 
 
 def real(ctx: Context, a: Tensor) -> Tensor:
-    out = Tensor.empty(ctx, REAL_OF[a.dtype], int(np.prod(a.shape())))
+    out = Tensor.empty(ctx, REAL_OF[a.dtype], int(math.prod(a.shape())))
     _check(lib().tci_real(ctx.h, a.h, out.h), "tci_real")
     return out
 
 
 def imag(ctx: Context, a: Tensor) -> Tensor:
-    out = Tensor.empty(ctx, REAL_OF[a.dtype], int(np.prod(a.shape())))
+    out = Tensor.empty(ctx, REAL_OF[a.dtype], int(math.prod(a.shape())))
     _check(lib().tci_imag(ctx.h, a.h, out.h), "tci_imag")
     return out
 
@@ -983,7 +991,7 @@ def diag(ctx: Context, a: Tensor, out: Tensor | None = None) -> Tensor:
 
 def cplx_conj(ctx: Context, a: Tensor, out: Tensor | None = None) -> Tensor:
     if out is None:
-        out = Tensor.empty(ctx, a.dtype, int(np.prod(a.shape())))
+        out = Tensor.empty(ctx, a.dtype, int(math.prod(a.shape())))
     _check(lib().tci_cplx_conj(ctx.h, a.h, out.h), "tci_cplx_conj")
     return out
 

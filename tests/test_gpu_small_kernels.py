@@ -178,3 +178,17 @@ def test_small_contraction_into_shared_memory(T, ctx):
     assert np.abs(T.contract(ctx, ta, "ab", tb, "bc", "ca", out=shared).numpy() - ref).max() < 1e-13
     ta = T.Tensor.from_numpy(ctx, a, T.C128)
     assert np.abs(T.contract(ctx, ta, "ab", tb, "bc", "ca", out=ta).numpy() - ref).max() < 1e-13
+
+
+# one block up to order 64, two launches above
+@pytest.mark.parametrize("n", [1, 3, 64, 65, 300])
+@pytest.mark.parametrize("dt", ["F32", "F64", "C64", "C128"])
+def test_normalize_trace(T, ctx, n, dt):
+    a = draw((n, n), dt.startswith("C"), n) + np.eye(n) * 4
+    a = a.astype(T.NUMPY_OF[getattr(T, dt)])
+    t = T.normalize_trace(ctx, T.Tensor.from_numpy(ctx, a, getattr(T, dt)))
+    ref = a.astype(np.complex128) / np.trace(a.astype(np.complex128))
+    u = 2.0 ** -24 if dt in ("F32", "C64") else U64
+    assert np.abs(t.numpy() - ref).max() <= (n + 8) * U64 * np.abs(ref).max() * np.sqrt(n) + 2 * u * np.abs(ref).max()
+    with pytest.raises(T.TciError):
+        T.normalize_trace(ctx, T.Tensor.from_numpy(ctx, np.zeros((2, 3)), T.F64))
