@@ -335,24 +335,41 @@ tci_status tci_bs_two_site_update_batched(tci_context ctx, int n, const tci_bs_t
 
   // gates on the host (identity when absent)
   std::vector<std::array<double, 16>> G(n);
-  for (int u = 0; u < n; ++u) {
-    G[u].fill(0.0);
-    for (int k = 0; k < 4; ++k) G[u][k * 5] = 1.0;
-    if (gates && gates[u]) {
-      const tci_tensor g = gates[u];
-      if (tsize(g) != 16) TCI_RET(TCI_ERR_SHAPE, "gate must have 16 elements");
-      if (g->dtype == TCI_F32) {
-        float h[16];
-        TCI_CHECK_HIP(hipMemcpyAsync(h, g->data, sizeof(h), hipMemcpyDeviceToHost, st));
-        TCI_CHECK_HIP(hipStreamSynchronize(st));
-        for (int k = 0; k < 16; ++k) G[u][k] = h[k];
-      } else if (g->dtype == TCI_F64) {
-        TCI_CHECK_HIP(hipMemcpyAsync(G[u].data(), g->data, sizeof(double) * 16, hipMemcpyDeviceToHost, st));
-        TCI_CHECK_HIP(hipStreamSynchronize(st));
-      } else {
+  {
+    // all gates of a dtype in one copy to the host
+    std::vector<int> of[2];   // updates with an F64 / F32 gate
+    for (int u = 0; u < n; ++u) {
+      G[u].fill(0.0);
+      for (int k = 0; k < 4; ++k) G[u][k * 5] = 1.0;
+      if (!gates || !gates[u]) continue;
+      if (tsize(gates[u]) != 16) TCI_RET(TCI_ERR_SHAPE, "gate must have 16 elements");
+      if (gates[u]->dtype != TCI_F32 && gates[u]->dtype != TCI_F64)
         TCI_RET(TCI_ERR_DTYPE, "gate must be real (F32 or F64)");
-      }
+      of[gates[u]->dtype == TCI_F32].push_back(u);
     }
+    const std::vector<size_t> mark = ctx->arena.used_state();
+    std::vector<double> h64(of[0].size() * 16);
+    std::vector<float> h32(of[1].size() * 16);
+    for (int f = 0; f < 2; ++f) {
+      if (of[f].empty()) continue;
+      const size_t each = f ? sizeof(float) * 16 : sizeof(double) * 16;
+      char* dev = static_cast<char*>(ctx->arena.get(each * of[f].size()));
+      if (!dev) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "gate staging");
+      for (size_t i0 = 0; i0 < of[f].size(); i0 += PTR_TABLE) {
+        const int nt = (int)std::min<size_t>(PTR_TABLE, of[f].size() - i0);
+        PtrTable t{};
+        for (int i = 0; i < nt; ++i) t.p[i] = gates[of[f][i0 + i]]->data;
+        TCI_CHECK_HIP(copy_from_table(t, dev + each * i0, each, each, nt, st));
+      }
+      TCI_CHECK_HIP(hipMemcpyAsync(f ? (void*)h32.data() : (void*)h64.data(), dev, each * of[f].size(),
+                                   hipMemcpyDeviceToHost, st));
+    }
+    if (!of[0].empty() || !of[1].empty()) TCI_CHECK_HIP(hipStreamSynchronize(st));
+    for (size_t i = 0; i < of[0].size(); ++i)
+      for (int k = 0; k < 16; ++k) G[of[0][i]][k] = h64[i * 16 + k];
+    for (size_t i = 0; i < of[1].size(); ++i)
+      for (int k = 0; k < 16; ++k) G[of[1][i]][k] = h32[i * 16 + k];
+    ctx->arena.restore(mark);
   }
 
   // 1. sector layout of every new bond
@@ -733,11 +750,31 @@ tci_status tci_bs_two_site_update_batched(tci_context ctx, int n, const tci_bs_t
     TCI_CHECK_HIP(hipMemcpyAsync(sd_d, sd.data(), sizeof(ScatDesc) * sd.size(), hipMemcpyHostToDevice, st));
     TCI_CHECK_HIP(scatter_blocks(sd_d, (int)sd.size(), st));
   }
+  // spectra: one upload, then one launch per 64 updates
+  int maxlen = 0;
+  for (int u = 0; u < n; ++u) maxlen = std::max(maxlen, (int)s_host[u].size());
+  std::vector<double> s_all((size_t)maxlen * n, 0.0);
+  std::vector<int> s_len(n);
+  double* s_dev = static_cast<double*>(ctx->arena.get(sizeof(double) * std::max<size_t>(1, s_all.size())));
+  int* l_dev = static_cast<int*>(ctx->arena.get(sizeof(int) * n));
+  if (!s_dev || !l_dev) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "spectra");
   for (int u = 0; u < n; ++u) {
-    const int64_t sh[1] = {(int64_t)s_host[u].size()};
+    s_len[u] = (int)s_host[u].size();
+    std::copy(s_host[u].begin(), s_host[u].end(), s_all.begin() + (size_t)maxlen * u);
+    const int64_t sh[1] = {(int64_t)s_len[u]};
     TCI_TRY(ensure_shape(ctx, s_out[u], TCI_F64, 1, sh));
-    if (sh[0]) TCI_CHECK_HIP(hipMemcpyAsync(s_out[u]->data, s_host[u].data(), sizeof(double) * sh[0],
-                                            hipMemcpyHostToDevice, st));
+  }
+  if (maxlen > 0) {
+    TCI_CHECK_HIP(hipMemcpyAsync(s_dev, s_all.data(), sizeof(double) * s_all.size(), hipMemcpyHostToDevice, st));
+    TCI_CHECK_HIP(hipMemcpyAsync(l_dev, s_len.data(), sizeof(int) * n, hipMemcpyHostToDevice, st));
+    for (int u0 = 0; u0 < n; u0 += PTR_TABLE) {
+      const int nt = std::min(PTR_TABLE, n - u0);
+      PtrTable t{};
+      for (int i = 0; i < nt; ++i) t.p[i] = s_out[u0 + i]->data;
+      TCI_CHECK_HIP(copy_doubles_to_table(s_dev + (size_t)maxlen * u0, maxlen, t, l_dev + u0, maxlen, nt, st));
+    }
+  }
+  for (int u = 0; u < n; ++u) {
     if (infos) {
       infos[u].chi = chi_u[u];
       infos[u].trunc_err = eps_u[u];

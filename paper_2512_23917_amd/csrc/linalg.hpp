@@ -41,11 +41,29 @@ hipError_t gauge_columns(int dtype, void* U, long long ldu, long long sU, int m,
 hipError_t real_to_complex(const double* z, void* u, long long n, long long sz, long long su, int batch,
                            hipStream_t s);
 
-hipError_t compact_columns(int dtype, const void* in, long long ldin, long long sin_, void* out,
-                           long long sout, int rows, int maxchi, const int* chi, const double* cs,
-                           long long scs, int batch, hipStream_t s);
-hipError_t scale_rows(int dtype, const void* in, long long sin_, void* out, long long sout, long long ncols,
-                      int maxchi, const int* chi, const double* rs, long long srs, int batch, hipStream_t s);
+// Addresses of up to 64 tensors, passed to a kernel by value: one launch moves
+// the tensors of a whole batch where a copy each would cost a few microseconds
+// of host and device time per tensor.
+constexpr int PTR_TABLE = 64;
+struct PtrTable {
+  void* p[PTR_TABLE];
+};
+
+// dst + b * stride <- src.p[b] (bytes each, a multiple of 4), b < n <= PTR_TABLE.
+hipError_t copy_from_table(const PtrTable& src, void* dst, size_t stride, size_t bytes, int n, hipStream_t s);
+// dst.p[b] <- src + b * stride: the len[b] first doubles, b < n.
+hipError_t copy_doubles_to_table(const double* src, long long stride, const PtrTable& dst, const int* len, int maxlen,
+                                 int n, hipStream_t s);
+
+// Write-back of the factors of n <= PTR_TABLE problems from the working type
+// wdt (F64 or C128) to tensors of dtype dt: columns j < chi[b] of in (rows x
+// ldin) to the dense rows x chi[b] tensor out.p[b], column j scaled by
+// cs[b][j]; rows j < chi[b] of in (contiguous, ncols wide) to out.p[b], row j
+// scaled by rs[b][j] (cs, rs may be null).
+hipError_t store_columns(int wdt, int dt, const void* in, long long ldin, long long sin_, const PtrTable& out, int rows,
+                         int maxchi, const int* chi, const double* cs, long long scs, int n, hipStream_t s);
+hipError_t store_rows(int wdt, int dt, const void* in, long long sin_, const PtrTable& out, long long ncols, int maxchi,
+                      const int* chi, const double* rs, long long srs, int n, hipStream_t s);
 
 // x[i] /= lam[(i / div) % mod], i < n (Vidal-form inverse bond weights).
 hipError_t inv_scale_axis(int dtype, void* x, long long n, long long div, long long mod, const double* lam,

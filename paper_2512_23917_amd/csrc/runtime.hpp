@@ -59,7 +59,8 @@ struct Arena {
     return u;
   }
   void restore(const std::vector<size_t>& u) {
-    for (size_t i = 0; i < chunks.size() && i < u.size(); ++i) chunks[i].used = u[i];
+    // chunks added since the state was taken held nothing then
+    for (size_t i = 0; i < chunks.size(); ++i) chunks[i].used = i < u.size() ? u[i] : 0;
   }
   std::vector<long long> layout() const {
     std::vector<long long> l;

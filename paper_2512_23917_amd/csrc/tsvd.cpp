@@ -368,32 +368,44 @@ static tci_status store_outputs(tci_context ctx, int dt, int wdt, int chil, int 
   const int m = chil * d, n = d * chir, nb = (int)idx.size();
   const size_t wes = elem_bytes(wdt);
   const int kz = o.kz;
-  ARENA(Ucmp, char, wes * (size_t)m * kz * nb);
-  ARENA(Vcmp, char, wes * (size_t)kz * n * nb);
   const bool right = p.direction == TCI_DIR_RIGHT, left = p.direction == TCI_DIR_LEFT;
   const bool vidal = p.direction == TCI_DIR_VIDAL;
-  TCI_CHECK_HIP(compact_columns(wdt, o.U, kz, (long long)m * kz, Ucmp, (long long)m * kz, m, kz, o.chi,
-                                right ? o.sn : nullptr, o.kmax, nb, s));
-  TCI_CHECK_HIP(scale_rows(wdt, o.Vh, (long long)kz * n, Vcmp, (long long)kz * n, n, kz, o.chi,
-                           left ? o.sn : nullptr, o.kmax, nb, s));
+  for (int i0 = 0; i0 < nb; i0 += PTR_TABLE) {
+    const int nt = std::min(PTR_TABLE, nb - i0);
+    PtrTable ta{}, tb{}, ts{};
+    for (int i = 0; i < nt; ++i) {
+      const int g = idx[i0 + i];
+      const int64_t chi = o.chi_h[i0 + i];
+      const int64_t ash[3] = {chil, d, chi}, bsh[3] = {chi, d, chir}, ssh[1] = {chi};
+      TCI_TRY(ensure_shape(ctx, A_out[g], dt, 3, ash));
+      TCI_TRY(ensure_shape(ctx, B_out[g], dt, 3, bsh));
+      TCI_TRY(ensure_shape(ctx, s_out[g], F64, 1, ssh));
+      ta.p[i] = A_out[g]->data;
+      tb.p[i] = B_out[g]->data;
+      ts.p[i] = s_out[g]->data;
+    }
+    const int* chi_d = o.chi + i0;
+    const double* sn = o.sn + (size_t)o.kmax * i0;
+    TCI_CHECK_HIP(store_columns(wdt, dt, static_cast<const char*>(o.U) + wes * (size_t)m * kz * i0, kz, (long long)m * kz,
+                                ta, m, kz, chi_d, right ? sn : nullptr, o.kmax, nt, s));
+    TCI_CHECK_HIP(store_rows(wdt, dt, static_cast<const char*>(o.Vh) + wes * (size_t)kz * n * i0, (long long)kz * n, tb,
+                             n, kz, chi_d, left ? sn : nullptr, o.kmax, nt, s));
+    if (vidal)
+      for (int i = 0; i < nt; ++i) {
+        // Gamma_A = diag(1/lambda_l) U, Gamma_B = V^H diag(1/lambda_r)
+        const int g = idx[i0 + i];
+        const int64_t chi = o.chi_h[i0 + i];
+        TCI_CHECK_HIP(inv_scale_axis(dt, A_out[g]->data, (long long)chil * d * chi, (long long)d * chi, chil,
+                                     static_cast<const double*>(p.lambda_left[g]->data), s));
+        TCI_CHECK_HIP(inv_scale_axis(dt, B_out[g]->data, chi * d * (long long)chir, 1, chir,
+                                     static_cast<const double*>(p.lambda_right[g]->data), s));
+      }
+    // last, since a weight of the Vidal form may be an output spectrum's tensor
+    TCI_CHECK_HIP(copy_doubles_to_table(sn, o.kmax, ts, chi_d, kz, nt, s));
+  }
   for (int i = 0; i < nb; ++i) {
     const int g = idx[i];
     const int64_t chi = o.chi_h[i];
-    const int64_t ash[3] = {chil, d, chi}, bsh[3] = {chi, d, chir}, ssh[1] = {chi};
-    TCI_TRY(ensure_shape(ctx, A_out[g], dt, 3, ash));
-    TCI_TRY(ensure_shape(ctx, B_out[g], dt, 3, bsh));
-    TCI_TRY(ensure_shape(ctx, s_out[g], F64, 1, ssh));
-    TCI_TRY(store_as(ctx, wdt, Ucmp + wes * (size_t)m * kz * i, A_out[g]));
-    TCI_TRY(store_as(ctx, wdt, Vcmp + wes * (size_t)kz * n * i, B_out[g]));
-    if (vidal) {
-      // Gamma_A = diag(1/lambda_l) U, Gamma_B = V^H diag(1/lambda_r)
-      TCI_CHECK_HIP(inv_scale_axis(dt, A_out[g]->data, (long long)chil * d * chi, (long long)d * chi, chil,
-                                   static_cast<const double*>(p.lambda_left[g]->data), s));
-      TCI_CHECK_HIP(inv_scale_axis(dt, B_out[g]->data, chi * d * (long long)chir, 1, chir,
-                                   static_cast<const double*>(p.lambda_right[g]->data), s));
-    }
-    TCI_CHECK_HIP(hipMemcpyAsync(s_out[g]->data, o.sn + (size_t)o.kmax * i, sizeof(double) * chi,
-                                 hipMemcpyDeviceToDevice, s));
     if (infos) {
       tci_update_info& inf = infos[g];
       std::memset(&inf, 0, sizeof(inf));
@@ -416,9 +428,13 @@ static tci_status gather(tci_context ctx, int dt, const void* src, long long str
   const size_t es = elem_bytes(dt);
   char* dst = static_cast<char*>(ctx->arena.get(es * (size_t)stride * idx.size()));
   if (!dst) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "workspace");
-  for (size_t i = 0; i < idx.size(); ++i)
-    TCI_CHECK_HIP(hipMemcpyAsync(dst + es * stride * i, static_cast<const char*>(src) + es * stride * idx[i],
-                                 es * stride, hipMemcpyDeviceToDevice, ctx->stream));
+  for (size_t i0 = 0; i0 < idx.size(); i0 += PTR_TABLE) {
+    const int nt = (int)std::min<size_t>(PTR_TABLE, idx.size() - i0);
+    PtrTable t{};
+    for (int i = 0; i < nt; ++i)
+      t.p[i] = const_cast<char*>(static_cast<const char*>(src)) + es * stride * idx[i0 + i];
+    TCI_CHECK_HIP(copy_from_table(t, dst + es * stride * i0, es * stride, es * stride, nt, ctx->stream));
+  }
   *out = dst;
   return TCI_OK;
 }
@@ -793,12 +809,10 @@ tci_status tci_trunc_svd(tci_context ctx, tci_tensor a, int k_rows, tci_tensor u
   TCI_TRY(ensure_shape(ctx, vdag, odt, order_a - k_rows + 1, vshape));
   int64_t sshape[1] = {chi};
   TCI_TRY(ensure_shape(ctx, s, rdt, 1, sshape));
-  const size_t es = elem_bytes(wdt);
-  void* ucmp = ctx->arena.get(es * (size_t)rows * chi);
-  if (!ucmp) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "workspace");
-  TCI_CHECK_HIP(compact_columns(wdt, o.U, o.kz, (long long)rows * o.kz, ucmp, (long long)rows * chi, (int)rows, chi,
-                                o.chi, nullptr, 0, 1, ctx->stream));
-  TCI_TRY(store_as(ctx, wdt, ucmp, u));
+  PtrTable tu{};
+  tu.p[0] = u->data;
+  TCI_CHECK_HIP(store_columns(wdt, odt, o.U, o.kz, (long long)rows * o.kz, tu, (int)rows, chi, o.chi, nullptr, 0, 1,
+                              ctx->stream));
   TCI_TRY(store_as(ctx, wdt, o.Vh, vdag));  // first chi rows are contiguous
   TCI_TRY(store_as(ctx, F64, o.s, s));
   TCI_CHECK_HIP(hipStreamSynchronize(ctx->stream));
@@ -1251,9 +1265,15 @@ tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tens
     const size_t szA = (size_t)chil * d * chim, szB = (size_t)chim * d * chir;
     ARENA(Ab, char, es * szA * nb);
     ARENA(Bb, char, es * szB * nb);
-    for (int i = 0; i < nb; ++i) {
-      TCI_CHECK_HIP(hipMemcpyAsync(Ab + es * szA * i, A[c0 + i]->data, es * szA, hipMemcpyDeviceToDevice, s));
-      TCI_CHECK_HIP(hipMemcpyAsync(Bb + es * szB * i, B[c0 + i]->data, es * szB, hipMemcpyDeviceToDevice, s));
+    for (int i0 = 0; i0 < nb; i0 += PTR_TABLE) {
+      const int nt = std::min(PTR_TABLE, nb - i0);
+      PtrTable ta{}, tb{};
+      for (int i = 0; i < nt; ++i) {
+        ta.p[i] = A[c0 + i0 + i]->data;
+        tb.p[i] = B[c0 + i0 + i]->data;
+      }
+      TCI_CHECK_HIP(copy_from_table(ta, Ab + es * szA * i0, es * szA, es * szA, nt, s));
+      TCI_CHECK_HIP(copy_from_table(tb, Bb + es * szB * i0, es * szB, es * szB, nt, s));
     }
     // theta = A . B  (contraction over the shared bond)
     const long long smn = (long long)m * n;
@@ -1286,20 +1306,30 @@ tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tens
     if (gates) {
       const int g2 = (int)(d * d * d * d);
       ARENA(Gb, char, es * (size_t)g2 * nb);
-      std::vector<double> eye(2 * 16, 0.0);
-      for (int i = 0; i < nb; ++i) {
-        if (gates[c0 + i]) {
-          TCI_CHECK_HIP(hipMemcpyAsync(Gb + es * g2 * i, gates[c0 + i]->data, es * g2, hipMemcpyDeviceToDevice, s));
-        } else {
-          // identity in the batch's dtype
-          std::vector<char> host(es * g2, 0);
-          for (int q = 0; q < 4; ++q) {
-            char* p0 = host.data() + es * (q * 4 + q);
-            if (dt == C128 || dt == F64) { const double one = 1.0; std::memcpy(p0, &one, 8); }
-            else { const float one = 1.0f; std::memcpy(p0, &one, 4); }
+      std::vector<char> host;   // identity in the batch's dtype, for updates without a gate
+      void* id_dev = nullptr;
+      for (int i0 = 0; i0 < nb; i0 += PTR_TABLE) {
+        const int nt = std::min(PTR_TABLE, nb - i0);
+        PtrTable t{};
+        for (int i = 0; i < nt; ++i) {
+          if (gates[c0 + i0 + i]) {
+            t.p[i] = gates[c0 + i0 + i]->data;
+            continue;
           }
-          TCI_CHECK_HIP(hipMemcpy(Gb + es * g2 * i, host.data(), es * g2, hipMemcpyHostToDevice));
+          if (!id_dev) {
+            host.assign(es * g2, 0);
+            for (int q = 0; q < 4; ++q) {
+              char* p0 = host.data() + es * (q * 4 + q);
+              if (dt == C128 || dt == F64) { const double one = 1.0; std::memcpy(p0, &one, 8); }
+              else { const float one = 1.0f; std::memcpy(p0, &one, 4); }
+            }
+            ARENA(idb, char, es * g2);
+            id_dev = idb;
+            TCI_CHECK_HIP(hipMemcpy(id_dev, host.data(), es * g2, hipMemcpyHostToDevice));
+          }
+          t.p[i] = id_dev;
         }
+        TCI_CHECK_HIP(copy_from_table(t, Gb + es * g2 * i0, es * g2, es * g2, nt, s));
       }
       TCI_CHECK_HIP(gate_apply(dt, th, smn, Gb, g2, (int)chil, (int)d, (int)chir, nb, s));
     }

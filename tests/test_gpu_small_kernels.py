@@ -192,3 +192,24 @@ def test_normalize_trace(T, ctx, n, dt):
     assert np.abs(t.numpy() - ref).max() <= (n + 8) * U64 * np.abs(ref).max() * np.sqrt(n) + 2 * u * np.abs(ref).max()
     with pytest.raises(T.TciError):
         T.normalize_trace(ctx, T.Tensor.from_numpy(ctx, np.zeros((2, 3)), T.F64))
+
+
+# 64 tensors per launch; complex64 factors with an odd element count (8-byte copies); an update without a gate
+@pytest.mark.parametrize("batch,dt", [(1, "C64"), (63, "F32"), (65, "C64"), (130, "F64")])
+def test_update_batches_beyond_one_table(T, ctx, batch, dt):
+    """Every update of a batch equals the same update alone, up to the rounding of a single-precision result."""
+    code = getattr(T, dt)
+    prec = T.PREC_FP64 if dt == "F64" else T.PREC_FP32
+    p = T.update_params(chi_min=1, chi_max=4, direction=T.DIR_LEFT, precision=prec, max_batch=128)
+    up = lambda x: T.Tensor.from_numpy(ctx, x.astype(T.NUMPY_OF[code]), code)  # noqa: E731
+    c = dt.startswith("C")
+    A = [up(draw((3, 2, 5), c, 3 * i)) for i in range(batch)]
+    B = [up(draw((5, 2, 3), c, 3 * i + 1)) for i in range(batch)]
+    G = [up(draw((2, 2, 2, 2), c, 3 * i + 2)) if i % 3 else None for i in range(batch)]
+    Ao, so, Bo, info = T.two_site_update_batched(ctx, A, B, G, p)
+    tol = 1e-12 if dt == "F64" else 2e-6
+    for i in range(batch):
+        a1, s1, b1, _ = T.two_site_update_batched(ctx, [A[i]], [B[i]], [G[i]], p)
+        assert Ao[i].numpy().shape == (3, 2, 4) and info[i].chi == 4
+        for x, y in ((Ao[i], a1[0]), (so[i], s1[0]), (Bo[i], b1[0])):
+            assert np.abs(x.numpy() - y.numpy()).max() <= tol
