@@ -113,21 +113,23 @@ hipError_t split_planes(int dtype, const void* src, long long ld, long long ssrc
 }
 
 // ---------------------------------------------------------------------------
-// GEMM on planes.  Workgroup tile 128 x 128 with 8 waves in a 2 x 4 grid,
-// each wave 64 x 32 (4 x 2 MFMA blocks), so that a wave needs at most 256
-// registers and two waves share each SIMD: one wave's LDS and global-load
-// waits are covered by the other's matrix work.  Staging: each plane tile is
-// 128 rows x 32 k = 8 KB = 512 chunks of 16 bytes; thread t moves chunk t of
-// every plane of both operands, straight from global memory into LDS
-// (global_load_lds, no staging registers), one k tile ahead.
+// GEMM on planes.  Workgroup tile BM x BN with a WM x WN grid of waves: 128 x
+// 128 with 8 waves of 64 x 32 (4 x 2 MFMA blocks), so that a wave needs at most
+// 256 registers and two waves share each SIMD: one wave's LDS and global-load
+// waits are covered by the other's matrix work; 64 x 64 and 32 x 32 with 4
+// waves where a launch of large tiles leaves compute units idle.  Staging: a
+// plane tile is BM rows x 32 k = 4 BM chunks of 16 bytes, moved straight from
+// global memory into LDS (global_load_lds, no staging registers), one k tile
+// ahead.  The k order of the sums is the same for every tile.
 // ---------------------------------------------------------------------------
-constexpr int XWM = 64, XWN = 32;   // wave tile
-template <bool CPLX>
-__global__ __launch_bounds__(512) void gemm_planes_kernel(PlaneGemmArgs a) {
+template <bool CPLX, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_planes_kernel(PlaneGemmArgs a) {
   constexpr int NP = CPLX ? 4 : 2;
+  constexpr int XWM = BM / WM, XWN = BN / WN;   // wave tile
   constexpr int IM = XWM / 16, JN = XWN / 16;
-  __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][XBM][XBK];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][XBN][XBK];
+  static_assert(BM == BN && (BM / 16 == WM * WN || 2 * BM / 16 == WM * WN), "staging: 16 rows per wave and operand");
+  __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][BM][XBK];
+  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][BN][XBK];
   // tile coordinates, XCD-aware as in the plain GEMM
   const int gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
   const long total = (long)gx * gy * gz;
@@ -144,12 +146,12 @@ __global__ __launch_bounds__(512) void gemm_planes_kernel(PlaneGemmArgs a) {
   const int gm = min(GM, gy - first);
   const int rr = tt % gsize;
   const int tm = first + rr % gm, tn = rr / gm;
-  const int m0 = tm * XBM, n0 = tn * XBN;
+  const int m0 = tm * BM, n0 = tn * BN;
   const __bf16* A = a.Ap + b * a.sAp;
   const __bf16* B = a.Bp + b * a.sBp;
   const long long pa = (long long)a.Mp * a.Kp, pb = (long long)a.Np * a.Kp;
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-  const int wm = wid >> 2, wn = wid & 3;
+  const int wm = wid / WN, wn = wid % WN;
   const int lr = lane & 15, lk = lane >> 4;
   const int rd = 8 * (lk ^ (((lr >> 1) ^ (lr >> 2)) & 3));   // swizzled k offset of this lane's operand chunk
 
@@ -165,11 +167,15 @@ __global__ __launch_bounds__(512) void gemm_planes_kernel(PlaneGemmArgs a) {
       acc_ii[i][j] = f4v{0, 0, 0, 0};
     }
 
-  // Global -> LDS without registers: each wave moves rows 16 wid .. 16 wid + 15
-  // of every plane tile, lane l writing the 16 bytes at l * 16 of that
-  // 1 KB block (row 16 wid + l / 4, chunk position l & 3), so it loads the
-  // k chunk that the swizzle puts there, (l & 3) ^ swz(row).
-  const int srow = t >> 2, skc = t & 3;
+  // Global -> LDS without registers: each wave moves 16 rows of every plane
+  // tile, of both operands (16 wid .., when there are as many waves as row
+  // groups) or of one of them (the first half of the waves A, the others B);
+  // lane l writes the 16 bytes at l * 16 of that 1 KB block (row l / 4, chunk
+  // position l & 3), so it loads the k chunk that the swizzle puts there,
+  // (l & 3) ^ swz(row).
+  constexpr bool BOTH = BM / 16 == WM * WN;
+  const int grp = BOTH ? wid : wid % (BM / 16);
+  const int srow = 16 * grp + (lane >> 2), skc = lane & 3;
   const int gk = 8 * (skc ^ (((srow >> 1) ^ (srow >> 2)) & 3));
   typedef __attribute__((address_space(3))) void lds_void;
   typedef __attribute__((address_space(1))) void glb_void;
@@ -178,8 +184,10 @@ __global__ __launch_bounds__(512) void gemm_planes_kernel(PlaneGemmArgs a) {
   auto issue = [&](int k0, int st) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      __builtin_amdgcn_global_load_lds((glb_void*)(ga + p * pa + k0), (lds_void*)&As[st][p][16 * wid][0], 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((glb_void*)(gb + p * pb + k0), (lds_void*)&Bs[st][p][16 * wid][0], 16, 0, 0);
+      if (BOTH || wid < BM / 16)
+        __builtin_amdgcn_global_load_lds((glb_void*)(ga + p * pa + k0), (lds_void*)&As[st][p][16 * grp][0], 16, 0, 0);
+      if (BOTH || wid >= BM / 16)
+        __builtin_amdgcn_global_load_lds((glb_void*)(gb + p * pb + k0), (lds_void*)&Bs[st][p][16 * grp][0], 16, 0, 0);
     }
   };
 
@@ -261,12 +269,32 @@ __global__ __launch_bounds__(512) void gemm_planes_kernel(PlaneGemmArgs a) {
 hipError_t gemm_planes(int dtype, const PlaneGemmArgs& a, hipStream_t s) {
   if (a.m <= 0 || a.n <= 0 || a.batch <= 0) return hipSuccess;
   if (a.Mp % XBM || a.Np % XBN || a.Kp % XBK || a.Mp < a.m || a.Np < a.n) return hipErrorInvalidValue;
-  dim3 grid(a.Np / XBN, a.Mp / XBM, a.batch);
   const bool cplx = dtype == C64;
   const double flops = (cplx ? 8.0 : 2.0) * 3.0 * a.m * (double)a.n * a.k * a.batch;
   ProfScope ps(s, flops, cplx ? "c64_bf16x3_planes" : "f32_bf16x3_planes");
-  if (cplx) hipLaunchKernelGGL(gemm_planes_kernel<true>, grid, dim3(512), 0, s, a);
-  else hipLaunchKernelGGL(gemm_planes_kernel<false>, grid, dim3(512), 0, s, a);
+  // Tile by a model of the cycles per k tile: rounds of 256 workgroups at the
+  // tile's matrix (128, 64) or LDS (32) time, plus the latency of a step; a
+  // smaller tile has to win 10%.  Effective-Hamiltonian products at chi 250
+  // (80 and 16 tiles of 128): 42.9 us on average in large tiles, 16.6 us with
+  // 64 x 64 for the left and 32 x 32 for the right step.
+  const int tile[3] = {128, 64, 32};
+  const double cyc[3] = {3072.0, 768.0, 375.0};
+  int best = 0;
+  double best_t = 0.0;
+  for (int c = 0; c < 3; ++c) {
+    const long long w = (long long)((a.m + tile[c] - 1) / tile[c]) * ((a.n + tile[c] - 1) / tile[c]) * a.batch;
+    const double t = (double)((w + 255) / 256) * cyc[c] + 700.0;
+    if (c == 0 || t < 0.9 * best_t) {
+      best = c;
+      best_t = t;
+    }
+  }
+  const int bt = tile[best];
+  const dim3 grid((a.n + bt - 1) / bt, (a.m + bt - 1) / bt, a.batch);
+  auto go = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a); };
+  if (bt == 128) cplx ? go(gemm_planes_kernel<true, 128, 128, 2, 4>, 512) : go(gemm_planes_kernel<false, 128, 128, 2, 4>, 512);
+  else if (bt == 64) cplx ? go(gemm_planes_kernel<true, 64, 64, 2, 2>, 256) : go(gemm_planes_kernel<false, 64, 64, 2, 2>, 256);
+  else cplx ? go(gemm_planes_kernel<true, 32, 32, 2, 2>, 256) : go(gemm_planes_kernel<false, 32, 32, 2, 2>, 256);
   return hipGetLastError();
 }
 
