@@ -213,3 +213,33 @@ def test_update_batches_beyond_one_table(T, ctx, batch, dt):
         assert Ao[i].numpy().shape == (3, 2, 4) and info[i].chi == 4
         for x, y in ((Ao[i], a1[0]), (so[i], s1[0]), (Bo[i], b1[0])):
             assert np.abs(x.numpy() - y.numpy()).max() <= tol
+
+
+# left / right products of the split-BF16x3 planes: 1 x 1, 8 x 3 and 33 x 70 in 32 x 32 tiles, 250 x 200 in
+# 64 x 64 and 32 x 32, 400 x 390 in 128 x 128 and 64 x 64; bonds that leave a remainder in every tile
+@pytest.mark.parametrize("complex_", [True, False])
+@pytest.mark.parametrize("cl,cr", [(1, 1), (8, 3), (33, 70), (250, 200), (400, 390)])
+def test_plane_product_tiles(T, ctx, cl, cr, complex_):
+    """With 8-bit significands the split leaves 2^-18 of each factor and drops a product of at most 2^-18: 3 x 2^-18
+    per term and step, 3.5e-5 in three steps, of random sign; single-precision sums add far less.  Bounded by the
+    sum of the terms' moduli for each element, and by the norm where there are enough of them to average."""
+    from oracle import dmrg as odmrg
+    lo, code = (np.complex64, T.C64) if complex_ else (np.float32, T.F32)
+    w = synth.heisenberg_mpo()
+    arrs = [draw((cl, 5, cl), complex_, cl), w if complex_ else w.real, draw((cr, 5, cr), complex_, cr + 1),
+            draw((cl, 2, 2, cr), complex_, cl + 2)]
+    left, w, right, x = (np.asarray(a).astype(lo) for a in arrs)
+    l64, w64, r64, x64 = (a.astype(np.complex128) for a in (left, w, right, x))
+    ref = odmrg.heff_apply(l64, w64, w64, r64, x64)
+    up = lambda a: T.Tensor.from_numpy(ctx, a, code)  # noqa: E731
+    ctx.set_precision(T.PREC_BF16X3)
+    try:
+        y = T.heff_matvec(ctx, up(left), up(w), up(w), up(right), up(x)).numpy()
+    finally:
+        ctx.set_precision(T.PREC_FP32)
+    err = np.abs(y - ref)
+    terms = odmrg.heff_apply(*(np.abs(a) for a in (l64, w64, w64, r64, x64))).real
+    assert (err <= 2 * 3.5e-5 * terms + 1e-30).all()
+    if cl > 1:
+        assert np.linalg.norm(err) <= 3.5e-5 * np.linalg.norm(ref)
+        assert err.max() <= 40 * 3.5e-5 * np.linalg.norm(ref) / np.sqrt(ref.size)
