@@ -1113,176 +1113,222 @@ __device__ inline double hash_uniform(unsigned b, unsigned j, unsigned i) {
   return ((double)h + 0.5) * (2.0 / 4294967296.0) - 1.0;
 }
 
-// The recurrences below are sequential in i, one lane per eigenvector.  Each
-// pass walks i in blocks of IV_BLK and issues all loads of a block before the
-// block's arithmetic, so that one memory latency is paid per block rather than
-// per step (the stores of a step could alias the next step's loads, which
-// keeps the compiler from moving them ahead by itself).
-constexpr int IV_BLK = 16;
+// The recurrences below are sequential in i, one lane per eigenvector; a launch
+// has few waves (2 per problem at 100 vectors), so what bounds it is the chain
+// of one step and the latency of its loads.  Each pass walks i in blocks of
+// IV_BLK with the next block's loads issued before this block's arithmetic
+// (the stores of a step could alias them, which keeps the compiler from moving
+// them ahead by itself).  The first forward solve runs inside the elimination,
+// the 2-norm is summed in the last backward one, a pivot's reciprocal comes
+// from refined seeds and interchanges are selections.  16 complex problems of
+// order 200, 100 vectors each: 202 us with divisions, branches, a pass of its
+// own for each of these and loads at a block's start; 93 us now (300 of order
+// 300: 308 and 140).
+constexpr int IV_BLK = 16, IV_BK2 = 8;   // forward; backward, with twice the loads per step
 
-// One solve with the stored factors of column j: z[:, j] <- (T - lam_j)^-1
-// (pre * z[:, j]); returns the factor 1 / max|z| for the next right-hand side.
-// ru holds the reciprocals of U's diagonal.
-__device__ inline double invit_solve(double* z, long ld, int j, int n, const double* ru, const double* du,
-                                     const double* du2, const double* dl, double pre) {
-  // forward: b <- L^-1 P b, writing the intermediate into z
+// forward: b <- L^-1 P (pre * z[:, j]), in place
+__device__ __forceinline__ void invit_forward(double* z, long ld, unsigned j, int n, const double* dl, double pre) {
+  struct Blk { double z[IV_BLK], s[IV_BLK]; };
   double bi = z[j] * pre;
-  for (int i0 = 0; i0 < n - 1; i0 += IV_BLK) {
-    double zb[IV_BLK], sb[IV_BLK];
+  auto load = [&](Blk& k, int i0) {
 #pragma unroll
     for (int u = 0; u < IV_BLK; ++u) {
-      const int i = i0 + u;
-      zb[u] = 0.0;
-      sb[u] = 0.0;
-      if (i < n - 1) {
-        zb[u] = z[(long)(i + 1) * ld + j];
-        sb[u] = dl[(long)i * ld + j];
-      }
+      const int i = min(i0 + u, n - 2);
+      k.z[u] = (z + (long)(i + 1) * ld)[j];
+      k.s[u] = (dl + (long)i * ld)[j];
     }
+  };
+  auto step = [&](const Blk& k, int u, int i) {
+    const double bn = k.z[u] * pre, sv = k.s[u];
+    const bool sw = fabs(sv) >= 4.0;
+    const double m = sw ? sv - copysign(4.0, sv) : sv;
+    (z + (long)i * ld)[j] = sw ? bn : bi;
+    const double p = sw ? bn : bi, q = sw ? bi : bn;
+    bi = q - m * p;
+  };
+  auto block = [&](const Blk& k, int i0) {
+    if (i0 + IV_BLK <= n - 1) {
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u) {
-      const int i = i0 + u;
-      if (i < n - 1) {
-        const double bn = zb[u] * pre;
-        const double sv = sb[u];
-        if (fabs(sv) >= 4.0) {
-          const double m = sv - (sv >= 0 ? 4.0 : -4.0);
-          z[(long)i * ld + j] = bn;
-          bi = bi - m * bn;
-        } else {
-          z[(long)i * ld + j] = bi;
-          bi = bn - sv * bi;
-        }
-      }
+      for (int u = 0; u < IV_BLK; ++u) step(k, u, i0 + u);
+    } else {
+#pragma unroll
+      for (int u = 0; u < IV_BLK; ++u)
+        if (i0 + u < n - 1) step(k, u, i0 + u);
+    }
+  };
+  if (n > 1) {
+    Blk p, q;
+    load(p, 0);
+    for (int i0 = 0; i0 < n - 1; i0 += 2 * IV_BLK) {
+      load(q, i0 + IV_BLK);
+      block(p, i0);
+      load(p, i0 + 2 * IV_BLK);
+      block(q, i0 + IV_BLK);
     }
   }
   z[(long)(n - 1) * ld + j] = bi;
-  // backward: U x = b
-  double x1 = 0.0, x2 = 0.0, amax = 0.0;
-  for (int i0 = n - 1; i0 >= 0; i0 -= IV_BLK) {
-    double zb[IV_BLK], c1[IV_BLK], c2[IV_BLK], r0[IV_BLK];
+}
+
+// backward: U x = b, in place; ru holds the reciprocals of U's diagonal.
+// Returns max|x| and the sum of squares.
+__device__ __forceinline__ double invit_backward(double* z, long ld, unsigned j, int n, const double* ru,
+                                                 const double* du, const double* du2, double& sq) {
+  struct Blk { double z[IV_BK2], c1[IV_BK2], c2[IV_BK2], r[IV_BK2]; };
+  double x1 = 0.0, x2 = 0.0, amax = 0.0, nn = 0.0;
+  auto load = [&](Blk& k, int i0) {
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u) {
-      const int i = i0 - u;
-      zb[u] = 0.0; c1[u] = 0.0; c2[u] = 0.0; r0[u] = 0.0;
-      if (i >= 0) {
-        zb[u] = z[(long)i * ld + j];
-        c1[u] = du[(long)i * ld + j];
-        c2[u] = du2[(long)i * ld + j];
-        r0[u] = ru[(long)i * ld + j];
-      }
+    for (int u = 0; u < IV_BK2; ++u) {
+      const long o = (long)max(i0 - u, 0) * ld;
+      k.z[u] = (z + o)[j];
+      k.c1[u] = (du + o)[j];
+      k.c2[u] = (du2 + o)[j];
+      k.r[u] = (ru + o)[j];
     }
+  };
+  auto step = [&](const Blk& k, int u, int i) {
+    const double x = ((k.z[u] - k.c2[u] * x2) - k.c1[u] * x1) * k.r[u];
+    (z + (long)i * ld)[j] = x;
+    x2 = x1;
+    x1 = x;
+    amax = fmax(amax, fabs(x));
+    nn += x * x;
+  };
+  auto block = [&](const Blk& k, int i0) {
+    if (i0 - IV_BK2 >= -1) {
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u) {
-      const int i = i0 - u;
-      if (i >= 0) {
-        const double x = (zb[u] - c1[u] * x1 - c2[u] * x2) * r0[u];
-        z[(long)i * ld + j] = x;
-        x2 = x1;
-        x1 = x;
-        amax = fmax(amax, fabs(x));
-      }
+      for (int u = 0; u < IV_BK2; ++u) step(k, u, i0 - u);
+    } else {
+#pragma unroll
+      for (int u = 0; u < IV_BK2; ++u)
+        if (i0 - u >= 0) step(k, u, i0 - u);
     }
+  };
+  Blk p, q;
+  load(p, n - 1);
+  for (int i0 = n - 1; i0 >= 0; i0 -= 2 * IV_BK2) {
+    load(q, i0 - IV_BK2);
+    block(p, i0);
+    load(p, i0 - 2 * IV_BK2);
+    block(q, i0 - IV_BK2);
   }
+  sq = nn;
+  return amax;
+}
+
+// One solve with the stored factors of column j: z[:, j] <- (T - lam_j)^-1
+// (pre * z[:, j]); returns the factor 1 / max|z| for the next right-hand side.
+__device__ __forceinline__ double invit_solve(double* z, long ld, unsigned j, int n, const double* ru, const double* du,
+                                     const double* du2, const double* dl, double pre) {
+  double sq;
+  invit_forward(z, ld, j, n, dl, pre);
+  const double amax = invit_backward(z, ld, j, n, ru, du, du2, sq);
   return amax > 0.0 ? 1.0 / amax : 1.0;
 }
 
-__global__ __launch_bounds__(64) void invit_kernel(const double* d, const double* e, long long sde, int n,
-                                                   const double* lam, long long slam, const int* chi,
-                                                   int kmax, double* Z, long long ldz, long long sZ,
-                                                   double* w_ru, double* w_du, double* w_du2,
-                                                   double* w_dl, long long sw, int batch) {
+__global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d, const double* __restrict__ e,
+                                                   long long sde, int n, const double* __restrict__ lam,
+                                                   long long slam, const int* __restrict__ chi, int kmax, double* Z,
+                                                   long long ldz, long long sZ, double* w_ru, double* w_du,
+                                                   double* w_du2, double* w_dl, long long sw_, int batch) {
   const int b = blockIdx.y;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch || j >= kmax) return;
-  const int cb = chi ? chi[b] : kmax;
-  if (j >= cb) return;
+  const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
+  const int cb = chi ? min(chi[b], kmax) : kmax;
+  if ((int)(blockIdx.x * blockDim.x) >= cb) return;
   const double* db = d + b * sde;
   const double* eb = e + b * sde;
-  double* ru = w_ru + b * sw;
-  double* du = w_du + b * sw;
-  double* du2 = w_du2 + b * sw;
-  double* dl = w_dl + b * sw;
+  double* ru = w_ru + b * sw_;
+  double* du = w_du + b * sw_;
+  double* du2 = w_du2 + b * sw_;
+  double* dl = w_dl + b * sw_;
   double* z = Z + b * sZ;
   const long ld = ldz;
-  const double lamj = lam[b * slam + j];
   double tnorm = 0.0;
-  for (int i = 0; i < n; ++i) tnorm = fmax(tnorm, fabs(db[i]) + (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i < n - 1 ? fabs(eb[i]) : 0.0));
-  const double tiny = fmax(tnorm, 1e-300) * 2.220446049250313e-16;
+  for (int i = threadIdx.x; i < n; i += 64)
+    tnorm = fmax(tnorm, fabs(db[i]) + (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i < n - 1 ? fabs(eb[i]) : 0.0));
+  for (int off = 32; off > 0; off >>= 1) tnorm = fmax(tnorm, __shfl_xor(tnorm, off, 64));
+  if ((int)j >= cb) return;
+  // in units of a power of two near the norm (the vectors do not depend on
+  // it), so that no reciprocal leaves the range
+  int ex = 0;
+  if (tnorm > 0.0 && tnorm < 1e308) (void)frexp(tnorm, &ex);
+  const double un = ldexp(1.0, -max(ex, -1000));
+  const double lamj = lam[b * slam + j] * un;
+  const double tiny = fmax(tnorm * un, 0.5) * 2.220446049250313e-16;
 
   // Elimination keeps one "active" row (entries a_i, c_i in columns i, i+1)
   // and meets original row i+1 (e_i, d_{i+1} - lam, e_{i+1}).  U row i is
   // stored as (1 / pivot, du, du2); the multiplier goes to dl, offset by +-4
-  // when the rows were interchanged (|multiplier| <= 1 in both cases).
-  double a_i = db[0] - lamj;       // current diagonal entry of the active row i
-  double c_i = (n > 1) ? eb[0] : 0.0;  // super-diagonal of active row
-  for (int i0 = 0; i0 < n - 1; i0 += IV_BLK) {
-    double ev[IV_BLK + 1], dv[IV_BLK];
+  // when the rows were interchanged (|multiplier| <= 1 in both cases).  bi is
+  // the active row's right-hand side, from the pseudo-random start.
+  double a_i = db[0] * un - lamj;  // current diagonal entry of the active row i
+  double c_i = (n > 1) ? eb[0] * un : 0.0;  // super-diagonal of active row
+  double bi = hash_uniform(b, j, 0);
+  auto step = [&](int i, double sub, double dn, double c_n) {  // entries (i+1, i), (i+1, i+1), (i+1, i+2)
+    const double a_n = dn - lamj;
+    const bool sw = (fabs(a_i) < fabs(sub)) & (fabs(sub) > 1e-290);   // interchange rows i and i+1
+    const double pa = fabs(a_i) < tiny ? (a_i >= 0 ? tiny : -tiny) : a_i;
+    const double piv = sw ? sub : pa, num = sw ? a_i : sub;
+    const double y0 = __builtin_amdgcn_rcp(piv);
+    const double y1 = fma(y0, fma(-piv, y0, 1.0), y0);
+    const double m0 = num * y1;
+    const double m = fma(fma(-piv, m0, num), y1, m0);   // num / piv, the residual corrected once
+    const long o = (long)i * ld;
+    const double p = sw ? a_n : c_i, q = sw ? c_i : a_n;
+    (ru + o)[j] = fma(y1, fma(-piv, y1, 1.0), y1);
+    (du + o)[j] = p;
+    (du2 + o)[j] = sw ? c_n : 0.0;
+    (dl + o)[j] = sw ? m + copysign(4.0, m) : m;       // |stored| >= 4 marks an interchange
+    a_i = q - m * p;
+    c_i = sw ? -m * c_n : c_n;
+    const double bn = hash_uniform(b, j, i + 1);
+    const double bp = sw ? bn : bi, bq = sw ? bi : bn;
+    (z + o)[j] = bp;
+    bi = bq - m * bp;
+  };
+  int i0 = 0;
+  for (; i0 + IV_BK2 < n - 1; i0 += IV_BK2) {
+    double ev[IV_BK2 + 1], dv[IV_BK2];
 #pragma unroll
-    for (int u = 0; u <= IV_BLK; ++u) {
-      const int i = i0 + u;
-      ev[u] = i < n - 1 ? eb[i] : 0.0;
-    }
+    for (int u = 0; u <= IV_BK2; ++u) ev[u] = eb[i0 + u] * un;
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u) {
-      const int i = i0 + u;
-      dv[u] = i + 1 < n ? db[i + 1] : 0.0;
-    }
+    for (int u = 0; u < IV_BK2; ++u) dv[u] = db[i0 + 1 + u] * un;
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u) {
-      const int i = i0 + u;
-      if (i < n - 1) {
-        const double sub = ev[u];                              // entry (i+1, i)
-        const double a_n = dv[u] - lamj;                       // entry (i+1, i+1)
-        const double c_n = (i + 1 < n - 1) ? ev[u + 1] : 0.0;  // entry (i+1, i+2)
-        if (fabs(a_i) >= fabs(sub)) {
-          double piv = a_i;
-          if (fabs(piv) < tiny) piv = (piv >= 0 ? tiny : -tiny);
-          const double m = sub / piv;
-          ru[(long)i * ld + j] = 1.0 / piv;
-          du[(long)i * ld + j] = c_i;
-          du2[(long)i * ld + j] = 0.0;
-          dl[(long)i * ld + j] = m;
-          a_i = a_n - m * c_i;
-          c_i = c_n;
-        } else {
-          // interchange rows i and i+1
-          const double m = a_i / sub;
-          ru[(long)i * ld + j] = 1.0 / sub;
-          du[(long)i * ld + j] = a_n;
-          du2[(long)i * ld + j] = c_n;
-          dl[(long)i * ld + j] = m + (m >= 0 ? 4.0 : -4.0);  // |stored| >= 4 marks an interchange
-          const double na = c_i - m * a_n;
-          a_i = na;
-          c_i = -m * c_n;
-        }
-      }
-    }
+    for (int u = 0; u < IV_BK2; ++u) step(i0 + u, ev[u], dv[u], ev[u + 1]);
   }
+  for (; i0 < n - 1; ++i0) step(i0, eb[i0] * un, db[i0 + 1] * un, i0 + 1 < n - 1 ? eb[i0 + 1] * un : 0.0);
   {
     double piv = a_i;
     if (fabs(piv) < tiny) piv = (piv >= 0 ? tiny : -tiny);
-    ru[(long)(n - 1) * ld + j] = 1.0 / piv;
-    du[(long)(n - 1) * ld + j] = 0.0;
-    du2[(long)(n - 1) * ld + j] = 0.0;
+    const long o = (long)(n - 1) * ld + j;
+    ru[o] = 1.0 / piv;
+    du[o] = 0.0;
+    du2[o] = 0.0;
+    z[o] = bi;
   }
-  // two solves from a pseudo-random start
-  for (int i = 0; i < n; ++i) z[(long)i * ld + j] = hash_uniform(b, j, i);
-  double scale = 1.0;
-  for (int it = 0; it < 2; ++it) scale = invit_solve(z, ld, j, n, ru, du, du2, dl, scale);
-  // normalise to unit 2-norm (after the last max-scaling)
-  double nn = 0.0;
-  for (int i = 0; i < n; ++i) {
-    const double x = z[(long)i * ld + j] * scale;
-    nn += x * x;
+  double nn;
+  double amax = invit_backward(z, ld, j, n, ru, du, du2, nn);
+  invit_forward(z, ld, j, n, dl, amax > 0.0 ? 1.0 / amax : 1.0);
+  amax = invit_backward(z, ld, j, n, ru, du, du2, nn);
+  // normalise to unit 2-norm; squares that could leave the range are summed
+  // again after scaling by the largest entry
+  double inv;
+  if (amax > 1e-130 && amax < 1e130) {
+    inv = 1.0 / sqrt(nn);
+  } else {
+    const double scale = amax > 0.0 ? 1.0 / amax : 1.0;
+    nn = 0.0;
+    for (int i = 0; i < n; ++i) {
+      const double x = z[(long)i * ld + j] * scale;
+      nn += x * x;
+    }
+    inv = scale / sqrt(nn);
   }
-  const double inv = scale / sqrt(nn);
-  for (int i0 = 0; i0 < n; i0 += IV_BLK) {
-    double zb[IV_BLK];
+  for (int i0 = 0; i0 < n; i0 += 2 * IV_BLK) {
+    double zb[2 * IV_BLK];
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u) zb[u] = i0 + u < n ? z[(long)(i0 + u) * ld + j] : 0.0;
+    for (int u = 0; u < 2 * IV_BLK; ++u) zb[u] = z[(long)min(i0 + u, n - 1) * ld + j];
 #pragma unroll
-    for (int u = 0; u < IV_BLK; ++u)
+    for (int u = 0; u < 2 * IV_BLK; ++u)
       if (i0 + u < n) z[(long)(i0 + u) * ld + j] = zb[u] * inv;
   }
 }
