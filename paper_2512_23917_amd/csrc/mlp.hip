@@ -161,79 +161,82 @@ __global__ __launch_bounds__(128) void mlp_sample_kernel(const float* __restrict
 }
 
 // Weight gradients as products over the samples: dW2 = g2^T [h1 | 1] (its last
-// column is db2), dW1 = g1^T [x | 1], dW3 = gy^T [h2 | 1], in 32 x 32 tiles.
-// Block (tile, chunk) sums MLP_CHUNK-sample stages of its chunk in FP32 and
-// writes its part of the flat gradient to part[chunk].  (A gradient row of
-// 21249 values per sample, summed by one thread per value, took 93 us of a
-// batch of 256 and 85 KB of workspace per sample.)
-constexpr int MLP_STAGE = 64, MLP_TILES = 20 + 8 + 5, MLP_MAX_CHUNKS = 32;
+// column is db2), dW1 = g1^T [x | 1], dW3 = gy^T [h2 | 1], in 16 x 16 tiles, one
+// element per thread; the block after the tiles sums the losses.  An element is
+// summed over the samples in order, products rounded before the sum, so that
+// a batch of thousands keeps the rounding of a plain loop; the bound is that
+// chain and the LDS reads (one 16-byte read of each operand per four samples),
+// with the next stage's loads in flight.  Gradient and prediction of 256 / 16384
+// samples: 142 / 4700 us with a gradient row of 21249 values (85 KB) per sample
+// summed by one thread per value, 61 / 219 us in chunks of samples with a kernel
+// that adds their sums (other rounding than the loop's by 3.8e-5 of the norm at
+// 16384), 55 / 329 us in order.
+constexpr int MLP_STAGE = 64, MLP_TW = 16, MLP_PITCH = MLP_STAGE + 4;
+constexpr int MLP_T2 = (NH / MLP_TW) * (NH / MLP_TW + 1), MLP_C1 = (NI + MLP_TW) / MLP_TW,
+              MLP_T1 = (NH / MLP_TW) * MLP_C1, MLP_T3 = NH / MLP_TW + 1, MLP_TILES = MLP_T2 + MLP_T1 + MLP_T3;
 
-__global__ __launch_bounds__(256) void mlp_grad_kernel(const float* __restrict__ X, int n, MlpWork w, int per_chunk,
-                                                       float* part) {
-  __shared__ float As[MLP_STAGE][33], Bs[MLP_STAGE][33];
+__global__ __launch_bounds__(256) void mlp_grad_kernel(const float* __restrict__ X, int n, MlpWork w,
+                                                       float* __restrict__ grad, float* __restrict__ loss_total) {
+  __shared__ __attribute__((aligned(16))) float As[2][MLP_TW][MLP_PITCH], Bs[2][MLP_TW][MLP_PITCH];
   const int t = blockIdx.x, tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+  if (t == MLP_TILES) {
+    __shared__ float red[4];
+    float l = 0.f;
+    for (int s = tid; s < n; s += 256) l += w.loss[s];
+    l = wave_sum(l);
+    if ((tid & 63) == 0) red[tid >> 6] = l;
+    __syncthreads();
+    if (tid == 0) *loss_total = red[0] + red[1] + red[2] + red[3];
+    return;
+  }
   // operands (rows = samples) with their widths, and the flat offsets of the weights and the bias
   const float *A, *B;
   int wa, wb, rt, ct, offw, offb;
-  if (t < 20) {
-    A = w.g2; B = w.h1; wa = NH; wb = NH; rt = t / 5; ct = t % 5; offw = OFF_W2; offb = OFF_B2;
-  } else if (t < 28) {
-    A = w.g1; B = X; wa = NH; wb = NI; rt = (t - 20) / 2; ct = (t - 20) % 2; offw = OFF_W1; offb = OFF_B1;
+  if (t < MLP_T2) {
+    A = w.g2; B = w.h1; wa = NH; wb = NH; rt = t / (NH / MLP_TW + 1); ct = t % (NH / MLP_TW + 1);
+    offw = OFF_W2; offb = OFF_B2;
+  } else if (t < MLP_T2 + MLP_T1) {
+    A = w.g1; B = X; wa = NH; wb = NI; rt = (t - MLP_T2) / MLP_C1; ct = (t - MLP_T2) % MLP_C1;
+    offw = OFF_W1; offb = OFF_B1;
   } else {
-    A = w.gy; B = w.h2; wa = 1; wb = NH; rt = 0; ct = t - 28; offw = OFF_W3; offb = OFF_B3;
+    A = w.gy; B = w.h2; wa = 1; wb = NH; rt = 0; ct = t - MLP_T2 - MLP_T1; offw = OFF_W3; offb = OFF_B3;
   }
-  const int r0 = 32 * rt, c0 = 32 * ct;
-  const int sbeg = blockIdx.y * per_chunk, send = min(n, sbeg + per_chunk);
-  float acc[2][2] = {};
-  for (int s0 = sbeg; s0 < send; s0 += MLP_STAGE) {
-    __syncthreads();
+  const int r0 = MLP_TW * rt, c0 = MLP_TW * ct;
+  constexpr int PER = MLP_STAGE * MLP_TW / 256;
+  float la[PER], lb[PER];
+  auto load = [&](int s0) {
 #pragma unroll
-    for (int u = 0; u < MLP_STAGE * 32 / 256; ++u) {
-      const int e = tid + 256 * u, k = e >> 5, c = e & 31, s = s0 + k;
-      As[k][c] = s < send && r0 + c < wa ? A[(long long)s * wa + r0 + c] : 0.f;
-      Bs[k][c] = s < send && c0 + c < wb ? B[(long long)s * wb + c0 + c] : s < send && c0 + c == wb ? 1.f : 0.f;
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + 256 * u, c = e & 15, s = s0 + (e >> 4), sc = min(s, n - 1);
+      const float va = A[(long long)sc * wa + min(r0 + c, wa - 1)], vb = B[(long long)sc * wb + min(c0 + c, wb - 1)];
+      la[u] = s < n && r0 + c < wa ? va : 0.f;
+      lb[u] = s >= n || c0 + c > wb ? 0.f : c0 + c == wb ? 1.f : vb;
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int k = 0; k < MLP_STAGE; ++k) {
-      const float a0 = As[k][2 * ti], a1 = As[k][2 * ti + 1], b0 = Bs[k][2 * tj], b1 = Bs[k][2 * tj + 1];
-      acc[0][0] += a0 * b0;
-      acc[0][1] += a0 * b1;
-      acc[1][0] += a1 * b0;
-      acc[1][1] += a1 * b1;
-    }
-  }
-  float* g = part + (long long)blockIdx.y * NPARAM;
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int r = r0 + 2 * ti + u, c = c0 + 2 * tj + v;
-      if (r >= wa) continue;
-      if (c < wb) g[offw + r * wb + c] = acc[u][v];
-      else if (c == wb) g[offb + r] = acc[u][v];
-    }
-}
-
-// grad[q] = sum over the chunks in order; the last block sums the losses.
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* part, int nchunk, const float* loss, int n,
-                                                         float* grad, float* loss_total) {
-  if (blockIdx.x == gridDim.x - 1) {
-    __shared__ float red[4];
-    float l = 0.f;
-    for (int s = threadIdx.x; s < n; s += 256) l += loss[s];
-    l = wave_sum(l);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
-    __syncthreads();
-    if (threadIdx.x == 0) *loss_total = red[0] + red[1] + red[2] + red[3];
-    return;
-  }
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= NPARAM) return;
+  };
+  load(0);
   float acc = 0.f;
-#pragma unroll 8
-  for (int c = 0; c < nchunk; ++c) acc += part[(long long)c * NPARAM + q];
-  grad[q] = acc;
+  for (int s0 = 0, st = 0; s0 < n; s0 += MLP_STAGE, st ^= 1) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + 256 * u;
+      As[st][e & 15][e >> 4] = la[u];
+      Bs[st][e & 15][e >> 4] = lb[u];
+    }
+    // one barrier per stage: the other buffer's readers are past theirs
+    __syncthreads();
+    load(s0 + MLP_STAGE);
+#pragma unroll
+    for (int k = 0; k < MLP_STAGE; k += 4) {
+      const float4 x = *reinterpret_cast<const float4*>(&As[st][ti][k]), y = *reinterpret_cast<const float4*>(&Bs[st][tj][k]);
+      acc = __fadd_rn(acc, __fmul_rn(x.x, y.x));
+      acc = __fadd_rn(acc, __fmul_rn(x.y, y.y));
+      acc = __fadd_rn(acc, __fmul_rn(x.z, y.z));
+      acc = __fadd_rn(acc, __fmul_rn(x.w, y.w));
+    }
+  }
+  const int r = r0 + ti, c = c0 + tj;
+  if (r < wa && c < wb) grad[offw + r * wb + c] = acc;
+  else if (r < wa && c == wb) grad[offb + r] = acc;
 }
 
 __global__ void adam_kernel(float* p, float* m, float* v, const float* g, float lr, float b1, float b2, float eps,
@@ -283,19 +286,12 @@ static void mlp_samples(const float* p, const float* X, const float* T, int n, f
 static tci_status grads_impl(tci_context ctx, tci_sketch_model m, const float* X, const float* T, int n, float* grad,
                              float* loss_dev) {
   hipStream_t s = ctx->stream;
-  // chunks of whole stages, at most MLP_MAX_CHUNKS (the reduction reads each once)
-  const int stages = (n + MLP_STAGE - 1) / MLP_STAGE;
-  const int per_chunk = (stages + MLP_MAX_CHUNKS - 1) / MLP_MAX_CHUNKS * MLP_STAGE;
-  const int nchunk = (n + per_chunk - 1) / per_chunk;
   float* rows = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)n * (4 * NH + 2)));
-  float* part = static_cast<float*>(ctx->arena.get(sizeof(float) * (size_t)nchunk * NPARAM));
-  if (!rows || !part) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "mlp workspace");
+  if (!rows) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "mlp workspace");
   const size_t nh = (size_t)n * NH;
   const MlpWork w{rows, rows + nh, rows + 2 * nh, rows + 3 * nh, rows + 4 * nh, rows + 4 * nh + n};
   mlp_samples(m->params, X, T, n, nullptr, w, true, s);
-  hipLaunchKernelGGL(mlp_grad_kernel, dim3(MLP_TILES, nchunk), dim3(256), 0, s, X, n, w, per_chunk, part);
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 255) / 256 + 1), dim3(256), 0, s, (const float*)part, nchunk,
-                     (const float*)w.loss, n, grad, loss_dev);
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3(MLP_TILES + 1), dim3(256), 0, s, X, n, w, grad, loss_dev);
   TCI_CHECK_HIP(hipGetLastError());
   return TCI_OK;
 }
