@@ -204,7 +204,7 @@ tci_status noalloc_scratch_init(int device) {
 //   LZ_STOP  1 after an invariant subspace was found (later steps are void)
 //   LZ_M     number of recorded alpha (the order of T)
 //   LZ_FLAG  1 when the step needs the second Gram-Schmidt pass
-//   LZ_B2    ||w||^2 after the first pass, LZ_RB2 after the second
+//   LZ_B2    ||w||^2 after the first pass
 //   LZ_SCALE complex factor of the next basis vector: 1/||theta|| for v_0,
 //            1/beta_j after step j (0 after a breakdown); at the end the
 //            phase and normalisation of psi
@@ -212,7 +212,7 @@ tci_status noalloc_scratch_init(int device) {
 //   LZ_START 1 when theta has a finite nonzero norm, LZ_VALID 1 when the
 //            Ritz vector is finite and nonzero (theta is written only then)
 enum {
-  LZ_ALPHA = 0, LZ_BETA = 32, LZ_TMAX = 64, LZ_STOP, LZ_M, LZ_FLAG, LZ_B2, LZ_RB2,
+  LZ_ALPHA = 0, LZ_BETA = 32, LZ_TMAX = 64, LZ_STOP, LZ_M, LZ_FLAG, LZ_B2,
   LZ_SCALE = 72, LZ_NREORTH = 74, LZ_START, LZ_VALID, LZ_WORDS = 80
 };
 
@@ -231,8 +231,29 @@ __global__ void lz_init_kernel(double* k, const double* n2) {
 // take ||w||^2 and the projections c = coef[128 ..) of the pass, and ask for
 // a second pass when it removed more than half of the norm, ||w||^2 < ||c||^2
 // (Daniel, Gragg, Kaufman and Stewart, 1976).
-__global__ void lz_decide_kernel(double* k, const double* coef, int j) {
-  if (threadIdx.x != 0) return;
+// Both sums run here, in one workgroup (||w||^2 from the block partials of the
+// subtraction sweep): a launch of a few microseconds less per step each than
+// with a reduction kernel of its own, here and in lz_beta_kernel.
+__device__ inline double lz_block_sum(double v, double* sh) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+__device__ inline double lz_sum_parts(const double* part, int nparts, double* sh) {
+  double v = 0.0;
+  for (int b = threadIdx.x; b < nparts; b += 256) v += part[b];
+  return lz_block_sum(v, sh);
+}
+
+__global__ __launch_bounds__(256) void lz_decide_kernel(double* k, const double* coef, int j, const double* part,
+                                                        int nparts) {
+  __shared__ double sh[2][4];
+  const double* c1 = coef + 128;
+  const int t = threadIdx.x;
+  const double b2 = lz_sum_parts(part, nparts, sh[0]);
+  const double cn2 = lz_block_sum(t < 2 * (j + 1) ? c1[t] * c1[t] : 0.0, sh[1]);
+  if (t != 0) return;
   if (k[LZ_STOP] != 0.0) {
     k[LZ_FLAG] = 0.0;
     return;
@@ -241,26 +262,25 @@ __global__ void lz_decide_kernel(double* k, const double* coef, int j) {
   k[LZ_ALPHA + j] = a;
   k[LZ_M] = j + 1;
   k[LZ_TMAX] = fmax(k[LZ_TMAX], fabs(a));
-  const double* c1 = coef + 128;
-  double cn2 = 0.0;
-  for (int q = 0; q < 2 * (j + 1); ++q) cn2 += c1[q] * c1[q];
-  const double b2 = c1[2 * (j + 1)];
   k[LZ_B2] = b2;
   k[LZ_FLAG] = b2 < cn2 ? 1.0 : 0.0;
 }
 
 // beta_j = ||w|| after the passes; stop when it falls below 1e-13 of the
 // largest entry of T seen so far (the Krylov space is invariant).
-__global__ void lz_beta_kernel(double* k, int j) {
+__global__ __launch_bounds__(256) void lz_beta_kernel(double* k, int j, const double* part, int nparts) {
+  __shared__ double sh[4];
+  const bool second = k[LZ_STOP] == 0.0 && k[LZ_FLAG] != 0.0;
+  double rb2 = 0.0;
+  if (second) rb2 = lz_sum_parts(part, nparts, sh);
   if (threadIdx.x != 0) return;
   k[LZ_SCALE + 1] = 0.0;
   if (k[LZ_STOP] != 0.0) {
     k[LZ_SCALE] = 0.0;
     return;
   }
-  const bool second = k[LZ_FLAG] != 0.0;
   if (second) k[LZ_NREORTH] += 1.0;
-  const double b = sqrt(second ? k[LZ_RB2] : k[LZ_B2]);
+  const double b = sqrt(second ? rb2 : k[LZ_B2]);
   const double tmax = fmax(k[LZ_TMAX], b);
   k[LZ_TMAX] = tmax;
   if (b <= 1e-13 * tmax) {
@@ -460,6 +480,7 @@ tci_status tci_lanczos_ground(tci_context ctx, tci_tensor L, tci_tensor W1, tci_
     // bytes of one stored basis vector and of the working vector
     const double vbytes = (double)ves * (double)N, wbytes = (double)sizeof(cd) * (double)N;
     ProfTag tag("lanczos");
+    int nparts = 0;
     {
       ProfScope ps(s, vbytes * (j + 1) + 2 * wbytes, "sweep_dot");
       TCI_CHECK_HIP(three_term_multidot(basis, j + 1, coef, j > 0 ? kst + LZ_BETA + j - 1 : nullptr, w, N, part,
@@ -467,13 +488,13 @@ tci_status tci_lanczos_ground(tci_context ctx, tci_tensor L, tci_tensor W1, tci_
     }
     {
       ProfScope ps(s, vbytes * (j + 1) + 2 * wbytes, "sweep_axpy");
-      TCI_CHECK_HIP(multiaxpy_norm2(basis, j + 1, coef + 128, -1.0, w, N, part, coef + 128 + 2 * (j + 1), s, vdt));
+      TCI_CHECK_HIP(multiaxpy_norm2(basis, j + 1, coef + 128, -1.0, w, N, part, &nparts, s, vdt));
     }
-    hipLaunchKernelGGL(lz_decide_kernel, dim3(1), dim3(64), 0, s, kst, coef, j);
+    hipLaunchKernelGGL(lz_decide_kernel, dim3(1), dim3(256), 0, s, kst, coef, j, part, nparts);
     TCI_CHECK_HIP(hipGetLastError());
     TCI_CHECK_HIP(multidot(basis, j + 1, w, N, part, coef + 256, s, vdt, kst + LZ_FLAG));
-    TCI_CHECK_HIP(multiaxpy_norm2(basis, j + 1, coef + 256, -1.0, w, N, part, kst + LZ_RB2, s, vdt, kst + LZ_FLAG));
-    hipLaunchKernelGGL(lz_beta_kernel, dim3(1), dim3(64), 0, s, kst, j);
+    TCI_CHECK_HIP(multiaxpy_norm2(basis, j + 1, coef + 256, -1.0, w, N, part, &nparts, s, vdt, kst + LZ_FLAG));
+    hipLaunchKernelGGL(lz_beta_kernel, dim3(1), dim3(256), 0, s, kst, j, part, nparts);
     TCI_CHECK_HIP(hipGetLastError());
     void* vnext = basis + ves * (size_t)N * (j + 1);
     if (c64) TCI_CHECK_HIP(scale_to_c64_dev(w, kst + LZ_SCALE, vnext, N, s));

@@ -236,21 +236,18 @@ __global__ __launch_bounds__(256) void multidot_partial_kernel(const VT* V, int 
 __global__ __launch_bounds__(256) void multidot_final_kernel(const double* partial, int nparts, int nv, double* out,
                                                              const double* gate = nullptr) {
   if (gate && *gate == 0.0) return;
-  __shared__ double sr[256], si[256];
+  __shared__ double sh[4][2];
   const int q = blockIdx.x, t = threadIdx.x;
   double ar = 0.0, ai = 0.0;
   for (int b = t; b < nparts; b += 256) {
     ar += partial[((long long)b * MD_MAXV + q) * 2 + 0];
     ai += partial[((long long)b * MD_MAXV + q) * 2 + 1];
   }
-  sr[t] = ar;
-  si[t] = ai;
+  ar = wave_sum64(ar);
+  ai = wave_sum64(ai);
+  if ((t & 63) == 0) { sh[t >> 6][0] = ar; sh[t >> 6][1] = ai; }
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (t < off) { sr[t] += sr[t + off]; si[t] += si[t + off]; }
-    __syncthreads();
-  }
-  if (t == 0) { out[2 * q] = sr[0]; out[2 * q + 1] = si[0]; }
+  if (t < 2) out[2 * q + t] = (sh[0][t] + sh[1][t]) + (sh[2][t] + sh[3][t]);
 }
 
 static unsigned md_grid(long long n) {
@@ -387,22 +384,6 @@ __global__ __launch_bounds__(256) void multiaxpy_kernel(const VT* V, int nv, con
     __syncthreads();
     if (threadIdx.x == 0) nrm_part[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
   }
-}
-
-__global__ __launch_bounds__(256) void sum_parts_kernel(const double* part, int nparts, double* out,
-                                                        const double* gate) {
-  if (gate && *gate == 0.0) return;
-  __shared__ double sh[256];
-  const int t = threadIdx.x;
-  double a = 0.0;
-  for (int b = t; b < nparts; b += 256) a += part[b];
-  sh[t] = a;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (t < off) sh[t] += sh[t + off];
-    __syncthreads();
-  }
-  if (t == 0) out[0] = sh[0];
 }
 
 template <typename VT>
@@ -550,12 +531,10 @@ hipError_t three_term_multidot(const void* V, int nv, const double* alpha, const
 }
 
 hipError_t multiaxpy_norm2(const void* V, int nv, const double* c, double sign, void* w, long long n,
-                           double* partial, double* out, hipStream_t s, int vdt, const double* gate) {
+                           double* partial, int* nparts, hipStream_t s, int vdt, const double* gate) {
   if (nv <= 0 || nv > MD_MAXV) return hipErrorInvalidValue;
-  hipError_t e = multiaxpy_launch(V, nv, c, sign, w, n, partial, s, vdt, gate);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(256), 0, s, partial, (int)md_grid(n), out, gate);
-  return hipGetLastError();
+  *nparts = (int)md_grid(n);
+  return multiaxpy_launch(V, nv, c, sign, w, n, partial, s, vdt, gate);
 }
 
 // w = x * (sr + i si) (scaled copy, complex128)

@@ -34,9 +34,10 @@ hipError_t multiaxpy(const void* V, int nv, const double* c, double sign, void* 
 // (partial: MULTIDOT_PARTIAL_DOUBLES doubles of workspace)
 hipError_t three_term_multidot(const void* V, int nv, const double* alpha, const double* beta, void* w, long long n,
                                double* partial, double* out, hipStream_t s, int vdt = C128);
-// multiaxpy, then out[0] = ||w||^2 (partial: MULTIDOT_PARTIAL_DOUBLES doubles of workspace)
+// multiaxpy; ||w||^2 is then the sum of partial[0 .. *nparts)
+// (partial: MULTIDOT_PARTIAL_DOUBLES doubles of workspace)
 hipError_t multiaxpy_norm2(const void* V, int nv, const double* c, double sign, void* w, long long n,
-                           double* partial, double* out, hipStream_t s, int vdt = C128,
+                           double* partial, int* nparts, hipStream_t s, int vdt = C128,
                            const double* gate = nullptr);
 hipError_t scale_copy(const void* x, double sr, double si, void* w, long long n, hipStream_t s);
 // w = x (ps[0] + i ps[1]) with the factor on the device (complex128 -> complex128 / complex64);
