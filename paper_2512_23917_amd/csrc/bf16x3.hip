@@ -282,6 +282,7 @@ hipError_t gemm_planes(int dtype, const PlaneGemmArgs& a, hipStream_t s) {
   int best = 0;
   double best_t = 0.0;
   for (int c = 0; c < 3; ++c) {
+    if (c && (a.m + tile[c] - 1) / tile[c] > 65535) break;   // grid limit
     const long long w = (long long)((a.m + tile[c] - 1) / tile[c]) * ((a.n + tile[c] - 1) / tile[c]) * a.batch;
     const double t = (double)((w + 255) / 256) * cyc[c] + 700.0;
     if (c == 0 || t < 0.9 * best_t) {

@@ -9,8 +9,10 @@
 //      Hermitian matrix-vector product with the trailing matrix (the only
 //      O(n^2) step, memory bound) and one small fused kernel; per panel a
 //      rank-2NB update of the trailing matrix on the matrix cores.
-//   2. Bisection with Sturm counts for the top eigenvalues of T (one thread
-//      per eigenvalue).
+//      The last TRI_CHIP_N columns run in one workgroup per problem that
+//      holds the trailing matrix on chip.
+//   2. Multisection with Sturm counts for the top eigenvalues of T (1 to 64
+//      lanes per eigenvalue).
 //   3. Inverse iteration (tridiagonal LU with partial pivoting, two solves
 //      from a fixed pseudo-random start) for their eigenvectors Z (one
 //      thread per vector).
@@ -55,8 +57,6 @@ __device__ inline double sub(double a, double b) { return a - b; }
 __device__ inline cd sub(cd a, cd b) { return a - b; }
 __device__ inline double shfl_xor_t(double v, int m) { return __shfl_xor(v, m); }
 __device__ inline cd shfl_xor_t(cd v, int m) { return cd{__shfl_xor(v.x, m), __shfl_xor(v.y, m)}; }
-__device__ inline double shfl_t(double v, int l) { return __shfl(v, l); }
-__device__ inline cd shfl_t(cd v, int l) { return cd{__shfl(v.x, l), __shfl(v.y, l)}; }
 __device__ inline double rl(double, double r) { return r; }   // a real number as the element type
 __device__ inline cd rl(cd, double r) { return cd{r, 0.0}; }
 __device__ inline double wsum(double v) { return wave_sum(v); }
@@ -83,8 +83,8 @@ __device__ inline cd bsum(cd v, double* sh) {
 //    reflector of a(i+1:n,i): beta = -sign(Re a) ||.||, tau = (beta - a)/beta,
 //    v = [1, x / (a - beta)];  the chunk of tiles (R, cA..cB) adds
 //    sum_C A_RC v_C to P[cA][R rows], and each tile with C < R adds A_RC^H v_R
-//    to P[R][C rows]; partial quadratic form v^H A v and, with the diagonal
-//    tile, t1 = W^H v and t2 = V^H v over its rows, one partial per chunk.
+//    to P[R][C rows]; v^H A v, one partial per chunk, and with the diagonal tile
+//    t1 = W^H v and t2 = V^H v over its rows, one partial per band.
 // Every tile of the lower triangle is read once per column.  Partials are
 // summed by the kernel that consumes them (colC sums colA's norm partials,
 // colA the chunk partials of colC): the kernel boundary makes them visible,
