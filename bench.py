@@ -42,7 +42,7 @@ sys.path.insert(0, ROOT)
 
 KERNEL_OF_CLASS = {  # kernel that carries each profiling class
     "c64_bf16x3_planes": ("gemm_planes_kernel<true,128,128,2,4>", "paper_2512_23917_amd/csrc/bf16x3.hip"),
-    "c128_fp64": ("gemm_f64_kernel<cd,128,64>", "paper_2512_23917_amd/csrc/gemm.hip"),
+    "c128_fp64": ("gemm_f64_kernel<cd>", "paper_2512_23917_amd/csrc/gemm.hip"),
     "hemv": ("tri_colC_kernel<cd,32>", "paper_2512_23917_amd/csrc/eig.hip"),
     "tri_chip": ("tri_chip_kernel<double>", "paper_2512_23917_amd/csrc/eig.hip"),
 }
