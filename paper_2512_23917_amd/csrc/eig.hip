@@ -522,7 +522,10 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0,
                                  add(s_colsum[sb][2][lane], s_colsum[sb][3][lane]));
     } else {
       // t1 = W^H v and t2 = V^H v over the diagonal tile's rows: values
-      // m = 16 part .. + 15, m < NB for W's column m, else V's row m - NB
+      // m = 16 part .. + 15, m < NB for W's column m, else V's row m - NB.
+      // Rows <= i of W may never have been written, so they are selected away
+      // and not left to v = 0
+      const bool live = R * TT + lane > i && R * TT + lane < n;
 #pragma unroll 1
       for (int m0 = 16 * part; m0 < 16 * part + 16; m0 += 8) {
         T tt[8];
@@ -533,7 +536,7 @@ __global__ __launch_bounds__(256) void tri_colC_kernel(TriArgs a, int i, int j0,
           tt[u] = src[(long)min((m0 + u) & (NB - 1), max(p - 1, 0)) * n + rr];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) tt[u] = ((m0 + u) & (NB - 1)) < p ? mulr(cj(tt[u]), vR) : zero;
+        for (int u = 0; u < 8; ++u) tt[u] = ((m0 + u) & (NB - 1)) < p && live ? mulr(cj(tt[u]), vR) : zero;
 #pragma unroll
         for (int u = 0; u < 8; u += 4) {
           const T four[4] = {tt[u], tt[u + 1], tt[u + 2], tt[u + 3]};
@@ -845,8 +848,8 @@ hipError_t tridiagonalize(int dtype, const TriArgs& a, int batch, hipStream_t s)
     return hipGetLastError();
   }
   if (a.sws < (long long)tridiag_ws_bytes(dtype, a.n)) return hipErrorInvalidValue;
-  // partial sums and the reflector panel start at zero; the
-  // trailing-update operands are written before they are read
+  // the partial sums start at zero; the trailing-update operands, and what is
+  // used of the panel W, are written before they are read
   const size_t zb = dtype == C128 ? TriWs<cd, TRIDIAG_NB>::cat1(a.n) : TriWs<double, TRIDIAG_NB>::cat1(a.n);
   if (a.sws % 4 != 0) return hipErrorInvalidValue;
   hipError_t e = zero_fill_rows(a.ws, zb, (size_t)a.sws, batch, s);
