@@ -375,7 +375,10 @@ hipError_t copy_from_table(const PtrTable& src, void* dst, size_t stride, size_t
   if (n <= 0 || bytes == 0) return hipSuccess;
   // the widest elements that every address and size are multiples of
   size_t bits = (size_t)(uintptr_t)dst | stride | bytes;
-  for (int b = 0; b < n; ++b) bits |= (size_t)(uintptr_t)src.p[b];
+  for (int b = 0; b < n; ++b) {
+    if (!src.p[b]) return hipErrorInvalidValue;   // a moved-from tensor
+    bits |= (size_t)(uintptr_t)src.p[b];
+  }
   auto go = [&](auto kernel, size_t w) {
     const dim3 grid((unsigned)std::min<size_t>(1024, (bytes / w + 255) / 256), n);
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, src, static_cast<char*>(dst), stride, (long long)(bytes / w));
