@@ -745,7 +745,16 @@ tci_status tci_contract(tci_context ctx, tci_tensor a, const int32_t* la, int na
   for (int i : J) nat.push_back(lb[i]);
   bool same = (int)nat.size() == nc;
   for (int i = 0; same && i < nc; ++i) same = (nat[i] == lc[i]);
-  const bool alias = (c == a || c == b);
+  // Does the result share memory with an operand?  Wrapped tensors may, also with
+  // the present storage of an owning result, which ensure_shape frees when it has
+  // to grow: then the operands are read before that.
+  const size_t out_bytes = (size_t)M * N * es;
+  const size_t span = c->owns && c->cap < out_bytes ? c->cap : out_bytes;   // written or freed
+  auto shares = [&](tci_tensor t) {
+    const char *x = static_cast<const char*>(t->data), *y = static_cast<const char*>(c->data);
+    return t == c || (x && y && x < y + span && y < x + tbytes(t));
+  };
+  const bool alias = shares(a) || shares(b);
   // A^T form: a == [S..., I...]
   std::vector<int> permAt;
   for (int i : S) permAt.push_back(i);
@@ -761,33 +770,27 @@ tci_status tci_contract(tci_context ctx, tci_tensor a, const int32_t* la, int na
   if ((dt == C128 || dt == F64) && !alias && M > 0 && N > 0 && K > 0 && K <= (moves ? CONTRACT_MAX_K : 32) &&
       M * N <= CONTRACT_MAX_WORK / K && std::max({na, nb, nc}) <= CONTRACT_MAX_BONDS) {
     TCI_TRY(ensure_shape(ctx, c, dt, nc, cshape));
-    auto apart = [&](tci_tensor t) {   // wrapped tensors may share memory
-      const char *x = static_cast<const char*>(t->data), *y = static_cast<const char*>(c->data);
-      return x + tbytes(t) <= y || y + tbytes(c) <= x;
-    };
-    if (apart(a) && apart(b)) {
-      long long sta[MAX_ORDER + 1], stb[MAX_ORDER + 1];
-      int64_t sha[MAX_ORDER], shb[MAX_ORDER];
-      for (int i = 0; i < na; ++i) sha[i] = a->shape[i];
-      for (int i = 0; i < nb; ++i) shb[i] = b->shape[i];
-      row_major_strides(na, sha, sta);
-      row_major_strides(nb, shb, stb);
-      ContractArgs g{};
-      g.nc = nc; g.ns = (int)S.size(); g.nout = (int)(M * N); g.k = (int)K;
-      for (int i = 0; i < nc; ++i) {
-        const int ia = find_lab(la, na, lc[i]);
-        g.cdim[i] = (int)cshape[i];
-        g.sa[i] = ia >= 0 ? (int)sta[ia] : 0;
-        g.sb[i] = ia >= 0 ? 0 : (int)stb[find_lab(lb, nb, lc[i])];
-      }
-      for (size_t i = 0; i < S.size(); ++i) {
-        g.sdim[i] = (int)a->shape[S[i]];
-        g.ta[i] = (int)sta[S[i]];
-        g.tb[i] = (int)stb[Sb[i]];
-      }
-      TCI_CHECK_HIP(contract_small(dt, a->data, b->data, c->data, g, ctx->stream));
-      return TCI_OK;
+    long long sta[MAX_ORDER + 1], stb[MAX_ORDER + 1];
+    int64_t sha[MAX_ORDER], shb[MAX_ORDER];
+    for (int i = 0; i < na; ++i) sha[i] = a->shape[i];
+    for (int i = 0; i < nb; ++i) shb[i] = b->shape[i];
+    row_major_strides(na, sha, sta);
+    row_major_strides(nb, shb, stb);
+    ContractArgs g{};
+    g.nc = nc; g.ns = (int)S.size(); g.nout = (int)(M * N); g.k = (int)K;
+    for (int i = 0; i < nc; ++i) {
+      const int ia = find_lab(la, na, lc[i]);
+      g.cdim[i] = (int)cshape[i];
+      g.sa[i] = ia >= 0 ? (int)sta[ia] : 0;
+      g.sb[i] = ia >= 0 ? 0 : (int)stb[find_lab(lb, nb, lc[i])];
     }
+    for (size_t i = 0; i < S.size(); ++i) {
+      g.sdim[i] = (int)a->shape[S[i]];
+      g.ta[i] = (int)sta[S[i]];
+      g.tb[i] = (int)stb[Sb[i]];
+    }
+    TCI_CHECK_HIP(contract_small(dt, a->data, b->data, c->data, g, ctx->stream));
+    return TCI_OK;
   }
   const void* Ap = a->data;
   const void* Bp = b->data;

@@ -41,3 +41,28 @@ def test_moved_from_operand_is_refused(T, ctx, side):
     # the context goes on
     out = T.two_site_update_batched(ctx, ops[0][:1], ops[1][:1], None, p) if side else None
     assert out is None or out[3][0].chi == 4
+
+
+# up to 2^17 multiply-adds (one launch) and above, the result permuted and in its own order
+@pytest.mark.parametrize("la,lb,lc,dims", [("ab", "bc", "ca", dict(a=3, b=4, c=5000)),
+                                           ("ab", "bc", "ac", dict(a=3, b=4, c=5000)),
+                                           ("ab", "bc", "ac", dict(a=3, b=70, c=5000)),
+                                           ("ab", "bc", "ca", dict(a=3, b=70, c=5000))])
+def test_result_grows_over_an_operand(T, ctx, la, lb, lc, dims):
+    """The result's handle owns the memory that an operand wraps, and is too small: the operand is read first."""
+    a, b = (draw([dims[x] for x in lab], 5 + i) for i, lab in enumerate((la, lb)))
+    out, view, ptr = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_void_p()
+    src, tb = T.Tensor.from_numpy(ctx, a, T.C128), T.Tensor.from_numpy(ctx, b, T.C128)
+    L, shape = T.lib(), T._i64(a.shape)
+    T._check(L.tci_copy(ctx.h, src.h, ctypes.byref(out)), "tci_copy")
+    T._check(L.tci_data_ptr(ctx.h, out, ctypes.byref(ptr)), "tci_data_ptr")
+    T._check(L.tci_wrap(ctx.h, T.C128, 2, shape, ptr, ctypes.byref(view)), "tci_wrap")
+    T._check(L.tci_contract(ctx.h, view, T._i32([ord(x) for x in la]), 2, tb.h, T._i32([ord(x) for x in lb]), 2, out,
+                            T._i32([ord(x) for x in lc]), 2), "tci_contract")
+    ref = np.einsum(f"{la},{lb}->{lc}", a, b)
+    got = T.Tensor.empty(ctx, T.C128, ref.size)
+    T._check(L.tci_reshape(ctx.h, out, 2, T._i64(ref.shape), got.h), "tci_reshape")
+    # sums of at most 70 products of values of order one
+    assert np.abs(got.numpy() - ref).max() < 1e-13 * 70
+    for h in (view, out):
+        T._check(L.tci_destroy(ctx.h, h), "tci_destroy")
