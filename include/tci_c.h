@@ -482,7 +482,9 @@ typedef struct {
   const tci_tensor* prev_spectra; /* TCI_SVD_LEARNED: per update, the bond's spectrum before the
                                      update (F64 vector, descending); indexed like A / theta */
   const tci_tensor* lambda_left;  /* TCI_DIR_VIDAL: per update, the outer bond weights on the left
-                                     (F64 vector of chi_l entries, all > 0); indexed like A */
+                                     (F64 vector of chi_l entries, all > 0); indexed like A.  A
+                                     weight may share memory with an output: its values at the call
+                                     count */
   const tci_tensor* lambda_right; /* TCI_DIR_VIDAL: the same on the right (chi_r entries) */
 } tci_update_params;
 

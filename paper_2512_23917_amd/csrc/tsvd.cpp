@@ -400,7 +400,6 @@ static tci_status store_outputs(tci_context ctx, int dt, int wdt, int chil, int 
         TCI_CHECK_HIP(inv_scale_axis(dt, B_out[g]->data, chi * d * (long long)chir, 1, chir,
                                      static_cast<const double*>(p.lambda_right[g]->data), s));
       }
-    // last, since a weight of the Vidal form may be an output spectrum's tensor
     TCI_CHECK_HIP(copy_doubles_to_table(sn, o.kmax, ts, chi_d, kz, nt, s));
   }
   for (int i = 0; i < nb; ++i) {
@@ -439,14 +438,33 @@ static tci_status gather(tci_context ctx, int dt, const void* src, long long str
   return TCI_OK;
 }
 
+// Vidal weights that share memory with an output of the call, as a spectrum that
+// is updated in place does: their values at the call, kept on the host, since an
+// output may be resized or written before the last weight is read.
+struct VidalCopies {
+  std::vector<std::vector<double>> host;   // weight 2 i + side; empty: not shared
+  std::vector<tci_tensor_s> copies;        // the present chunk's, in the arena
+  std::vector<tci_tensor> of[2];
+};
+
 // Direction and Vidal weights of an update batch: lambda_left[i] / lambda_right[i]
 // F64 vectors of chil / chir finite positive entries (checked on the host).
-static tci_status check_direction(tci_context ctx, const tci_update_params& p, int nupd, int64_t chil,
-                                  int64_t chir) {
+static tci_status check_direction(tci_context ctx, const tci_update_params& p, int nupd, int64_t chil, int64_t chir,
+                                  const tci_tensor* A_out, const tci_tensor* s_out, const tci_tensor* B_out,
+                                  VidalCopies& vc) {
   if (p.direction != TCI_DIR_LEFT && p.direction != TCI_DIR_RIGHT && p.direction != TCI_DIR_VIDAL)
     TCI_RET(TCI_ERR_INVALID_ARGUMENT, "bad direction");
   if (p.direction != TCI_DIR_VIDAL) return TCI_OK;
   if (!p.lambda_left || !p.lambda_right) TCI_RET(TCI_ERR_INVALID_ARGUMENT, "TCI_DIR_VIDAL needs lambda_left/right");
+  std::vector<std::pair<const char*, const char*>> outs;   // the outputs' storage
+  for (const tci_tensor* o : {A_out, s_out, B_out})
+    for (int i = 0; i < nupd; ++i)
+      if (o[i]->data) {
+        const char* x = static_cast<const char*>(o[i]->data);
+        outs.emplace_back(x, x + o[i]->cap);
+      }
+  std::sort(outs.begin(), outs.end());
+  for (size_t k = 1; k < outs.size(); ++k) outs[k].second = std::max(outs[k].second, outs[k - 1].second);
   std::vector<double> h;
   for (int i = 0; i < nupd; ++i) {
     for (int side = 0; side < 2; ++side) {
@@ -460,8 +478,44 @@ static tci_status check_direction(tci_context ctx, const tci_update_params& p, i
       TCI_CHECK_HIP(hipStreamSynchronize(ctx->stream));
       for (double x : h)
         if (!(x > 0.0) || !std::isfinite(x)) TCI_RET(TCI_ERR_NUMERIC, "Vidal weights must be finite and positive");
+      // the last output that begins below the weight's end reaches beyond its start (running maximum of the ends)?
+      const char* x = static_cast<const char*>(l->data);
+      const auto it = std::lower_bound(outs.begin(), outs.end(), std::make_pair(x + sizeof(double) * want, (const char*)nullptr));
+      if (it != outs.begin() && std::prev(it)->second > x) {
+        vc.host.resize((size_t)2 * nupd);
+        vc.host[(size_t)2 * i + side] = h;
+      }
     }
   }
+  return TCI_OK;
+}
+
+// The parameters of the chunk of nb updates from c0: weights indexed like its
+// outputs, shared ones replaced by copies in the arena.
+static tci_status chunk_params(tci_context ctx, const tci_update_params& p, VidalCopies& vc, int c0, int nb,
+                               tci_update_params& pc) {
+  pc = p;
+  if (p.lambda_left) pc.lambda_left += c0;
+  if (p.lambda_right) pc.lambda_right += c0;
+  if (vc.host.empty()) return TCI_OK;
+  vc.copies.assign((size_t)2 * nb, tci_tensor_s());
+  for (int side = 0; side < 2; ++side) {
+    const tci_tensor* src = side ? pc.lambda_right : pc.lambda_left;
+    vc.of[side].assign(src, src + nb);
+    for (int i = 0; i < nb; ++i) {
+      const std::vector<double>& h = vc.host[(size_t)2 * (c0 + i) + side];
+      if (h.empty()) continue;
+      ARENA(dev, double, h.size());
+      TCI_CHECK_HIP(hipMemcpyAsync(dev, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, ctx->stream));
+      tci_tensor_s& t = vc.copies[(size_t)2 * i + side];
+      t = *src[i];
+      t.data = dev;
+      t.owns = false;
+      vc.of[side][i] = &t;
+    }
+  }
+  pc.lambda_left = vc.of[0].data();
+  pc.lambda_right = vc.of[1].data();
   return TCI_OK;
 }
 
@@ -1247,7 +1301,8 @@ tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tens
     }
   }
   if (gates && d != 2) TCI_RET(TCI_ERR_UNSUPPORTED, "gates are supported for d = 2");
-  TCI_TRY(check_direction(ctx, p, nupd, chil, chir));
+  VidalCopies vidal;
+  TCI_TRY(check_direction(ctx, p, nupd, chil, chir, A_out, s_out, B_out, vidal));
   const int prec = p.precision;
   if (is_double(dt) != (prec == TCI_PREC_FP64))
     TCI_RET(TCI_ERR_DTYPE, "FP64 precision needs F64/C128 tensors, mixed precisions F32/C64");
@@ -1340,9 +1395,8 @@ tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tens
       TCI_CHECK_HIP(convert(dt, th, wdt, tw, smn * nb, s));
       thw = tw;
     }
-    tci_update_params pc = p;  // Vidal weights indexed like the outputs of this chunk
-    if (pc.lambda_left) pc.lambda_left += c0;
-    if (pc.lambda_right) pc.lambda_right += c0;
+    tci_update_params pc;
+    TCI_TRY(chunk_params(ctx, p, vidal, c0, nb, pc));
     TCI_TRY(split_and_store(ctx, dt, wdt, nb, (int)chil, (int)d, (int)chir, th, thw, pc, c0, A_out + c0,
                             s_out + c0, B_out + c0, infos ? infos + c0 : nullptr));
     TCI_CHECK_HIP(hipStreamSynchronize(s));
@@ -1379,7 +1433,8 @@ tci_status tci_split_batched(tci_context ctx, int nupd, const tci_tensor* theta,
     for (int k = 0; k < 4; ++k)
       if (theta[i]->shape[k] != t0->shape[k]) TCI_RET(TCI_ERR_SHAPE, "all thetas of a batch must have one shape");
   }
-  TCI_TRY(check_direction(ctx, p, nupd, chil, chir));
+  VidalCopies vidal;
+  TCI_TRY(check_direction(ctx, p, nupd, chil, chir, A_out, s_out, B_out, vidal));
   Trace tr(ctx, "split_batched", std::to_string(nupd) + " x " + std::to_string(chil) + "," + std::to_string(chir));
   const int wdt = work_dtype(dt);
   const size_t es = elem_bytes(dt), wes = elem_bytes(wdt);
@@ -1398,9 +1453,8 @@ tci_status tci_split_batched(tci_context ctx, int nupd, const tci_tensor* theta,
       TCI_CHECK_HIP(convert(dt, tl, wdt, t64, smn * nb, s));
       tw = t64;
     }
-    tci_update_params pc = p;
-    if (pc.lambda_left) pc.lambda_left += c0;
-    if (pc.lambda_right) pc.lambda_right += c0;
+    tci_update_params pc;
+    TCI_TRY(chunk_params(ctx, p, vidal, c0, nb, pc));
     TCI_TRY(split_and_store(ctx, dt, wdt, nb, (int)chil, (int)d, (int)chir, tl, tw, pc, c0, A_out + c0, s_out + c0,
                             B_out + c0, infos ? infos + c0 : nullptr));
   }

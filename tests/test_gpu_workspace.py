@@ -1,6 +1,8 @@
 """Calls on workspace that holds NaN: memory of an allocator comes with the bits
 of its last use, and a result may depend on none of them.  0xFF bytes are a NaN
 in every floating type and -1 in every integer type."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -192,3 +194,36 @@ def test_calls_do_not_read_unwritten_workspace(T, name):
         assert x.shape == y.shape and np.isfinite(y).all()
         tol = 1e-11 if x.dtype.itemsize >= (16 if x.dtype.kind == "c" else 8) else 1e-5
         assert np.abs(x - y).max() <= tol * np.abs(x).max()
+
+
+# one launch of the write-back, more than one, several chunks
+@pytest.mark.parametrize("n,max_batch", [(3, 0), (70, 0), (5, 2)])
+def test_vidal_weights_that_are_output_spectra(T, poisoned, n, max_batch):
+    """Every spectrum handle is an outer weight of two other updates of the batch and has to grow: the same results
+    as with weights of their own."""
+    ctx, L = poisoned.refill(), T.lib()
+    a, b = draw((3, 2, 5), True, 1), draw((5, 2, 3), True, 2)
+    lam = [np.sort(draw((3,), False, 10 + i) ** 2 + 0.1)[::-1].copy() for i in range(n)]
+    A, B = ([T.Tensor.from_numpy(ctx, x * (1 + i), T.C128) for i in range(n)] for x in (a, b))
+    wrapped = [T.Tensor.from_numpy(ctx, x, T.F64) for x in lam]
+    p = T.update_params(chi_min=1, chi_max=6, direction=T.DIR_VIDAL, max_batch=max_batch)
+    left, right = [(i + 1) % n for i in range(n)], [(i + 2) % n for i in range(n)]
+    want = T.two_site_update_batched(ctx, A, B, None, p, lambda_left=[wrapped[i] for i in left],
+                                     lambda_right=[wrapped[i] for i in right])
+    P = ctypes.c_void_p * n
+    own = [ctypes.c_void_p() for _ in range(n)]
+    for h, w in zip(own, wrapped):
+        T._check(L.tci_copy(ctx.h, w.h, ctypes.byref(h)), "tci_copy")
+    Ao, Bo = ([T.Tensor.empty(ctx, T.C128, 36) for _ in range(n)] for _ in range(2))
+    infos = (T.UpdateInfo * n)()
+    for field, at in (("lambda_left", left), ("lambda_right", right)):
+        setattr(p, field, ctypes.cast(P(*[own[i].value for i in at]), ctypes.POINTER(ctypes.c_void_p)))
+    T._check(L.tci_two_site_update_batched(ctx.h, n, P(*[x.h.value for x in A]), P(*[x.h.value for x in B]), None,
+                                           ctypes.byref(p), P(*[x.h.value for x in Ao]), P(*[h.value for h in own]),
+                                           P(*[x.h.value for x in Bo]), infos), "tci_two_site_update_batched")
+    for i in range(n):
+        s = T.Tensor.empty(ctx, T.F64, 6)
+        T._check(L.tci_reshape(ctx.h, own[i], 1, T._i64([infos[i].chi]), s.h), "tci_reshape")
+        for x, y in ((Ao[i], want[0][i]), (s, want[1][i]), (Bo[i], want[2][i])):
+            assert np.array_equal(x.numpy(), y.numpy())
+        T._check(L.tci_destroy(ctx.h, own[i]), "tci_destroy")
