@@ -177,8 +177,15 @@ __device__ cd inverse_trace(const T* a, int n, double* sh) {
   for (int i = threadIdx.x; i < n; i += 256) acc_add<T>(r, im, a[(long long)i * n + i]);
   r = block_sum(r, sh);
   im = block_sum(im, sh);
-  const double m2 = r * r + im * im;
-  return im == 0.0 ? cd{1.0 / r, 0.0} : cd{r / m2, -im / m2};
+  // by Smith's division, which forms no square: the modulus squared leaves the
+  // exponent range from 1e154 on, and below 1e-154
+  if (im == 0.0) return cd{1.0 / r, 0.0};
+  if (fabs(r) >= fabs(im)) {
+    const double t = im / r, d = r + im * t;
+    return cd{1.0 / d, -t / d};
+  }
+  const double t = r / im, d = im + r * t;
+  return cd{t / d, -1.0 / d};
 }
 
 __device__ inline cd widen(double v) { return cd{v, 0.0}; }

@@ -194,6 +194,17 @@ def test_normalize_trace(T, ctx, n, dt):
         T.normalize_trace(ctx, T.Tensor.from_numpy(ctx, np.zeros((2, 3)), T.F64))
 
 
+@pytest.mark.parametrize("n", [3, 100])
+@pytest.mark.parametrize("scale", [1e-300, 1e-160, 1e160, 1e300, 1e-200j, -1e200j, 1e180 * (1 - 1e-9j)])
+def test_normalize_trace_far_from_one(T, ctx, n, scale):
+    """Traces whose squared modulus leaves the exponent range, real and imaginary parts of either size."""
+    a = draw((n, n), True, n) + np.eye(n) * 4
+    t = T.normalize_trace(ctx, T.Tensor.from_numpy(ctx, a * scale, T.C128))
+    ref = a / np.trace(a)
+    # the trace to about n u of the sum of moduli, four roundings of the division, the product and the scaling
+    assert np.abs(t.numpy() - ref).max() <= (n + 16) * U64 * np.abs(ref).max() * np.sqrt(n)
+
+
 # 64 tensors per launch; complex64 factors with an odd element count (8-byte copies); an update without a gate
 @pytest.mark.parametrize("batch,dt", [(1, "C64"), (63, "F32"), (65, "C64"), (130, "F64")])
 def test_update_batches_beyond_one_table(T, ctx, batch, dt):
