@@ -55,6 +55,22 @@ def test_jacobi_svd_far_from_one(T, ctx, scale):
     assert isometry_err(u.numpy()) < 1e-13
 
 
+@pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("n", [24, 32, 60])
+def test_jacobi_svd_keeps_norms(T, ctx, n, complex_):
+    """The rows of V^H come from about 10 n rotations each.  A rotation's c^2 + s^2 is off by 0.6 to 0.85 u rms, of
+    either sign, which is 0.45 u in the norm and 0.6 u with the modulus of a complex phase: so many u times sqrt(10 n)
+    rms over the rows, and a few u on average.  A phase that is short by an ulp in a third of the rotations, or a
+    cosine that is long by as much, adds up to n / 2 u."""
+    norms = []
+    for i in range(8):
+        a = draw((n, n), complex_, 100 * n + i)
+        vh = T.svd(ctx, T.Tensor.from_numpy(ctx, a, T.C128 if complex_ else T.F64), 1)[2].numpy()
+        norms.append(np.sqrt((np.abs(vh.astype(np.clongdouble)) ** 2).sum(axis=1)) - 1)
+    assert abs(np.mean(norms)) < 6 * U64 * np.sqrt(n / 24)
+    assert np.sqrt(np.mean(np.square(norms))) < (0.6 if complex_ else 0.45) * U64 * np.sqrt(10 * n)
+
+
 # 64, 128, 192 (complex and real), 256 and 320 (real): row blocks held on chip; 321 .. 384 (193 .. 384 complex): first
 # columns from global memory, the rest on chip; 385 and up: panels, the rest on chip
 @pytest.mark.parametrize("complex_,n", [(True, n) for n in (1, 2, 3, 16, 17, 33, 64, 65, 128, 129, 192, 193, 290, 384,
