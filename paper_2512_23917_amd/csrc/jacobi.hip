@@ -102,20 +102,39 @@ __device__ inline double cos_of_tan(double t) {
   return __builtin_fma(y * 0.5, __builtin_fma(-p, p, __builtin_fma(-y, y, 1.0)), y);
 }
 
-// Modulus of z, its reciprocal and the conjugate of its phase (0, 0 and no phase
-// for z = 0).  A real phase is exactly +-1: as z / |z| by a reciprocal it is below
+// Modulus of z != 0, its reciprocal and the conjugate of its phase.  A real phase is exactly +-1: as z / |z| by a reciprocal it is below
 // one by an ulp now and then, and hundreds of rotations shrink the columns.
+// TINY: z may be 0 (then so are |z| and its reciprocal), and the square or the
+// reciprocal of |z| outside the exponent range.
+template <bool TINY>
 __device__ inline void modulus(double z, double& r, double& ir, double& phc) {
   r = fabs(z);
-  ir = r > 0.0 ? 1.0 / r : 0.0;
+  if constexpr (TINY) ir = r > 0.0 ? 1.0 / r : 0.0;
+  else ir = rcp_nr(r);
   phc = copysign(1.0, z);
 }
+template <bool TINY>
 __device__ inline void modulus(cd z, double& r, double& ir, cd& phc) {
+  int ex = 0;
+  if constexpr (TINY) {   // of z scaled to order one
+    const double a = fmax(fabs(z.x), fabs(z.y));
+    ex = a > 0.0 ? __builtin_amdgcn_frexp_exp(a) : 0;
+    z = cd{__builtin_amdgcn_ldexp(z.x, -ex), __builtin_amdgcn_ldexp(z.y, -ex)};
+  }
   const double r2 = z.x * z.x + z.y * z.y;
-  ir = r2 > 0.0 ? rsqrt_nr(r2) : 0.0;
-  r = r2 * ir;
+  ir = !TINY || r2 > 0.0 ? rsqrt_nr(r2) : 0.0;
   phc = cd{z.x * ir, -z.y * ir};
+  r = r2 * ir;
+  if constexpr (TINY) {
+    r = __builtin_amdgcn_ldexp(r, ex);
+    ir = __builtin_amdgcn_ldexp(ir, -ex);
+  }
 }
+
+__device__ inline double amax_of(double v) { return fabs(v); }
+__device__ inline double amax_of(cd v) { return fmax(fabs(v.x), fabs(v.y)); }
+__device__ inline double ldexp_of(double v, int e) { return __builtin_amdgcn_ldexp(v, e); }
+__device__ inline cd ldexp_of(cd v, int e) { return cd{__builtin_amdgcn_ldexp(v.x, e), __builtin_amdgcn_ldexp(v.y, e)}; }
 
 // unit-modulus phase of z (1 for z = 0) and its modulus
 __device__ inline void polar(double z, double& r, double& ph) {
@@ -187,41 +206,51 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
   T* W;
   if constexpr (W_LDS) W = reinterpret_cast<T*>(smem) + n * n;
   else W = Wk + b * sW;
-  __shared__ int rotated;
+  __shared__ int rotated, some_tiny;
   __shared__ double sig[JACOBI_MAX_K];   // squared column norms; at the end the singular values
   __shared__ int rank_of[JACOBI_MAX_K];
   using Idx = std::conditional_t<W_LDS, int, long long>;
   // load and V = I
+  __shared__ double s_max[NT / 64];
+  double am = 0.0;
   if (wide) {
     for (Idx e = tid; e < (Idx)m * n; e += NT) {
       const int j = (int)(e / m), i = (int)(e % m);
-      W[e] = cj(Ab[(long long)j * lda + i]);
+      const T v = cj(Ab[(long long)j * lda + i]);
+      am = fmax(am, amax_of(v));
+      W[e] = v;
     }
   } else {
     for (Idx e = tid; e < (Idx)m * n; e += NT) {   // consecutive threads along a row of A
       const int i = (int)(e / n), j = (int)(e % n);
-      W[(Idx)j * m + i] = Ab[(long long)i * lda + j];
+      const T v = Ab[(long long)i * lda + j];
+      am = fmax(am, amax_of(v));
+      W[(Idx)j * m + i] = v;
     }
   }
   for (int e = tid; e < n * n; e += NT) V[e] = (e / n == e % n) ? one_of(T{}) : zero_of(T{});
+  for (int off = 32; off > 0; off >>= 1) am = fmax(am, __shfl_xor(am, off, 64));
+  if (lane == 0) s_max[wv] = am;
+  if (tid == 0) some_tiny = 0;
   __syncthreads();
+  // A matrix whose largest entry is beyond 2^+-100 is scaled by a power of two
+  // (exact), so that squared inner products of its columns stay in range.
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) am = fmax(am, s_max[k]);
+  const int ae = am > 0.0 && am < INFINITY ? __builtin_amdgcn_frexp_exp(am) : 0;
+  const int ex = ae > 100 || ae < -100 ? ae : 0;
+  if (ex != 0) {
+    for (Idx e = tid; e < (Idx)m * n; e += NT) W[e] = ldexp_of(W[e], -ex);
+    __syncthreads();
+  }
   const int N = n + (n & 1);            // even player count (column n is a bye when n is odd)
   const double tol = (double)m * 0x1p-53;
   int sweep = 0;
   bool conv = (n < 2);
-  for (; !conv && sweep < max_sweeps; ++sweep) {
-    // squared norms afresh in every sweep; within it the rotations carry them
-    // along (|w_p|^2 - t |g|, |w_q|^2 + t |g|).  Their rounding can only spoil an
-    // angle or postpone a rotation: the sweep that ends the iteration rotated
-    // nothing and used the fresh norms.
-    if (tid == 0) rotated = 0;
-    for (int j = slot; j < n; j += NT / 16) {
-      double nn = 0.0;
-      for (int i = sub; i < m; i += 16) nn += sq(W[(Idx)j * m + i]);
-      nn = row_sum(nn);
-      if (sub == 0) sig[j] = nn;
-    }
-    __syncthreads();
+  // the steps of one sweep; TINY: with the scaled forms (a copy of the loop, as
+  // the few instructions more would cost a step 3% of its time)
+  auto steps = [&](auto tiny) __attribute__((always_inline)) {
+    constexpr bool TINY = decltype(tiny)::value;
     // players of this slot: position 0 is fixed, the others advance by one per step
     int t1 = slot == 0 ? 0 : slot, t2 = N - 1 - slot;
     for (int r = 0; r < N - 1; ++r) {
@@ -245,14 +274,22 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
           for (int i = sub; i < m; i += 16) ga = addv(ga, mulr(cj(wp[i]), wq[i]));
         }
         ga = row_sum(ga);
+        // |g| > tol |w_p| |w_q|, squared where nothing can underflow
+        bool rot = al > 0.0 && be > 0.0;
         double ag, ig;
         T phc;
-        modulus(ga, ag, ig, phc);
-        const bool rot = al > 0.0 && be > 0.0 && ag > tol * (al * rsqrt_nr(al)) * (be * rsqrt_nr(be));
+        if constexpr (TINY) {
+          modulus<true>(ga, ag, ig, phc);
+          rot = rot && ag > tol * (al * rsqrt_nr(al)) * (be * rsqrt_nr(be));
+        } else {
+          rot = rot && sq(ga) > (tol * al) * (tol * be);
+        }
         if (rot) {
+          if constexpr (!TINY) modulus<false>(ga, ag, ig, phc);
           // rotate [w_p, w_q e^{-i phi}] by the real Jacobi rotation of
           // [[al, |g|], [|g|, be]]
-          const double zeta = (be - al) * (0.5 * ig);
+          double zeta = (be - al) * (0.5 * ig);
+          if (TINY && ag < 0x1p-1000) zeta = (be - al) / (2.0 * ag);   // ig may be Inf
           const double az = fabs(zeta);
           double t;
           if (az < 0x1p500) {
@@ -299,6 +336,26 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
       t2 = t2 == N - 1 ? 1 : t2 + 1;
       __syncthreads();
     }
+  };
+  for (; !conv && sweep < max_sweeps; ++sweep) {
+    // squared norms afresh in every sweep; within it the rotations carry them
+    // along (|w_p|^2 - t |g|, |w_q|^2 + t |g|).  Their rounding can only spoil an
+    // angle or postpone a rotation: the sweep that ends the iteration rotated
+    // nothing and used the fresh norms.
+    if (tid == 0) rotated = 0;
+    for (int j = slot; j < n; j += NT / 16) {
+      double nn = 0.0;
+      for (int i = sub; i < m; i += 16) nn += sq(W[(Idx)j * m + i]);
+      nn = row_sum(nn);
+      if (sub == 0) {
+        sig[j] = nn;
+        if (nn > 0.0 && nn < 0x1p-440) some_tiny = 1;
+      }
+    }
+    __syncthreads();
+    // without such columns every |g| to rotate is above tol 2^-440
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(some_tiny) == 0, 1)) steps(std::false_type{});
+    else steps(std::true_type{});
     conv = (rotated == 0);
     __syncthreads();
   }
@@ -316,7 +373,7 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
     const double sj = sig[tid];
     for (int i = 0; i < n; ++i) rk += (sig[i] > sj) || (sig[i] == sj && i < tid);
     rank_of[tid] = rk;
-    s[b * ss + rk] = sj;
+    s[b * ss + rk] = __builtin_amdgcn_ldexp(sj, ex);
   }
   __syncthreads();
   T* ub = u + b * su;

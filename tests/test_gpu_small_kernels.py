@@ -56,6 +56,24 @@ def test_jacobi_svd_far_from_one(T, ctx, scale):
 
 
 @pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("scale,grade", [(1e-150, 1.0), (1e-80, 1.0), (1e80, 1.0), (1e150, 1.0), (1.0, 1e-140),
+                                         (1e-60, 1e-90), (1e60, 1e-130)])
+@pytest.mark.parametrize("m,n", [(20, 12), (70, 33), (12, 900)])
+def test_jacobi_svd_exponent_range(T, ctx, m, n, scale, grade, complex_):
+    """Inner products of columns, or their squares, beyond either end of the exponent range; half of the columns
+    smaller by `grade`, whose inner products are far below the others'.  As near 1, since powers of two are exact."""
+    a = draw((m, n), complex_, 5) * scale
+    k = min(m, n)
+    np.moveaxis(a, int(m >= n), 0)[k // 2:k] *= grade
+    u, s, vh = T.svd(ctx, T.Tensor.from_numpy(ctx, a, T.C128 if complex_ else T.F64), 1)
+    u, s, vh = u.numpy(), s.numpy(), vh.numpy()
+    tol = 1e-13 + 4 * max(m, n) * U64
+    assert np.abs(s / scale - np.linalg.svd(a / scale, compute_uv=False)).max() < tol * s[0] / scale
+    assert np.linalg.norm((u * (s / scale)) @ vh - a / scale) < tol * s[0] / scale * np.sqrt(k)
+    assert isometry_err(u) < tol and isometry_err(vh, False) < tol
+
+
+@pytest.mark.parametrize("complex_", [False, True])
 @pytest.mark.parametrize("n", [24, 32, 60])
 def test_jacobi_svd_keeps_norms(T, ctx, n, complex_):
     """The rows of V^H come from about 10 n rotations each.  A rotation's c^2 + s^2 is off by 0.6 to 0.85 u rms, of
