@@ -11,20 +11,19 @@
 // truncation of message products and of tiny bonds decides on.
 //
 // One workgroup per problem, 16 lanes per column pair (a DPP row, so that the
-// three inner products of a pair are summed without LDS round trips).  Pairs
-// are scheduled by the round-robin (circle) ordering: n/2 disjoint pairs per
-// step, n - 1 steps per sweep, a workgroup barrier between steps; a step has
-// at most 32 pairs, so 256 threads (n <= 32) or 512 threads process all of
-// them at once.  V and, when it fits, W live in LDS.  A step is a chain of
-// latencies (LDS read, reduction, rotation scalars, LDS write, barrier), so
-// the scalars come from reciprocal-square-root seeds refined by two Newton
-// steps instead of the division and square-root sequences, the column norms
-// are carried along within a sweep, and up to 64 rows a lane holds its elements
-// in registers from the inner product to the rotation.  One complex problem
-// takes 330 us at 32 x 32 (1.1 us per step) and 1519 us at 64 x 64 (a step
-// moves up to 192 KiB of LDS); with the norms summed in every step 367 and 1788
-// us; four waves that took the pairs in turn from global memory, a wave per
-// pair, 2218 and 11220 us.
+// inner product of a pair is summed without LDS round trips), or a wave per pair
+// for a few long columns.  Pairs are scheduled by the round-robin (circle)
+// ordering: n/2 disjoint pairs per step, n - 1 steps per sweep, a workgroup
+// barrier between steps; a step has at most 32 pairs, and the workgroup processes
+// all of them at once.  V and, when it fits, W live in LDS.  A step is a chain of
+// latencies (LDS read, reduction, rotation scalars, LDS write, barrier), so the
+// scalars come from reciprocal-square-root seeds refined by two Newton steps
+// instead of the division and square-root sequences, the column norms are carried
+// along within a sweep, and up to 64 rows a lane holds its elements in registers
+// from the inner product to the rotation.  A call on one complex problem takes 383
+// us at 32 x 32 (about 1 us per step) and 1131 us at 64 x 64 (a step moves up to
+// 192 KiB of LDS); four waves that took the pairs in turn from global memory, a
+// wave per pair, 1943 and 8174 us.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -75,6 +74,19 @@ __device__ inline double row_sum(double v) {
   return dpp_add<0x140>(v); // row_mirror
 }
 __device__ inline cd row_sum(cd v) { return cd{row_sum(v.x), row_sum(v.y)}; }
+
+__device__ inline double shfl_add(double v, int m) { return v + __shfl_xor(v, m, 64); }
+__device__ inline cd shfl_add(cd v, int m) { return cd{shfl_add(v.x, m), shfl_add(v.y, m)}; }
+// over the LP lanes of a column pair
+template <int LP, typename T>
+__device__ inline T pair_sum(T v) {
+  v = row_sum(v);
+  if constexpr (LP == 64) {
+    v = shfl_add(v, 16);
+    v = shfl_add(v, 32);
+  }
+  return v;
+}
 
 // 1 / sqrt(x) and 1 / x for positive finite x: hardware seed, two Newton steps
 __device__ inline double rsqrt_nr(double x) {
@@ -182,7 +194,7 @@ __device__ void complete_vector(T* P, long long vs, long long is, int len, int r
 // A: problem b at A + b*sA, row-major with leading dimension lda.
 // wide == 0: the matrix is A itself (m x n, m >= n).  wide == 1: the matrix
 // is the conjugate transpose of A, A being n x m (so again m x n, m >= n).
-// W: m x n column-major, Vw: n x n column-major (workspace per problem).
+// W: m x n column-major, V: n x n column-major.
 // Outputs of the SVD of the ORIGINAL A (rows x cols, k = n):
 //   wide == 0: u (m x k) = W_j / s_j,       vh (k x n) = V^H
 //   wide == 1: u (n x k) = V,               vh (k x m) = (W_j / s_j)^H
@@ -191,8 +203,9 @@ __device__ void complete_vector(T* P, long long vs, long long is, int len, int r
 // phase.  sweeps[b] receives the sweep count (-1 if not converged).
 // LDS: bytes of shared memory; W_LDS: W fits there beside V (otherwise W is
 // the global workspace Wk).  MI > 0: m <= 16 MI, and a lane keeps its elements
-// of both columns in registers between the inner product and the rotation.
-template <typename T, int NT, int LDS, bool W_LDS, int MI>
+// of both columns in registers between the inner product and the rotation.  LP:
+// lanes per column pair.
+template <typename T, int NT, int LDS, bool W_LDS, int MI, int LP>
 __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long lda, long long sA, int m, int n,
                                                         int wide, T* Wk, long long sW, T* u, long long su, T* vh,
                                                         long long svh, double* s, long long ss, int* sweeps,
@@ -200,7 +213,8 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
   __shared__ __align__(16) char smem[LDS];
   const int b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int sub = tid & 15, slot = tid >> 4;   // lane of the pair, pair of the step
+  const int sub = tid % LP, slot = tid / LP;   // lane of the pair, pair of the step
+  static_assert(LP == 16 || (LP == 64 && MI == 0), "a DPP row or a wave per pair");
   const T* Ab = A + b * sA;
   T* V = reinterpret_cast<T*>(smem);
   T* W;
@@ -210,6 +224,7 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
   __shared__ double sig[JACOBI_MAX_K];   // squared column norms; at the end the singular values
   __shared__ int rank_of[JACOBI_MAX_K];
   using Idx = std::conditional_t<W_LDS, int, long long>;
+  constexpr int UB = LP == 16 ? 2 : 4;   // elements of a column in flight per lane where they are not kept
   // load and V = I
   __shared__ double s_max[NT / 64];
   double am = 0.0;
@@ -271,9 +286,20 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
 #pragma unroll
           for (int k = 0; k < MI; ++k) ga = addv(ga, mulr(cj(x[k]), y[k]));
         } else {
-          for (int i = sub; i < m; i += 16) ga = addv(ga, mulr(cj(wp[i]), wq[i]));
+          for (int i0 = sub; i0 < m; i0 += UB * LP) {
+            T u0[UB], u1[UB];
+#pragma unroll
+            for (int k = 0; k < UB; ++k) {
+              const int i = min(i0 + k * LP, m - 1);
+              u0[k] = wp[i];
+              u1[k] = wq[i];
+            }
+#pragma unroll
+            for (int k = 0; k < UB; ++k)
+              if (i0 + k * LP < m) ga = addv(ga, mulr(cj(u0[k]), u1[k]));
+          }
         }
-        ga = row_sum(ga);
+        ga = pair_sum<LP>(ga);
         // |g| > tol |w_p| |w_q|, squared where nothing can underflow
         bool rot = al > 0.0 && be > 0.0;
         double ag, ig;
@@ -311,16 +337,29 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
               }
             }
           } else {
-            for (int i = sub; i < m; i += 16) {
-              const T u0 = wp[i], z = mulr(wq[i], phc);
-              wp[i] = addv(scl(c, u0), scl(-sn, z));
-              wq[i] = addv(scl(sn, u0), scl(c, z));
+            for (int i0 = sub; i0 < m; i0 += UB * LP) {
+              T u0[UB], u1[UB];
+#pragma unroll
+              for (int k = 0; k < UB; ++k) {
+                const int i = min(i0 + k * LP, m - 1);
+                u0[k] = wp[i];
+                u1[k] = wq[i];
+              }
+#pragma unroll
+              for (int k = 0; k < UB; ++k) {
+                const int i = i0 + k * LP;
+                const T z = mulr(u1[k], phc);
+                if (i < m) {
+                  wp[i] = addv(scl(c, u0[k]), scl(-sn, z));
+                  wq[i] = addv(scl(sn, u0[k]), scl(c, z));
+                }
+              }
             }
           }
           T* vp = V + p * n;
           T* vq = V + q * n;
 #pragma unroll 4
-          for (int i = sub; i < n; i += 16) {
+          for (int i = sub; i < n; i += LP) {
             const T u0 = vp[i], z = mulr(vq[i], phc);
             vp[i] = addv(scl(c, u0), scl(-sn, z));
             vq[i] = addv(scl(sn, u0), scl(c, z));
@@ -343,10 +382,11 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
     // angle or postpone a rotation: the sweep that ends the iteration rotated
     // nothing and used the fresh norms.
     if (tid == 0) rotated = 0;
-    for (int j = slot; j < n; j += NT / 16) {
+    for (int j = slot; j < n; j += NT / LP) {
       double nn = 0.0;
-      for (int i = sub; i < m; i += 16) nn += sq(W[(Idx)j * m + i]);
-      nn = row_sum(nn);
+#pragma unroll 4
+      for (int i = sub; i < m; i += LP) nn += sq(W[(Idx)j * m + i]);
+      nn = pair_sum<LP>(nn);
       if (sub == 0) {
         sig[j] = nn;
         if (nn > 0.0 && nn < 0x1p-440) some_tiny = 1;
@@ -445,20 +485,41 @@ size_t jacobi_work_elems(int m, int n) { return (size_t)m * n; }
 // when W stays in global memory).
 static constexpr int JACOBI_LDS_SMALL = 2 * 32 * 32 * 16, JACOBI_LDS = 9 * 64 * 64 * 4;
 
-template <typename T, int NT>
+// Lanes per pair: 16, so that a step has all pairs of up to 64 columns in at most
+// 512 threads; a wave for matrices of few columns and many rows, where 16 lanes
+// would walk long columns with most of the workgroup idle: 2048 x 8 complex 0.51 ms
+// (1.75 with 16 lanes), 20000 x 24 34 ms (131), 300 x 32 1.4 ms (1.7).  Up to about
+// six rows per column 16 lanes are faster (128 x 32: 0.62 and 0.67 ms), and above 32
+// columns they fill the workgroup.
+template <typename T>
 static void jacobi_launch(const T* A, long long lda, long long sA, int m, int n, int wide, T* W, T* u, long long su,
                           T* vh, long long svh, double* s, long long ss, int* sweeps, int batch, hipStream_t st) {
   const size_t need = sizeof(T) * ((size_t)m * n + (size_t)n * n);
+  const bool w_lds = need <= (size_t)JACOBI_LDS;
+  constexpr int V32 = 32 * 32 * (int)sizeof(T), V64 = 64 * 64 * (int)sizeof(T);
   const int max_sweeps = 80;
   const long long sW = (long long)m * n;
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(batch), dim3(NT), 0, st, A, lda, sA, m, n, wide, W, sW, u, su, vh, svh, s, ss,
+  auto go = [&](auto kernel, int nt) {
+    hipLaunchKernelGGL(kernel, dim3(batch), dim3(nt), 0, st, A, lda, sA, m, n, wide, W, sW, u, su, vh, svh, s, ss,
                        sweeps, max_sweeps);
   };
-  if (need <= (size_t)JACOBI_LDS_SMALL && m <= 32) go(jacobi_svd_kernel<T, NT, JACOBI_LDS_SMALL, true, 2>);
-  else if (need <= (size_t)JACOBI_LDS && m <= 64) go(jacobi_svd_kernel<T, NT, JACOBI_LDS, true, 4>);
-  else if (need <= (size_t)JACOBI_LDS) go(jacobi_svd_kernel<T, NT, JACOBI_LDS, true, 0>);
-  else go(jacobi_svd_kernel<T, NT, 64 * 64 * (int)sizeof(T), false, 0>);
+  if (n <= 32 && m <= 32) {
+    go(jacobi_svd_kernel<T, 256, JACOBI_LDS_SMALL, true, 2, 16>, 256);
+  } else if (m <= 64) {
+    if (n <= 32) go(jacobi_svd_kernel<T, 256, JACOBI_LDS, true, 4, 16>, 256);
+    else go(jacobi_svd_kernel<T, 512, JACOBI_LDS, true, 4, 16>, 512);
+  } else if (n <= 8) {
+    if (w_lds) go(jacobi_svd_kernel<T, 256, JACOBI_LDS, true, 0, 64>, 256);
+    else go(jacobi_svd_kernel<T, 256, V32, false, 0, 64>, 256);
+  } else if (n <= 32 && m < 6 * n) {   // at most 192 x 32: W is in LDS
+    go(jacobi_svd_kernel<T, 256, JACOBI_LDS, true, 0, 16>, 256);
+  } else if (n <= 32) {
+    if (w_lds) go(jacobi_svd_kernel<T, 1024, JACOBI_LDS, true, 0, 64>, 1024);
+    else go(jacobi_svd_kernel<T, 1024, V32, false, 0, 64>, 1024);
+  } else {
+    if (w_lds) go(jacobi_svd_kernel<T, 512, JACOBI_LDS, true, 0, 16>, 512);
+    else go(jacobi_svd_kernel<T, 512, V64, false, 0, 16>, 512);
+  }
 }
 
 hipError_t jacobi_svd(int dtype, const void* A, long long lda, long long sA, int rows, int cols, void* work,
@@ -470,12 +531,7 @@ hipError_t jacobi_svd(int dtype, const void* A, long long lda, long long sA, int
   if (n > JACOBI_MAX_K || n < 1) return hipErrorInvalidValue;
   auto run = [&](auto tag) {
     using T = decltype(tag);
-    if (n <= 32)
-      jacobi_launch<T, 256>((const T*)A, lda, sA, m, n, wide, (T*)work, (T*)u, su, (T*)vh, svh, s, ss, sweeps, batch,
-                            st);
-    else
-      jacobi_launch<T, 512>((const T*)A, lda, sA, m, n, wide, (T*)work, (T*)u, su, (T*)vh, svh, s, ss, sweeps, batch,
-                            st);
+    jacobi_launch<T>((const T*)A, lda, sA, m, n, wide, (T*)work, (T*)u, su, (T*)vh, svh, s, ss, sweeps, batch, st);
   };
   if (dtype == C128) run(cd{});
   else if (dtype == F64) run(double{});

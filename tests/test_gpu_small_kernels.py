@@ -46,6 +46,17 @@ def test_jacobi_svd_edges(T, ctx, complex_, m, n):
     assert isometry_err(u) < tol and isometry_err(vh, False) < tol
 
 
+# more than 64 rows: a wave per pair for up to 8 columns or from 6 rows per column on (up to 32 columns), 16 lanes
+# else; 192 x 32 and 191 x 32: either side of the line; 4 and 5 x 256 rows: whole and partial batches of a lane's
+# elements; 1100 x 8 and 1200 x 8 (complex): W in LDS and in global memory
+@pytest.mark.parametrize("complex_,m,n", [(True, 65, 1), (True, 65, 2), (False, 70, 8), (True, 9, 80), (True, 191, 32),
+                                          (True, 192, 32), (False, 97, 16), (False, 95, 16), (True, 1024, 3),
+                                          (True, 1025, 7), (True, 1100, 8), (True, 1200, 8), (False, 31, 2100),
+                                          (True, 33, 400), (True, 5000, 17)])
+def test_jacobi_svd_long_columns(T, ctx, complex_, m, n):
+    test_jacobi_svd_edges(T, ctx, complex_, m, n)
+
+
 @pytest.mark.parametrize("scale", [1e-100, 1e100])
 def test_jacobi_svd_far_from_one(T, ctx, scale):
     """Real matrices whose squared inner products leave the exponent range."""
