@@ -422,7 +422,8 @@ tci_status tci_lq(tci_context ctx, tci_tensor a, int k_rows, tci_tensor l, tci_t
 
 /* Spec, eigh: the tensor matricised with its first k_rows bonds as rows
  * (1 <= k_rows < order; I = prod d_0..d_{k-1} must equal J = prod d_k..) is
- * read as a Hermitian matrix (as given, no symmetrisation)
+ * read as a Hermitian matrix, by its lower triangle (entries with row >=
+ * column, a real diagonal; what stands above the diagonal is not used)
  * -> w (I eigenvalues ascending, real: F64 for F64/C128, F32 for F32/C64)
  * and v {d_0, .., d_{k-1}, I} in a's dtype whose last bond indexes the
  * eigenvectors (gauge as in tci_svd).  Single-precision inputs are solved in

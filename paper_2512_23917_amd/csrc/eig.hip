@@ -835,6 +835,25 @@ static void tri_chip(const TriArgs& a, int i0, int batch, hipStream_t s) {
   else go(tri_chip_kernel<T, 10, 3>);
 }
 
+// One workgroup per diagonal tile.
+template <typename T>
+__global__ __launch_bounds__(256) void mirror_tiles_kernel(T* G, long long ldg, int n) {
+  const int t0 = blockIdx.x * TT;
+  for (int e = threadIdx.x; e < TT * TT; e += 256) {
+    const int r = t0 + e / TT, c = t0 + e % TT;
+    if (c > r && c < n) G[r * ldg + c] = cj(G[c * ldg + r]);
+  }
+}
+
+hipError_t tridiag_mirror_tiles(int dtype, void* G, long long ldg, int n, hipStream_t s) {
+  if (n <= (dtype == C128 ? TRI_CHIP_N<cd> : TRI_CHIP_N<double>)) return hipSuccess;   // read by its lower triangle
+  const dim3 grid((n + TT - 1) / TT);
+  if (dtype == C128) hipLaunchKernelGGL(mirror_tiles_kernel<cd>, grid, dim3(256), 0, s, (cd*)G, ldg, n);
+  else if (dtype == F64) hipLaunchKernelGGL(mirror_tiles_kernel<double>, grid, dim3(256), 0, s, (double*)G, ldg, n);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 size_t tridiag_ws_bytes(int dtype, int n) {
   return dtype == C128 ? TriWs<cd, TRIDIAG_NB>::bytes(n) : TriWs<double, TRIDIAG_NB>::bytes(n);
 }

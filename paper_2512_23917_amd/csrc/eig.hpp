@@ -29,6 +29,9 @@ struct TriArgs {
 // Bytes of the per-problem workspace of the reduction (zero-fill before use).
 size_t tridiag_ws_bytes(int dtype, int n);
 
+// Fills the entries above the diagonal that tridiagonalize reads of a matrix
+// given by its lower triangle (those of the diagonal tiles).
+hipError_t tridiag_mirror_tiles(int dtype, void* G, long long ldg, int n, hipStream_t s);
 // G = Q T Q^H (dtype C128 or F64).
 hipError_t tridiagonalize(int dtype, const TriArgs& a, int batch, hipStream_t s);
 // lam[b][j], j < kmax: the j-th largest eigenvalue of tridiag(d, e), stored with

@@ -1106,6 +1106,7 @@ static tci_status eigh_core(tci_context ctx, tci_tensor a, int k_rows, tci_tenso
   hipStream_t s = ctx->stream;
   ARENA(G, char, es * (size_t)n * n);
   TCI_CHECK_HIP(hipMemcpyAsync(G, src, es * (size_t)n * n, hipMemcpyDeviceToDevice, s));
+  TCI_CHECK_HIP(tridiag_mirror_tiles(dt, G, n, n, s));   // the lower triangle counts, whatever the order
   ARENA(d, double, n);
   ARENA(e, double, n);
   ARENA(e2, double, tridiag_e2_elems(n, 1));

@@ -119,6 +119,21 @@ def test_eigh_edges(T, ctx, complex_, n):
     assert isometry_err(v) < (8 * n + 64) * U64
 
 
+# on chip; first columns from 64 x 64 tiles, one and many of them; panels
+@pytest.mark.parametrize("complex_,n", [(True, 7), (True, 192), (True, 193), (True, 200), (True, 290), (True, 384),
+                                        (True, 450), (False, 320), (False, 330), (False, 384), (False, 450)])
+def test_eigh_reads_the_lower_triangle(T, ctx, complex_, n):
+    """Values above the diagonal that are not the conjugates of those below do not count."""
+    a = draw((n, n), complex_, 9 * n)
+    h = (a + a.conj().T) / 2
+    given = np.tril(h) + np.triu(draw((n, n), complex_, 9 * n + 1), 1)
+    code = T.C128 if complex_ else T.F64
+    w, v = (x.numpy() for x in T.eigh(ctx, T.Tensor.from_numpy(ctx, given, code)))
+    tol = (8 * n + 64) * U64 * np.linalg.norm(h, 2)
+    assert np.abs(w - np.linalg.eigvalsh(h)).max() < tol and np.abs(h @ v - v * w).max() < tol
+    assert np.abs(T.eigvalsh(ctx, T.Tensor.from_numpy(ctx, given, code)).numpy() - w).max() < tol
+
+
 @pytest.mark.parametrize("n,scale", [(9, 1.0), (40, 1e-120), (40, 1e120), (130, 1.0)])
 def test_eigvalsh_of_diagonals(T, ctx, n, scale):
     """Diagonal matrices with values over 200 decades, both signs, repeated values and zeros: the reduction
