@@ -386,7 +386,7 @@ hipError_t copy_from_table(const PtrTable& src, void* dst, size_t stride, size_t
   if (bits % 16 == 0) go(copy_table_kernel<uint4>, 16);
   else if (bits % 8 == 0) go(copy_table_kernel<uint2>, 8);
   else if (bits % 4 == 0) go(copy_table_kernel<uint32_t>, 4);
-  else return hipErrorInvalidValue;
+  else go(copy_table_kernel<uint8_t>, 1);
   return hipGetLastError();
 }
 

@@ -49,7 +49,7 @@ struct PtrTable {
   void* p[PTR_TABLE];
 };
 
-// dst + b * stride <- src.p[b] (bytes each, a multiple of 4), b < n <= PTR_TABLE.
+// dst + b * stride <- src.p[b] (bytes each), b < n <= PTR_TABLE.
 hipError_t copy_from_table(const PtrTable& src, void* dst, size_t stride, size_t bytes, int n, hipStream_t s);
 // dst.p[b] <- src + b * stride: the len[b] first doubles, b < n.
 hipError_t copy_doubles_to_table(const double* src, long long stride, const PtrTable& dst, const int* len, int maxlen,

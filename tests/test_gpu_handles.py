@@ -66,3 +66,28 @@ def test_result_grows_over_an_operand(T, ctx, la, lb, lc, dims):
     assert np.abs(got.numpy() - ref).max() < 1e-13 * 70
     for h in (view, out):
         T._check(L.tci_destroy(ctx.h, h), "tci_destroy")
+
+
+@pytest.mark.parametrize("shift", [1, 2, 4, 8])
+def test_operands_at_any_address(T, ctx, shift):
+    """Operands are copied before they are used, so a wrapped address may be any multiple of a byte."""
+    arrs = [draw(s, 7 + i) for i, s in enumerate(((3, 2, 5), (5, 2, 3), (2, 2, 2, 2)))]
+    ops, keep = [], []
+    for a in arrs:
+        buf = torch.zeros(a.nbytes + 16, dtype=torch.uint8, device="cuda")
+        buf[shift:shift + a.nbytes] = torch.from_numpy(np.frombuffer(a.tobytes(), np.uint8).copy()).cuda()
+        h = ctypes.c_void_p()
+        T._check(T.lib().tci_wrap(ctx.h, T.C128, a.ndim, T._i64(a.shape), ctypes.c_void_p(buf.data_ptr() + shift),
+                                  ctypes.byref(h)), "tci_wrap")
+        ops.append(h)
+        keep.append(buf)
+    p = T.update_params(chi_min=1, chi_max=4, direction=T.DIR_LEFT)
+    want = T.two_site_update_batched(ctx, *([T.Tensor.from_numpy(ctx, a, T.C128)] for a in arrs), p)
+    out = [T.Tensor.empty(ctx, t, n) for t, n in ((T.C128, 24), (T.F64, 4), (T.C128, 24))]
+    P, info = ctypes.c_void_p * 1, (T.UpdateInfo * 1)()
+    T._check(T.lib().tci_two_site_update_batched(ctx.h, 1, *(P(h.value) for h in ops), ctypes.byref(p),
+                                                 *(P(x.h.value) for x in out), info), "tci_two_site_update_batched")
+    for x, y in zip(out, want[:3]):
+        assert np.array_equal(x.numpy(), y[0].numpy())
+    for h in ops:
+        T._check(T.lib().tci_destroy(ctx.h, h), "tci_destroy")
