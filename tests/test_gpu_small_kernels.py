@@ -170,8 +170,9 @@ def test_singular_values_of_padded_batches(T, ctx, batch, chi):
         assert np.all(x[chi:] ** 2 < 8 * n * U64 * r[0] ** 2)
 
 
-# complex FP64 tiles are 128 x 64, 64 x 64 or 32 x 32 by the size of the launch: a single element, remainders of each
-# tile, a long inner dimension (split) on a small output, and sizes that choose each shape
+# complex FP64 tiles are 128 x 64, 64 x 64 or 32 x 32 by the size of the launch: remainders of each tile, a long inner
+# dimension (split) on a small output, and sizes that choose each shape; the four with K <= 32 and at most 2^17
+# multiply-adds take the one-launch path
 @pytest.mark.parametrize("complex_,m,n,k", [(True, 1, 1, 1), (True, 33, 31, 17), (True, 31, 65, 1), (True, 129, 63, 300),
                                             (True, 520, 530, 40), (True, 1100, 1000, 33), (True, 2050, 2047, 19),
                                             (False, 33, 70, 5), (False, 65, 64, 1000), (False, 1030, 1040, 20),
@@ -184,7 +185,22 @@ def test_fp64_product_tiles(T, ctx, complex_, m, n, k):
     assert np.all(np.abs(c - a @ b) <= 4 * (k + 2) * U64 * (np.abs(a) @ np.abs(b)))
 
 
-# 64 samples per stage, one per workgroup up to 512 and four above, more than one stage per chunk above 2048
+# the same kernel below one tile: a single element, inner dimensions shorter than a k tile, remainders of the 32 x 32
+# tile; the result shares memory with an operand, which keeps such small products off the one-launch path
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (7, 5, 3), (33, 31, 17), (31, 65, 1), (33, 70, 5), (16, 16, 15),
+                                   (32, 32, 16), (64, 33, 31), (1, 200, 2)])
+@pytest.mark.parametrize("complex_", [True, False])
+def test_fp64_products_below_one_tile(T, ctx, m, n, k, complex_):
+    a, b = draw((m, k), complex_, m + k), draw((k, n), complex_, n + 2 * k)
+    dt = T.C128 if complex_ else T.F64
+    buf = torch.zeros(m * max(n, k), dtype=T.TORCH_OF[dt], device="cuda")
+    buf[:m * k] = torch.from_numpy(a.reshape(-1))
+    ta, out = T.Tensor(ctx, buf[:m * k].view(m, k)), T.Tensor(ctx, buf)
+    c = T.contract(ctx, ta, "ik", T.Tensor.from_numpy(ctx, b, dt), "kj", "ij", out=out).numpy()
+    assert np.all(np.abs(c - a @ b) <= 4 * (k + 2) * U64 * (np.abs(a) @ np.abs(b)))
+
+
+# 64 samples per stage, one sample per workgroup up to 512 and four above; several stages
 @pytest.mark.parametrize("n", [1, 63, 65, 512, 513, 2051])
 def test_sketch_gradients(T, ctx, n):
     """FP32 sums of n products of values of order one: error at most about n 2^-24 of the sum of magnitudes, which
