@@ -773,8 +773,9 @@ static hipError_t launch(K kern, const GemmArgs& a, int BM, int BN, hipStream_t 
 // its epilogue; cutting K into sp chunks adds a reduction pass that writes and
 // reads sp partial slabs.  The largest tile and the fewest chunks win unless
 // another choice is 10% cheaper.  Chunks have SPLITK_MIN_K or more and fit the
-// caller's scratch.  Neither choice changes the order of the sums within a
-// chunk, so the tile shape does not change a result.
+// caller's scratch.  Without a split the sums run over k in order whatever the
+// tile; a chunk of a split is a multiple of the tile's k step (8 in the largest
+// complex tile, 16 in the others), so there the cut depends on the tile.
 constexpr int SPLITK_MIN_K = 128;
 constexpr int SPLITK_MAX = 32;
 constexpr long long SPLITK_MAX_TILES = 1024;
@@ -815,9 +816,8 @@ static F64Plan f64_plan(const GemmArgs& a, bool cplx) {
 }
 
 template <typename T>
-static hipError_t launch_f64(const GemmArgs& a0, hipStream_t s) {
+static hipError_t launch_f64(const GemmArgs& a0, const F64Plan& pl, hipStream_t s) {
   GemmArgs a = a0;
-  const F64Plan pl = f64_plan(a, Elem<T>::cplx);
   a.ksplit = pl.sp > 1 ? pl.sp : 0;
   const dim3 grid((a.n + pl.bn - 1) / pl.bn, (a.m + pl.bm - 1) / pl.bm, a.batch * pl.sp);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
@@ -838,13 +838,15 @@ hipError_t gemm(int dtype, int prec, const GemmArgs& a, hipStream_t s) {
   // real one; split-BF16x3 executes three bf16 products per multiply-add
   const bool cplx = dtype == C64 || dtype == C128;
   double flops = (cplx ? 8.0 : 2.0) * a.m * (double)a.n * a.k * a.batch;
-  if (a.lower_band > 0 && !a.dims) {
-    // only the output tiles the kernel computes (FP64 tiles: 128 x 64 complex, 128 x 128 real)
-    const int bm = 128, bn = cplx ? 64 : 128;
+  const bool fp64 = dtype == C128 || dtype == F64;
+  const F64Plan pl = fp64 ? f64_plan(a, cplx) : F64Plan{128, cplx ? 64 : 128, 1};
+  if (prof_on() && a.lower_band > 0 && !a.dims) {
+    // only the output tiles the kernel computes: in row m0 those with n0 < m0 + bm - 1 + lower_band
     double cells = 0.0;
-    for (int m0 = 0; m0 < a.m; m0 += bm)
-      for (int n0 = 0; n0 < a.n; n0 += bn)
-        if (n0 - (m0 + bm - 1) < a.lower_band) cells += (double)std::min(bm, a.m - m0) * std::min(bn, a.n - n0);
+    for (int m0 = 0; m0 < a.m; m0 += pl.bm) {
+      const long long tiles = (m0 + pl.bm - 1 + (long long)a.lower_band + pl.bn - 1) / pl.bn;
+      cells += (double)std::min(pl.bm, a.m - m0) * std::min<long long>(a.n, tiles * pl.bn);
+    }
     flops *= cells / ((double)a.m * a.n);
   }
   if ((dtype == C64 || dtype == F32) && prec == PREC_BF16X3) flops *= 3.0;
@@ -858,9 +860,9 @@ hipError_t gemm(int dtype, int prec, const GemmArgs& a, hipStream_t s) {
   }
   switch (dtype) {
     case C128:
-      return launch_f64<cd>(a, s);
+      return launch_f64<cd>(a, pl, s);
     case F64:
-      return launch_f64<double>(a, s);
+      return launch_f64<double>(a, pl, s);
     case C64:
       if (prec == PREC_BF16X3) return launch(gemm_bf16x3_kernel<cf, 64, 64>, a, 64, 64, s);
       return launch(gemm_f32_kernel<cf, 128, 64>, a, 128, 64, s);

@@ -200,6 +200,19 @@ def test_fp64_products_below_one_tile(T, ctx, m, n, k, complex_):
     assert np.all(np.abs(c - a @ b) <= 4 * (k + 2) * U64 * (np.abs(a) @ np.abs(b)))
 
 
+def test_profiled_work_of_a_lower_triangle(T, ctx):
+    """A complex Gram matrix of order 128 runs in 32 x 32 tiles, without those whose columns are 64 or more beyond
+    their rows: one tile of the first tile row is left out."""
+    a = draw((128, 128), True, 3)
+    T.profile_enable(ctx, True)
+    try:
+        T.trunc_svd(ctx, T.Tensor.from_numpy(ctx, a, T.C128), 1, 1, 20)
+        count, _, work = T.profile_query(ctx, "svd_gram:c128_fp64")
+    finally:
+        T.profile_enable(ctx, False)
+    assert count == 1 and work == 8 * 128 * (128 * 128 - 32 * 32)
+
+
 # 64 samples per stage, one sample per workgroup up to 512 and four above; several stages
 @pytest.mark.parametrize("n", [1, 63, 65, 512, 513, 2051])
 def test_sketch_gradients(T, ctx, n):
