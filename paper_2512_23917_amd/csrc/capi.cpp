@@ -768,7 +768,8 @@ tci_status tci_contract(tci_context ctx, tci_tensor a, const int32_t* la, int na
   // instead of one outweigh the uncoalesced loads up to 64 terms).
   const bool moves = !(is_ident(permA) || is_ident(permAt)) || !(is_ident(permB) || is_ident(permBt)) || !same;
   if ((dt == C128 || dt == F64) && !alias && M > 0 && N > 0 && K > 0 && K <= (moves ? CONTRACT_MAX_K : 32) &&
-      M * N <= CONTRACT_MAX_WORK / K && std::max({na, nb, nc}) <= CONTRACT_MAX_BONDS) {
+      M * N <= CONTRACT_MAX_WORK / K) {
+    static_assert(MAX_ORDER <= CONTRACT_MAX_BONDS, "tables of bonds");
     TCI_TRY(ensure_shape(ctx, c, dt, nc, cshape));
     long long sta[MAX_ORDER + 1], stb[MAX_ORDER + 1];
     int64_t sha[MAX_ORDER], shb[MAX_ORDER];

@@ -4,7 +4,7 @@
 
 namespace tci {
 
-constexpr int CONTRACT_MAX_BONDS = 16;
+constexpr int CONTRACT_MAX_BONDS = 8;
 constexpr int CONTRACT_MAX_K = 64;                 // summed terms per element
 constexpr long long CONTRACT_MAX_WORK = 1 << 17;   // multiply-adds
 

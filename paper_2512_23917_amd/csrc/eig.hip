@@ -59,14 +59,6 @@ __device__ inline double shfl_xor_t(double v, int m) { return __shfl_xor(v, m); 
 __device__ inline cd shfl_xor_t(cd v, int m) { return cd{__shfl_xor(v.x, m), __shfl_xor(v.y, m)}; }
 __device__ inline double rl(double, double r) { return r; }   // a real number as the element type
 __device__ inline cd rl(cd, double r) { return cd{r, 0.0}; }
-__device__ inline double wsum(double v) { return wave_sum(v); }
-__device__ inline cd wsum(cd v) { return cd{wave_sum(v.x), wave_sum(v.y)}; }
-__device__ inline double bsum(double v, double* sh) { return block_sum(v, sh); }
-__device__ inline cd bsum(cd v, double* sh) {
-  const double a = block_sum(v.x, sh);
-  const double b = block_sum(v.y, sh);
-  return cd{a, b};
-}
 
 // ---------------------------------------------------------------------------
 // Per-column kernels of the blocked reduction (LAPACK latrd organisation,
@@ -141,23 +133,6 @@ static int tri_chunk_len(int nact, int batch) {
 __device__ inline bool tri_slot_used(int t, int r, int b0, int ch) {
   const int Rr = r / TT;
   return t > Rr || ((t - b0) & (ch - 1)) == 0;
-}
-
-// Sum of a per-thread complex / real value over groups of 4 consecutive lanes.
-template <typename T>
-__device__ inline T quad_sum(T v) {
-  if constexpr (sizeof(T) == 16) {
-    double r = v.x, i = v.y;
-    r += __shfl_xor(r, 1);
-    i += __shfl_xor(i, 1);
-    r += __shfl_xor(r, 2);
-    i += __shfl_xor(i, 2);
-    return cd{r, i};
-  } else {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    return v;
-  }
 }
 
 // Sum over the 16 lanes of a DPP row; every lane receives the total.
@@ -418,7 +393,7 @@ __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int 
     }
     // ||x||^2 partial of this block (summed by the next kernel)
     xn2 = wave64_sum(xn2);
-    if (lane == 0 && icol + 1 < n) pa[blockIdx.x] = xn2;
+    if (lane == 0) pa[blockIdx.x] = xn2;
   }
 }
 
@@ -604,36 +579,29 @@ static hipError_t tridiag_impl(const TriArgs& a, int batch, hipStream_t s) {
       const int rowsA = n - i;
       hipLaunchKernelGGL((tri_colA_kernel<T, NB>), dim3((rowsA + TT - 1) / TT, batch), dim3(256), 0, s, a, i, i,
                          p > 0 ? i - 1 : -1, j0, tri_chunk_len(nbt - i / TT, batch));
-      if (i + 1 < n) {
-        const int nact = nbt - (i + 1) / TT, ch = tri_chunk_len(nact, batch);
-        // algorithmic bytes: the lower triangle of the trailing matrix read once
-        ProfScope ps(s, 0.5 * (double)(n - i - 1) * (n - i) * sizeof(T) * batch, "hemv");
-        hipLaunchKernelGGL((tri_colC_kernel<T, NB>), dim3(batch, tri_chunks(nact, ch)), dim3(256), 0, s, a, i,
-                           j0, ch);
-      }
+      const int nact = nbt - (i + 1) / TT, ch = tri_chunk_len(nact, batch);
+      // algorithmic bytes: the lower triangle of the trailing matrix read once
+      ProfScope ps(s, 0.5 * (double)(n - i - 1) * (n - i) * sizeof(T) * batch, "hemv");
+      hipLaunchKernelGGL((tri_colC_kernel<T, NB>), dim3(batch, tri_chunks(nact, ch)), dim3(256), 0, s, a, i, j0, ch);
     }
     const int t = j0 + pe;
-    if (t < n) {
-      // finish w of the panel's last column, then the trailing update
-      hipLaunchKernelGGL((tri_colA_kernel<T, NB>), dim3((n - t + TT - 1) / TT, batch), dim3(256), 0, s, a, t, -1,
-                         t - 1, j0, tri_chunk_len(nbt - t / TT, batch));
-      const int m = n - t;
-      {
-        const long long tot = (long long)pe * m;
-        const unsigned gx = (unsigned)std::min<long long>(256, (tot + 255) / 256);
-        hipLaunchKernelGGL((tri_cat_kernel<T, NB>), dim3(gx, batch), dim3(256), 0, s, a, j0, pe, t);
-      }
-      // one rank-2pe update: G[t:, t:] -= cat1[:, t:]^T conj(cat2[:, t:])
-      char* G = reinterpret_cast<char*>(a.G);
-      char* ws = reinterpret_cast<char*>(a.ws);
-      GemmArgs g = gemm_args(m, m, 2 * pe, OP_T, OP_R, ws + TriWs<T, NB>::cat1(n) + (size_t)t * es, n,
-                             ws + TriWs<T, NB>::cat2(n) + (size_t)t * es, n, G + ((long)t * a.ldg + t) * es, a.ldg);
-      g.sA = a.sws / (long long)es; g.sB = a.sws / (long long)es; g.sC = a.sG;
-      g.alpha_re = -1.0; g.beta_re = 1.0; g.batch = batch;
-      g.lower_band = TRIDIAG_BAND;
-      hipError_t err = gemm(EigT<T>::dtype, PREC_FP64, g, s);
-      if (err != hipSuccess) return err;
-    }
+    // finish w of the panel's last column, then the trailing update
+    hipLaunchKernelGGL((tri_colA_kernel<T, NB>), dim3((n - t + TT - 1) / TT, batch), dim3(256), 0, s, a, t, -1, t - 1,
+                       j0, tri_chunk_len(nbt - t / TT, batch));
+    const int m = n - t;
+    const long long tot = (long long)pe * m;
+    const unsigned gx = (unsigned)std::min<long long>(256, (tot + 255) / 256);
+    hipLaunchKernelGGL((tri_cat_kernel<T, NB>), dim3(gx, batch), dim3(256), 0, s, a, j0, pe, t);
+    // one rank-2pe update: G[t:, t:] -= cat1[:, t:]^T conj(cat2[:, t:])
+    char* G = reinterpret_cast<char*>(a.G);
+    char* ws = reinterpret_cast<char*>(a.ws);
+    GemmArgs g = gemm_args(m, m, 2 * pe, OP_T, OP_R, ws + TriWs<T, NB>::cat1(n) + (size_t)t * es, n,
+                           ws + TriWs<T, NB>::cat2(n) + (size_t)t * es, n, G + ((long)t * a.ldg + t) * es, a.ldg);
+    g.sA = a.sws / (long long)es; g.sB = a.sws / (long long)es; g.sC = a.sG;
+    g.alpha_re = -1.0; g.beta_re = 1.0; g.batch = batch;
+    g.lower_band = TRIDIAG_BAND;
+    hipError_t err = gemm(EigT<T>::dtype, PREC_FP64, g, s);
+    if (err != hipSuccess) return err;
   }
   return hipGetLastError();
 }

@@ -13,7 +13,6 @@ constexpr int TRIDIAG_BAND = 64;
 //   G    n x n, ld ldg      the Hermitian matrix; read (and overwritten) only at col - row < TRIDIAG_BAND
 //   Vt   n x n, ld n        Vt[c * n + r] = reflector c at row r (0 for r <= c, 1 at r = c+1)
 //   Wp   NB x n, ld n       panel W^T of the blocked reduction
-//   y    n                  Hermitian matrix-vector product
 //   d, e (real), tau        tridiagonal diagonal / off-diagonal, reflector scalars (dtype)
 struct TriArgs {
   int n;
@@ -22,7 +21,6 @@ struct TriArgs {
   void* tau; long long stau;
   void* Vt; long long sVt;
   void* Wp; long long sWp;
-  void* y; long long sy;
   void* ws; long long sws;   // per-problem workspace of tridiag_ws_bytes(n) bytes
 };
 

@@ -55,7 +55,6 @@ __device__ inline double wsum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
-__device__ inline double wsum_re(double v) { return wsum(v); }
 __device__ inline cd wsum_c(cd v) { return cd{wsum(v.x), wsum(v.y)}; }
 __device__ inline double wsum_c(double v) { return wsum(v); }
 

@@ -188,10 +188,9 @@ tci_status sketch_run(tci_context ctx, int dt_lo, int wdt, int prec, int nb, int
   SK_ARENA(tau, char, ew * (size_t)ng * nb);
   SK_ARENA(Vt, char, ew * (size_t)sG * nb);
   SK_ARENA(Wp, char, ew * (size_t)ng * TRIDIAG_NB * nb);
-  SK_ARENA(yv, char, ew * (size_t)ng * nb);
   TriArgs ta{};
   ta.n = ng; ta.G = Gk; ta.ldg = ng; ta.sG = sG; ta.d = d; ta.e = e; ta.sde = ng; ta.tau = tau; ta.stau = ng;
-  ta.Vt = Vt; ta.sVt = sG; ta.Wp = Wp; ta.sWp = (long long)ng * TRIDIAG_NB; ta.y = yv; ta.sy = ng;
+  ta.Vt = Vt; ta.sVt = sG; ta.Wp = Wp; ta.sWp = (long long)ng * TRIDIAG_NB;
   ta.sws = (long long)tridiag_ws_bytes(wdt, ng);
   ta.ws = ctx->arena.get((size_t)ta.sws * nb);
   if (!ta.ws) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "workspace");

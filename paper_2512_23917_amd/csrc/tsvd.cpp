@@ -140,7 +140,6 @@ tci_status tsvd_eigvals(tci_context ctx, int wdt, int nb, int m, int n, const vo
   ARENA(tau, char, es * (size_t)ng * nb);
   ARENA(Vt, char, es * (size_t)ng * ng * nb);
   ARENA(Wp, char, es * (size_t)ng * TRIDIAG_NB * nb);
-  ARENA(y, char, es * (size_t)ng * nb);
   TriArgs& ta = st.ta;
   ta = TriArgs{};
   ta.n = ng;
@@ -149,7 +148,6 @@ tci_status tsvd_eigvals(tci_context ctx, int wdt, int nb, int m, int n, const vo
   ta.tau = tau; ta.stau = ng;
   ta.Vt = Vt; ta.sVt = (long long)ng * ng;
   ta.Wp = Wp; ta.sWp = (long long)ng * TRIDIAG_NB;
-  ta.y = y; ta.sy = ng;
   ta.sws = (long long)tridiag_ws_bytes(wdt, ng);
   ta.ws = ctx->arena.get((size_t)ta.sws * nb);
   if (!ta.ws) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "workspace");
@@ -1113,9 +1111,8 @@ static tci_status eigh_core(tci_context ctx, tci_tensor a, int k_rows, tci_tenso
   ARENA(tau, char, es * n);
   ARENA(Vt, char, es * (size_t)n * n);
   ARENA(Wp, char, es * (size_t)n * TRIDIAG_NB);
-  ARENA(y, char, es * n);
   TriArgs ta{};
-  ta.n = n; ta.G = G; ta.ldg = n; ta.d = d; ta.e = e; ta.tau = tau; ta.Vt = Vt; ta.Wp = Wp; ta.y = y;
+  ta.n = n; ta.G = G; ta.ldg = n; ta.d = d; ta.e = e; ta.tau = tau; ta.Vt = Vt; ta.Wp = Wp;
   ta.sws = (long long)tridiag_ws_bytes(dt, n);
   ta.ws = ctx->arena.get((size_t)ta.sws);
   if (!ta.ws) TCI_RET(TCI_ERR_OUT_OF_MEMORY, "workspace");
