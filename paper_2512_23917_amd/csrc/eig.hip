@@ -267,7 +267,7 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // w takes every fourth slot of P and every fourth panel column).  A launch is
 // one chain of latencies, so every global load is issued before the first
 // wait, what all waves need of row icol and of the partials is reduced by each
-// wave for itself, and two barriers remain per half.
+// wave for itself, and two barriers remain before w and one in the column update.
 template <typename T, int NB>
 __global__ __launch_bounds__(256) void tri_colA_kernel(TriArgs a, int row0, int icol, int ifin, int j0, int ch) {
   constexpr int PU = NB / 4, SU = 8;   // panel columns and slots of P (the first 32) per wave
