@@ -159,13 +159,14 @@ __device__ inline void polar(cd z, double& r, cd& ph) {
 
 // Orthonormal completion of vector r of the set vec(q)[i] = P[q*vs + i*is]
 // (q < r already orthonormal, length len): the first unit vector e_t whose
-// component orthogonal to them has norm > 1/2, orthogonalised twice.  Run
-// by one wave.
+// component orthogonal to them has norm > 1/2, or else the e_t with the largest
+// one (a vector spread over all entries has no component above 1/2 anywhere),
+// orthogonalised twice.  Run by one wave.
 template <typename T>
 __device__ void complete_vector(T* P, long long vs, long long is, int len, int r) {
   const int lane = threadIdx.x & 63;
-  for (int t = 0; t < len; ++t) {
-    // v = e_t - sum_q conj(vec_q[t]) vec_q, twice
+  // v = e_t - sum_q conj(vec_q[t]) vec_q, twice; returns |v|^2
+  auto attempt = [&](int t) -> double {
     for (int i = lane; i < len; i += 64) P[r * vs + i * is] = (i == t) ? one_of(T{}) : zero_of(T{});
     __threadfence_block();
     for (int pass = 0; pass < 2; ++pass) {
@@ -180,14 +181,21 @@ __device__ void complete_vector(T* P, long long vs, long long is, int len, int r
     }
     double nn = 0.0;
     for (int i = lane; i < len; i += 64) nn += sq(P[r * vs + i * is]);
-    nn = wsum(nn);
-    if (nn > 0.25) {
-      const double inv = 1.0 / sqrt(nn);
-      for (int i = lane; i < len; i += 64) P[r * vs + i * is] = scl(inv, P[r * vs + i * is]);
-      __threadfence_block();
-      return;
+    return wsum(nn);
+  };
+  double nn = 0.0, best = 0.0;
+  int tb = 0;
+  for (int t = 0; t < len && nn <= 0.25; ++t) {
+    nn = attempt(t);
+    if (nn > best) {
+      best = nn;
+      tb = t;
     }
   }
+  if (nn <= 0.25) nn = attempt(tb);
+  const double inv = 1.0 / sqrt(nn);
+  for (int i = lane; i < len; i += 64) P[r * vs + i * is] = scl(inv, P[r * vs + i * is]);
+  __threadfence_block();
 }
 
 // A: problem b at A + b*sA, row-major with leading dimension lda.

@@ -85,6 +85,22 @@ def test_jacobi_svd_exponent_range(T, ctx, m, n, scale, grade, complex_):
 
 
 @pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("n", [3, 5, 17, 33, 63])
+def test_jacobi_svd_of_a_spread_null_vector(T, ctx, n, complex_):
+    """The adjacency matrix of an open chain of odd length, alone and with zero rows and columns around it: singular
+    values 2 |cos(pi k / (n + 1))|, the null vector spread over (n + 1) / 2 entries of equal size."""
+    chain = np.diag(np.ones(n - 1), 1) + np.diag(np.ones(n - 1), -1)
+    ref = np.sort(2 * np.abs(np.cos(np.pi * np.arange(1, n + 1) / (n + 1))))[::-1]
+    wide = np.zeros((n, n + 3))
+    wide[:, 2:2 + n] = chain
+    for a in (chain, wide, wide.T):
+        code = T.C128 if complex_ else T.F64
+        u, s, vh = (x.numpy() for x in T.svd(ctx, T.Tensor.from_numpy(ctx, a + 0j if complex_ else a, code), 1))
+        assert np.abs(s - ref).max() < 1e-13 and np.abs((u * s) @ vh - a).max() < 1e-13
+        assert isometry_err(u) < 1e-13 and isometry_err(vh, False) < 1e-13
+
+
+@pytest.mark.parametrize("complex_", [False, True])
 @pytest.mark.parametrize("n", [24, 32, 60])
 def test_jacobi_svd_keeps_norms(T, ctx, n, complex_):
     """The rows of V^H come from about 10 n rotations each.  A rotation's c^2 + s^2 is off by 0.6 to 0.85 u rms, of
