@@ -307,7 +307,8 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
           }
         }
         ga = pair_sum<LP>(ga);
-        // |g| > tol |w_p| |w_q|, squared where nothing can underflow
+        // |g| > tol |w_p| |w_q|, squared where that cannot underflow (a column
+        // that shrank below that within the sweep waits for the next one)
         bool rot = al > 0.0 && be > 0.0;
         double ag, ig;
         T phc;
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
           modulus<true>(ga, ag, ig, phc);
           rot = rot && ag > tol * (al * rsqrt_nr(al)) * (be * rsqrt_nr(be));
         } else {
-          rot = rot && sq(ga) > (tol * al) * (tol * be);
+          rot = rot && sq(ga) > fmax((tol * al) * (tol * be), 0x1p-960);
         }
         if (rot) {
           if constexpr (!TINY) modulus<false>(ga, ag, ig, phc);
@@ -396,11 +397,11 @@ __global__ __launch_bounds__(NT) void jacobi_svd_kernel(const T* A, long long ld
       nn = pair_sum<LP>(nn);
       if (sub == 0) {
         sig[j] = nn;
-        if (nn > 0.0 && nn < 0x1p-440) some_tiny = 1;
+        if (nn > 0.0 && nn < 0x1p-400) some_tiny = 1;
       }
     }
     __syncthreads();
-    // without such columns every |g| to rotate is above tol 2^-440
+    // without such columns every |g|^2 to rotate is above 2^-960
     if (__builtin_expect(__builtin_amdgcn_readfirstlane(some_tiny) == 0, 1)) steps(std::false_type{});
     else steps(std::true_type{});
     conv = (rotated == 0);

@@ -101,6 +101,32 @@ def test_jacobi_svd_of_a_spread_null_vector(T, ctx, n, complex_):
 
 
 @pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("kind", ["ones", "star", "phases", "projectors", "integers"])
+@pytest.mark.parametrize("n", [4, 17, 23, 48, 64])
+def test_jacobi_svd_of_exact_null_spaces(T, ctx, n, kind, complex_):
+    """Matrices of low rank and exact arithmetic: the columns of the null space shrink by the unit roundoff in every
+    sweep, through the smallest numbers to zero, and must leave the others as they are."""
+    star = np.zeros((n, n))
+    star[0, 1:] = star[1:, 0] = 1.0
+    k = np.arange(n)
+    half = np.ones((2, 2))
+    proj = np.eye(1)
+    while proj.shape[0] < n:
+        proj = np.kron(proj, half)
+    r = np.random.default_rng(n).integers(-2, 3, (n, max(1, n // 3)))
+    a = {"ones": np.ones((n, n)), "star": star, "projectors": proj, "integers": (r @ r.T).astype(float),
+         "phases": (np.diag(np.ones(n - 1), 1) + np.diag(np.ones(n - 1), -1)) * np.cos(np.outer(k, k))}[kind]
+    if complex_:
+        a = a * np.exp(1j * np.outer(np.arange(len(a)), np.arange(len(a)) + 1.0))
+    code = T.C128 if complex_ else T.F64
+    u, s, vh = (x.numpy() for x in T.svd(ctx, T.Tensor.from_numpy(ctx, a, code), 1))
+    tol = 1e-13 + 4 * n * U64
+    assert s.shape == (len(a),) and np.abs(s - np.linalg.svd(a, compute_uv=False)).max() < tol * s[0]
+    assert np.linalg.norm((u * s) @ vh - a) < tol * np.linalg.norm(a)
+    assert isometry_err(u) < tol and isometry_err(vh, False) < tol
+
+
+@pytest.mark.parametrize("complex_", [False, True])
 @pytest.mark.parametrize("n", [24, 32, 60])
 def test_jacobi_svd_keeps_norms(T, ctx, n, complex_):
     """The rows of V^H come from about 10 n rotations each.  A rotation's c^2 + s^2 is off by 0.6 to 0.85 u rms, of
