@@ -1255,7 +1255,10 @@ __global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d,
   double bi = hash_uniform(b, j, 0);
   auto step = [&](int i, double sub, double dn, double c_n) {  // entries (i+1, i), (i+1, i+1), (i+1, i+2)
     const double a_n = dn - lamj;
-    const bool sw = (fabs(a_i) < fabs(sub)) & (fabs(sub) > 1e-290);   // interchange rows i and i+1
+    // interchange rows i and i+1, but for no pivot below the smallest: a block of
+    // noise (what the reduction leaves of a null space) would otherwise be solved
+    // to its own relative accuracy, each vector to the same direction
+    const bool sw = (fabs(a_i) < fabs(sub)) & (fabs(sub) >= tiny);
     const double pa = fabs(a_i) < tiny ? (a_i >= 0 ? tiny : -tiny) : a_i;
     const double piv = sw ? sub : pa, num = sw ? a_i : sub;
     const double y0 = __builtin_amdgcn_rcp(piv);

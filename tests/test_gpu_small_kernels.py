@@ -176,6 +176,37 @@ def test_eigh_reads_the_lower_triangle(T, ctx, complex_, n):
     assert np.abs(T.eigvalsh(ctx, T.Tensor.from_numpy(ctx, given, code)).numpy() - w).max() < tol
 
 
+def check_eigh(T, ctx, a):
+    n = len(a)
+    w, v = (x.numpy() for x in T.eigh(ctx, T.Tensor.from_numpy(ctx, a, T.C128 if np.iscomplexobj(a) else T.F64)))
+    tol = (8 * n + 64) * U64
+    scale = np.linalg.norm(a, 2)
+    assert np.abs(w - np.linalg.eigvalsh(a)).max() < tol * scale
+    assert np.abs(a @ v - v * w).max() < tol * scale
+    assert isometry_err(v) < tol
+
+
+@pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("kind,n", [("ones", n) for n in (8, 25, 34, 51, 59, 192, 300, 320)] +
+                         [("bipartite", n) for n in (11, 14, 17, 22, 36, 50, 65, 129, 193, 256, 330)] +
+                         [("star", n) for n in (9, 64, 200)] + [("permutation", n) for n in (7, 15, 60)])
+def test_eigh_of_null_spaces(T, ctx, kind, n, complex_):
+    """Matrices whose reduction ends in blocks of rounding errors: eigenvectors of a null space of up to n - 1
+    dimensions, and of eigenvalues that several decoupled blocks share."""
+    a = np.zeros((n, n), dtype=complex if complex_ else float)
+    if kind == "ones":
+        a[:] = 1.0
+    elif kind == "bipartite":
+        a[:n // 2, n // 2:] = 1.0
+        a += a.T
+    elif kind == "star":
+        a[0, 1:] = a[1:, 0] = 1.0
+    else:
+        p = np.eye(n)[np.random.default_rng(n).permutation(n)]
+        a += p + p.T
+    check_eigh(T, ctx, a)
+
+
 @pytest.mark.parametrize("n,scale", [(9, 1.0), (40, 1e-120), (40, 1e120), (130, 1.0)])
 def test_eigvalsh_of_diagonals(T, ctx, n, scale):
     """Diagonal matrices with values over 200 decades, both signs, repeated values and zeros: the reduction
