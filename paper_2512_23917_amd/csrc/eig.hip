@@ -1242,7 +1242,13 @@ __global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d,
   int ex = 0;
   if (tnorm > 0.0 && tnorm < 1e308) (void)frexp(tnorm, &ex);
   const double un = ldexp(1.0, -max(ex, -1000));
-  const double lamj = lam[b * slam + j] * un;
+  // An eigenvalue that equals the one before it to rounding gets a shift a few
+  // ulps below: with both shifts the same, and exact, one direction of a
+  // multiple eigenvalue can outgrow the others by 1 / u in a solve, and what the
+  // orthonormalisation leaves of the next vector is noise (as in LAPACK's stein).
+  double lamj = lam[b * slam + j];
+  if (j > 0) lamj = fmin(lamj, lam[b * slam + j - 1] - 4.0 * 2.220446049250313e-16 * fabs(lamj));
+  lamj *= un;
   const double tiny = fmax(tnorm * un, 0.5) * 2.220446049250313e-16;
 
   // Elimination keeps one "active" row (entries a_i, c_i in columns i, i+1)

@@ -207,6 +207,27 @@ def test_eigh_of_null_spaces(T, ctx, kind, n, complex_):
     check_eigh(T, ctx, a)
 
 
+@pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("kind,n", [("ring", n) for n in (4, 9, 12, 33, 100)] + [("torus", 4), ("torus", 8), ("spins", 4),
+                                                                                ("spins", 6), ("spins", 8)])
+def test_eigh_of_multiple_eigenvalues(T, ctx, kind, n, complex_):
+    """Hopping on a ring and on a torus (pairs and quartets of equal eigenvalues) and a Heisenberg ring (multiplets)."""
+    ring = np.roll(np.eye(n), 1, axis=0)
+    ring = ring + ring.T
+    if kind == "ring":
+        a = ring
+    elif kind == "torus":
+        a = np.kron(ring, np.eye(n)) + np.kron(np.eye(n), ring)
+    else:
+        swap = np.arange(2 ** n)
+        a = np.zeros((2 ** n, 2 ** n))
+        for i in range(n):      # S_i . S_j = (exchange of the two spins) / 2 - 1 / 4
+            j = (i + 1) % n
+            bi, bj = (swap >> i) & 1, (swap >> j) & 1
+            a += np.eye(2 ** n)[swap ^ ((bi ^ bj) * ((1 << i) | (1 << j)))] / 2 - np.eye(2 ** n) / 4
+    check_eigh(T, ctx, a + 0j if complex_ else a)
+
+
 @pytest.mark.parametrize("n,scale", [(9, 1.0), (40, 1e-120), (40, 1e120), (130, 1.0)])
 def test_eigvalsh_of_diagonals(T, ctx, n, scale):
     """Diagonal matrices with values over 200 decades, both signs, repeated values and zeros: the reduction
