@@ -1205,52 +1205,20 @@ __device__ __forceinline__ double invit_backward(double* z, long ld, unsigned j,
   return amax;
 }
 
-// One solve with the stored factors of column j: z[:, j] <- (T - lam_j)^-1
-// (pre * z[:, j]); returns the factor 1 / max|z| for the next right-hand side.
-__device__ __forceinline__ double invit_solve(double* z, long ld, unsigned j, int n, const double* ru, const double* du,
-                                     const double* du2, const double* dl, double pre) {
-  double sq;
-  invit_forward(z, ld, j, n, dl, pre);
-  const double amax = invit_backward(z, ld, j, n, ru, du, du2, sq);
-  return amax > 0.0 ? 1.0 / amax : 1.0;
-}
-
-__global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d, const double* __restrict__ e,
-                                                   long long sde, int n, const double* __restrict__ lam,
-                                                   long long slam, const int* __restrict__ chi, int kmax, double* Z,
-                                                   long long ldz, long long sZ, double* w_ru, double* w_du,
-                                                   double* w_du2, double* w_dl, long long sw_, int batch) {
-  const int b = blockIdx.y;
-  const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int cb = chi ? min(chi[b], kmax) : kmax;
-  if ((int)(blockIdx.x * blockDim.x) >= cb) return;
-  const double* db = d + b * sde;
-  const double* eb = e + b * sde;
-  double* ru = w_ru + b * sw_;
-  double* du = w_du + b * sw_;
-  double* du2 = w_du2 + b * sw_;
-  double* dl = w_dl + b * sw_;
-  double* z = Z + b * sZ;
-  const long ld = ldz;
-  double tnorm = 0.0;
-  for (int i = threadIdx.x; i < n; i += 64)
-    tnorm = fmax(tnorm, fabs(db[i]) + (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i < n - 1 ? fabs(eb[i]) : 0.0));
-  for (int off = 32; off > 0; off >>= 1) tnorm = fmax(tnorm, __shfl_xor(tnorm, off, 64));
-  if ((int)j >= cb) return;
-  // in units of a power of two near the norm (the vectors do not depend on
-  // it), so that no reciprocal leaves the range
+// A power of two near 1 / norm: in these units (the vectors do not depend on them)
+// no reciprocal leaves the range.
+__device__ inline double invit_unit(double tnorm) {
   int ex = 0;
   if (tnorm > 0.0 && tnorm < 1e308) (void)frexp(tnorm, &ex);
-  const double un = ldexp(1.0, -max(ex, -1000));
-  // An eigenvalue that equals the one before it to rounding gets a shift a few
-  // ulps below: with both shifts the same, and exact, one direction of a
-  // multiple eigenvalue can outgrow the others by 1 / u in a solve, and what the
-  // orthonormalisation leaves of the next vector is noise (as in LAPACK's stein).
-  double lamj = lam[b * slam + j];
-  if (j > 0) lamj = fmin(lamj, lam[b * slam + j - 1] - 4.0 * 2.220446049250313e-16 * fabs(lamj));
-  lamj *= un;
-  const double tiny = fmax(tnorm * un, 0.5) * 2.220446049250313e-16;
+  return ldexp(1.0, -max(ex, -1000));
+}
+__device__ inline double invit_tiny(double tnorm, double un) { return fmax(tnorm * un, 0.5) * 2.220446049250313e-16; }
 
+// P (un T - lamj I) = L U of column j, and its forward solve of the pseudo-random
+// start vector in z[:, j].  un: a power of two near 1 / norm; tiny: the smallest pivot.
+__device__ __forceinline__ void invit_factor(const double* __restrict__ db, const double* __restrict__ eb, int n,
+                                             double lamj, double un, double tiny, int b, unsigned j, long ld, double* ru,
+                                             double* du, double* du2, double* dl, double* z) {
   // Elimination keeps one "active" row (entries a_i, c_i in columns i, i+1)
   // and meets original row i+1 (e_i, d_{i+1} - lam, e_{i+1}).  U row i is
   // stored as (1 / pivot, du, du2); the multiplier goes to dl, offset by +-4
@@ -1304,6 +1272,51 @@ __global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d,
     du2[o] = 0.0;
     z[o] = bi;
   }
+}
+
+// One solve with the stored factors of column j: z[:, j] <- (T - lam_j)^-1
+// (pre * z[:, j]); returns the factor 1 / max|z| for the next right-hand side.
+__device__ __forceinline__ double invit_solve(double* z, long ld, unsigned j, int n, const double* ru, const double* du,
+                                     const double* du2, const double* dl, double pre) {
+  double sq;
+  invit_forward(z, ld, j, n, dl, pre);
+  const double amax = invit_backward(z, ld, j, n, ru, du, du2, sq);
+  return amax > 0.0 ? 1.0 / amax : 1.0;
+}
+
+__global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d, const double* __restrict__ e,
+                                                   long long sde, int n, const double* __restrict__ lam,
+                                                   long long slam, const int* __restrict__ chi, int kmax, double* Z,
+                                                   long long ldz, long long sZ, double* w_ru, double* w_du,
+                                                   double* w_du2, double* w_dl, long long sw_, int batch) {
+  const int b = blockIdx.y;
+  const unsigned j = blockIdx.x * blockDim.x + threadIdx.x;
+  const int cb = chi ? min(chi[b], kmax) : kmax;
+  if ((int)(blockIdx.x * blockDim.x) >= cb) return;
+  const double* db = d + b * sde;
+  const double* eb = e + b * sde;
+  double* ru = w_ru + b * sw_;
+  double* du = w_du + b * sw_;
+  double* du2 = w_du2 + b * sw_;
+  double* dl = w_dl + b * sw_;
+  double* z = Z + b * sZ;
+  const long ld = ldz;
+  double tnorm = 0.0;
+  for (int i = threadIdx.x; i < n; i += 64)
+    tnorm = fmax(tnorm, fabs(db[i]) + (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i < n - 1 ? fabs(eb[i]) : 0.0));
+  for (int off = 32; off > 0; off >>= 1) tnorm = fmax(tnorm, __shfl_xor(tnorm, off, 64));
+  if ((int)j >= cb) return;
+  const double un = invit_unit(tnorm);
+  // An eigenvalue that equals the one before it to rounding gets a shift a few
+  // ulps below: with both shifts the same, and exact, one direction of a
+  // multiple eigenvalue can outgrow the others by 1 / u in a solve, and what the
+  // orthonormalisation leaves of the next vector is noise (as in LAPACK's stein).
+  double lamj = lam[b * slam + j];
+  if (j > 0) lamj = fmin(lamj, lam[b * slam + j - 1] - 4.0 * 2.220446049250313e-16 * fabs(lamj));
+  lamj *= un;
+  const double tiny = invit_tiny(tnorm, un);
+
+  invit_factor(db, eb, n, lamj, un, tiny, b, j, ld, ru, du, du2, dl, z);
   double nn;
   double amax = invit_backward(z, ld, j, n, ru, du, du2, nn);
   invit_forward(z, ld, j, n, dl, amax > 0.0 ? 1.0 / amax : 1.0);
@@ -1339,6 +1352,12 @@ __global__ __launch_bounds__(64) void invit_kernel(const double* __restrict__ d,
 // iterated together with their own factors, and after every solve they are
 // orthonormalised in order against the earlier members (modified
 // Gram-Schmidt), as in LAPACK's stein.
+// With shifts exact to the last bit of the eigenvalues themselves, one direction
+// of a cluster can outgrow the others by 1 / u and more in a solve (u^2 beside 1 in
+// a null space), and what the orthonormalisation leaves of a vector is noise.  Where
+// it leaves less than 1e-2 of one in the last pass, the members are solved again
+// with shifts 4 u ||T|| below: (T - shift)^-1 then stretches all directions of the
+// cluster about alike, and any of them are eigenvectors to that accuracy.
 // The threshold sits at about 90 u ||T||: for a larger gap g the vectors of
 // independent solves overlap by at most about u ||T|| / g < 1/90, which the
 // Cholesky-QR2 that follows on all vectors removes.  (Graded spectra, as the
@@ -1355,8 +1374,8 @@ __device__ inline double wave_sum_d(double v) {
 __global__ __launch_bounds__(64) void invit_cluster_kernel(const double* d, const double* e, long long sde, int n,
                                                            const double* lam, long long slam, const int* chi,
                                                            int kmax, double* Z, long long ldz, long long sZ,
-                                                           const double* w_ru, const double* w_du,
-                                                           const double* w_du2, const double* w_dl, long long sw) {
+                                                           double* w_ru, double* w_du, double* w_du2, double* w_dl,
+                                                           long long sw) {
   const int b = blockIdx.x, lane = threadIdx.x;
   const int cb = chi ? min(chi[b], kmax) : kmax;
   const double* db = d + b * sde;
@@ -1368,7 +1387,7 @@ __global__ __launch_bounds__(64) void invit_cluster_kernel(const double* d, cons
   for (int i = lane; i < n; i += 64)
     tn = fmax(tn, fabs(db[i]) + (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i < n - 1 ? fabs(eb[i]) : 0.0));
   for (int off = 32; off > 0; off >>= 1) tn = fmax(tn, __shfl_xor(tn, off, 64));
-  const double tol = INVIT_CLUSTER_TOL * tn;
+  const double tol = INVIT_CLUSTER_TOL * tn, un = invit_unit(tn);
   int j0 = 0;
   while (j0 < cb) {
     int j1 = j0;
@@ -1377,30 +1396,45 @@ __global__ __launch_bounds__(64) void invit_cluster_kernel(const double* d, cons
       for (int c0 = j0; c0 <= j1; c0 += 64) {
         const int cn = min(64, j1 - c0 + 1);
         const int m = c0 + lane;
-        double scale = 1.0;
-        for (int it = 0; it < 3; ++it) {
-          if (lane < cn)
-            scale = invit_solve(z, ld, m, n, w_ru + b * sw, w_du + b * sw, w_du2 + b * sw, w_dl + b * sw, scale);
-          __syncthreads();
-          // members c0 .. c0+cn-1 in order: apply the pending scale, remove the
-          // earlier members of the cluster, normalise
-          for (int q = c0; q < c0 + cn; ++q) {
-            const double sq = __shfl(scale, q - c0, 64);
-            for (int i = lane; i < n; i += 64) z[(long)i * ld + q] *= sq;
-            for (int r = j0; r < q; ++r) {
-              double dot = 0.0;
-              for (int i = lane; i < n; i += 64) dot += z[(long)i * ld + r] * z[(long)i * ld + q];
-              dot = wave_sum_d(dot);
-              for (int i = lane; i < n; i += 64) z[(long)i * ld + q] -= dot * z[(long)i * ld + r];
-            }
-            double nn = 0.0;
-            for (int i = lane; i < n; i += 64) nn += z[(long)i * ld + q] * z[(long)i * ld + q];
-            nn = wave_sum_d(nn);
-            const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
-            for (int i = lane; i < n; i += 64) z[(long)i * ld + q] *= inv;
+        for (int attempt = 0; attempt < 2; ++attempt) {
+          double scale = 1.0, least = 1.0;
+          if (attempt == 1 && lane < cn) {
+            const double lamm = lb[m] - 4.0 * 2.220446049250313e-16 * tn;
+            invit_factor(db, eb, n, lamm * un, un, invit_tiny(tn, un), b, m, ld, w_ru + b * sw, w_du + b * sw,
+                         w_du2 + b * sw, w_dl + b * sw, z);
+            double sq;
+            const double amax = invit_backward(z, ld, m, n, w_ru + b * sw, w_du + b * sw, w_du2 + b * sw, sq);
+            scale = amax > 0.0 ? 1.0 / amax : 1.0;
           }
-          scale = 1.0;
-          __syncthreads();
+          for (int it = 0; it < 3; ++it) {
+            if (lane < cn)
+              scale = invit_solve(z, ld, m, n, w_ru + b * sw, w_du + b * sw, w_du2 + b * sw, w_dl + b * sw, scale);
+            __syncthreads();
+            // members c0 .. c0+cn-1 in order: apply the pending scale, remove the
+            // earlier members of the cluster, normalise
+            least = 1.0;
+            for (int q = c0; q < c0 + cn; ++q) {
+              const double sq = __shfl(scale, q - c0, 64);
+              for (int i = lane; i < n; i += 64) z[(long)i * ld + q] *= sq;
+              double gone = 0.0;
+              for (int r = j0; r < q; ++r) {
+                double dot = 0.0;
+                for (int i = lane; i < n; i += 64) dot += z[(long)i * ld + r] * z[(long)i * ld + q];
+                dot = wave_sum_d(dot);
+                gone += dot * dot;
+                for (int i = lane; i < n; i += 64) z[(long)i * ld + q] -= dot * z[(long)i * ld + r];
+              }
+              double nn = 0.0;
+              for (int i = lane; i < n; i += 64) nn += z[(long)i * ld + q] * z[(long)i * ld + q];
+              nn = wave_sum_d(nn);
+              least = fmin(least, nn / (nn + gone));
+              const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
+              for (int i = lane; i < n; i += 64) z[(long)i * ld + q] *= inv;
+            }
+            scale = 1.0;
+            __syncthreads();
+          }
+          if (least > 1e-4) break;
         }
       }
     }

@@ -228,6 +228,20 @@ def test_eigh_of_multiple_eigenvalues(T, ctx, kind, n, complex_):
     check_eigh(T, ctx, a + 0j if complex_ else a)
 
 
+@pytest.mark.parametrize("complex_", [False, True])
+@pytest.mark.parametrize("n,seed", [(12, 0), (23, 1), (44, 2), (46, 3), (60, 4), (82, 5), (150, 6), (220, 7), (322, 8)])
+def test_eigh_of_clusters_over_many_scales(T, ctx, n, seed, complex_):
+    """Partial permutations with weights 1, 2, 1e-8, 1e-16 and 0, symmetrised: few distinct eigenvalues at each of the
+    scales, products of the small weights among them, shared by blocks with and without small couplings."""
+    g = np.random.default_rng(seed)
+    for _ in range(6):
+        a = np.zeros((n, n), dtype=complex if complex_ else float)
+        a[np.arange(n), g.permutation(n)] = g.choice([1.0, -1.0, 2.0, 1e-8, 1e-16, 0.0], n)
+        if complex_:
+            a *= np.exp(1j * (np.arange(n)[:, None] - np.arange(n)))
+        check_eigh(T, ctx, (a + a.conj().T) / 2)
+
+
 @pytest.mark.parametrize("n,scale", [(9, 1.0), (40, 1e-120), (40, 1e120), (130, 1.0)])
 def test_eigvalsh_of_diagonals(T, ctx, n, scale):
     """Diagonal matrices with values over 200 decades, both signs, repeated values and zeros: the reduction
