@@ -1267,6 +1267,22 @@ tci_status tci_eigvals(tci_context ctx, tci_tensor a, int k_rows, tci_tensor w) 
 } TCI_API_CATCH
 
 // ----------------------------------------------------------------- two-site update
+// The identity gate of two spins (4 x 4) in each dtype, for the life of the process.
+static const void* identity_gate(int dt) {
+  struct Tables {
+    double r64[16] = {}, c64[32] = {};
+    float r32[16] = {}, c32[32] = {};
+    Tables() {
+      for (int q = 0; q < 4; ++q) {
+        r64[5 * q] = c64[10 * q] = 1.0;
+        r32[5 * q] = c32[10 * q] = 1.0f;
+      }
+    }
+  };
+  static const Tables t;
+  return dt == C128 ? (const void*)t.c64 : dt == F64 ? (const void*)t.r64 : dt == C64 ? (const void*)t.c32 : t.r32;
+}
+
 tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tensor* A, const tci_tensor* B,
                                        const tci_tensor* gates, const tci_update_params* params,
                                        tci_tensor* A_out, tci_tensor* s_out, tci_tensor* B_out,
@@ -1359,7 +1375,6 @@ tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tens
     if (gates) {
       const int g2 = (int)(d * d * d * d);
       ARENA(Gb, char, es * (size_t)g2 * nb);
-      std::vector<char> host;   // identity in the batch's dtype, for updates without a gate
       void* id_dev = nullptr;
       for (int i0 = 0; i0 < nb; i0 += PTR_TABLE) {
         const int nt = std::min(PTR_TABLE, nb - i0);
@@ -1370,15 +1385,10 @@ tci_status tci_two_site_update_batched(tci_context ctx, int nupd, const tci_tens
             continue;
           }
           if (!id_dev) {
-            host.assign(es * g2, 0);
-            for (int q = 0; q < 4; ++q) {
-              char* p0 = host.data() + es * (q * 4 + q);
-              if (dt == C128 || dt == F64) { const double one = 1.0; std::memcpy(p0, &one, 8); }
-              else { const float one = 1.0f; std::memcpy(p0, &one, 4); }
-            }
             ARENA(idb, char, es * g2);
             id_dev = idb;
-            TCI_CHECK_HIP(hipMemcpy(id_dev, host.data(), es * g2, hipMemcpyHostToDevice));
+            // on the context's stream: work queued there may still use this part of the arena
+            TCI_CHECK_HIP(hipMemcpyAsync(id_dev, identity_gate(dt), es * g2, hipMemcpyHostToDevice, s));
           }
           t.p[i] = id_dev;
         }

@@ -227,3 +227,24 @@ def test_vidal_weights_that_are_output_spectra(T, poisoned, n, max_batch):
         for x, y in ((Ao[i], want[0][i]), (s, want[1][i]), (Bo[i], want[2][i])):
             assert np.array_equal(x.numpy(), y.numpy())
         T._check(L.tci_destroy(ctx.h, own[i]), "tci_destroy")
+
+
+def test_update_without_a_gate_leaves_queued_work_alone(T):
+    """On a stream that does not wait for the default one: contractions whose operands are permuted in the context's
+    workspace are still queued when an update without a gate of its own takes the same workspace."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = T.Context(0, stream=side)
+        x, y = (T.Tensor.from_numpy(ctx, draw((2, 1024, 1024), True, i), T.C128) for i in (1, 2))
+        a, b, gate = (T.Tensor.from_numpy(ctx, z, T.C128)
+                      for z in (draw((32, 2, 32), True, 3), draw((32, 2, 32), True, 4), np.eye(4) + 0j))
+        out = T.Tensor.empty(ctx, T.C128, 1024 * 1024)
+        p = T.update_params(chi_min=1, chi_max=32)
+        want = T.contract(ctx, x, "aij", y, "alj", "il", out=out).numpy().copy()
+        for _ in range(4):
+            T.contract(ctx, x, "aij", y, "alj", "il", out=out)
+        got = T.two_site_update_batched(ctx, [a] * 2, [b] * 2, [gate, None], p)
+        assert np.array_equal(out.numpy(), want)
+        for part in got[:3]:
+            assert np.array_equal(part[0].numpy(), part[1].numpy())
+        ctx.close()
